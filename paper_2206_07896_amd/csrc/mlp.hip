@@ -1,151 +1,432 @@
 // mlp.hip -- kernels of the schedule cost model (spmd_mlp.h).
 //
-// Forward: one thread per row, the parameters staged in LDS (every lane
-// reads the same weight at the same time: LDS broadcast).  Backward: a
-// block of 64 rows keeps their inputs, activations and back-propagated
-// errors in LDS and forms its partial weight gradients with sums over its
-// rows in row order; a second kernel adds the block partials in block
-// order.  Nothing depends on scheduling, so gradients are reproducible.
+// The layers are contractions and run on the matrix cores in fp32
+// (v_mfma_f32_32x32x2f32).  That instruction is, bit for bit, the chain
+// fma(a1, b1, fma(a0, b0, c)) -- subnormals, infinities and NaN included --
+// so a layer accumulated over k = 0, 1, 2, ... rounds exactly as one FMA
+// after another would.
+//
+// Forward and choose hold the activations transposed (units down the rows of
+// the matrix product, model rows across its columns), so a layer's result is
+// the next layer's operand where it lies, with no exchange between lanes:
+// accumulator register r holds, in lanes 0-31 and 32-63, two units of the
+// model row lane % 32, and a k step of the next layer wants exactly two k per
+// column, one per half-wave.  The weights' rows are permuted (unit_of) so that
+// those two units are 2r and 2r + 1, i.e. k runs in its natural order.
+//
+// Backward contracts over the model rows instead; a chunk of rows goes through
+// LDS, where it is read with rows across lanes (the error's way back) and with
+// units across lanes (the weight gradients).
+//
+// Nothing depends on scheduling: every sum runs in a fixed order, so
+// gradients are reproducible.
 #include "common.hpp"
 #include "spmd_mlp.h"
+#include "warp32.hpp"
 
 namespace spmd {
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // any float's address
 
 constexpr int DIN = SPMD_MLP_DIN, HID = SPMD_MLP_H, NP = SPMD_MLP_NPARAM;
 constexpr int OFF_W1 = 0, OFF_B1 = DIN * HID, OFF_W2 = OFF_B1 + HID, OFF_B2 = OFF_W2 + HID * HID,
               OFF_W3 = OFF_B2 + HID, OFF_B3 = OFF_W3 + HID;
 static_assert(OFF_B3 + 1 == NP, "parameter layout");
-constexpr int MLP_ROWS = 64;  // rows per block in forward and backward
+static_assert(DIN == 12 && HID == 64, "the operand layouts below");
+constexpr int MLP_ROWS = 64;  // rows of one wave's tile (forward, choose) and of one backward chunk
 
-__device__ __forceinline__ void stage_params(float* P, const float* params) {
-    for (int i = threadIdx.x; i < NP; i += blockDim.x) P[i] = params[i];
+__device__ __forceinline__ f32x16 mfma32(float a, float b, f32x16 c) {
+    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
 }
 
-// One row: normalised inputs -> h1 (registers) -> h2 -> y.
-template <bool STORE>
-__device__ __forceinline__ float row_forward(const float* P, const float* nm, const float* xrow, uint32_t i,
-                                             uint32_t n, float* h1t, float* h2t) {
-#pragma clang fp contract(fast)
-    float xn[DIN];
-#pragma unroll
-    for (int k = 0; k < DIN; ++k) xn[k] = (xrow[k] - nm[k]) * nm[DIN + k];
-    float h1[HID];
-#pragma unroll
-    for (int j = 0; j < HID; ++j) {
-        float z = P[OFF_B1 + j];
-#pragma unroll
-        for (int k = 0; k < DIN; ++k) z += xn[k] * P[OFF_W1 + k * HID + j];
-        h1[j] = z > 0.0f ? z : 0.0f;
-        if (STORE) h1t[(uint64_t)j * n + i] = h1[j];
+// Accumulator register r of half-wave h is matrix row 8*(r/4) + 4*h + r%4.
+__device__ __forceinline__ int acc_row(int r, int h) { return 8 * (r >> 2) + 4 * h + (r & 3); }
+// The unit at matrix row m of a 32-row tile: register r holds units 2r, 2r+1.
+__device__ __forceinline__ int unit_of(int m) { return 2 * (4 * (m >> 3) + (m & 3)) + ((m >> 2) & 1); }
+
+// One model's weights as matrix operands.
+struct MlpWeights {
+    alignas(16) float a1[2][DIN / 4][64][2];   // [unit tile][k step / 2][lane][k step % 2]
+    alignas(16) float a2[2][HID / 8][64][4];   // [unit tile][k step / 4][lane][k step % 4]
+    alignas(16) float b1[2][2][16];            // [unit tile][half-wave][register]
+    alignas(16) float b2[2][2][16];
+};
+
+__device__ __forceinline__ void stage_weights(MlpWeights& S, const float* __restrict__ params) {
+    float* a1 = &S.a1[0][0][0][0];
+    for (int i = threadIdx.x; i < DIN * HID; i += blockDim.x) {
+        const int e = i & 1, lane = (i >> 1) & 63, q = (i >> 7) % (DIN / 4), t = i / (DIN / 4 * 128);
+        const int k = 2 * (2 * q + e) + (lane >> 5);
+        a1[i] = params[OFF_W1 + k * HID + 32 * t + unit_of(lane & 31)];
     }
-    float y = P[OFF_B3];
-    for (int j = 0; j < HID; ++j) {
-        float z = P[OFF_B2 + j];
+    float* a2 = &S.a2[0][0][0][0];
+    for (int i = threadIdx.x; i < HID * HID; i += blockDim.x) {
+        const int e = i & 3, lane = (i >> 2) & 63, q = (i >> 8) & 7, t = i >> 11;
+        const int k = 2 * (4 * q + e) + (lane >> 5);
+        a2[i] = params[OFF_W2 + k * HID + 32 * t + unit_of(lane & 31)];
+    }
+    if (threadIdx.x < HID) {
+        const int r = threadIdx.x & 15, h = (threadIdx.x >> 4) & 1, t = threadIdx.x >> 5;
+        S.b1[t][h][r] = params[OFF_B1 + 32 * t + 2 * r + h];
+        S.b2[t][h][r] = params[OFF_B2 + 32 * t + 2 * r + h];
+    }
+}
+
+__device__ __forceinline__ f32x16 load_bias(const float* p) {
+    f32x16 v;
 #pragma unroll
-        for (int a = 0; a < HID; ++a) z += h1[a] * P[OFF_W2 + a * HID + j];
-        const float h2 = z > 0.0f ? z : 0.0f;
-        if (STORE) h2t[(uint64_t)j * n + i] = h2;
-        y += h2 * P[OFF_W3 + j];
+    for (int q = 0; q < 4; ++q) {
+        const f32x4 b = *reinterpret_cast<const f32x4*>(p + 4 * q);
+        v[4 * q] = b.x;
+        v[4 * q + 1] = b.y;
+        v[4 * q + 2] = b.z;
+        v[4 * q + 3] = b.w;
+    }
+    return v;
+}
+
+// 64 model rows of one wave: x[t][s] is normalised input 2s + lane/32 of row
+// 32 t + lane%32.  Returns the prediction of row `lane`.  With STORE, the
+// hidden activations go to h1t/h2t (feature-major), rows row0 + 0..63 below n.
+template <bool STORE>
+__device__ __forceinline__ float forward64(const MlpWeights& S, const float* __restrict__ params,
+                                           const float (&x)[2][DIN / 2], uint32_t row0, uint32_t n, float* h1t,
+                                           float* h2t) {
+#pragma clang fp contract(fast)
+    const int lane = (int)lane64(), half = lane >> 5;
+    f32x16 h1[2][2];  // [unit tile][row tile]
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const f32x16 b = load_bias(S.b1[t][half]);
+        h1[t][0] = b;
+        h1[t][1] = b;
+#pragma unroll
+        for (int q = 0; q < DIN / 4; ++q) {
+            const f32x2 a = *reinterpret_cast<const f32x2*>(S.a1[t][q][lane]);
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+#pragma unroll
+                for (int rt = 0; rt < 2; ++rt) h1[t][rt] = mfma32(a[e], x[rt][2 * q + e], h1[t][rt]);
+        }
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                h1[t][rt][r] = fmaxf(h1[t][rt][r], 0.0f);
+                if (STORE) {
+                    const uint32_t i = row0 + 32u * rt + (lane & 31);
+                    if (i < n) h1t[(uint64_t)(32 * t + 2 * r + half) * n + i] = h1[t][rt][r];
+                }
+            }
+    }
+    float y = params[OFF_B3];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const f32x16 b = load_bias(S.b2[t][half]);
+        f32x16 h2[2] = {b, b};
+#pragma unroll
+        for (int q = 0; q < HID / 8; ++q) {
+            const f32x4 a = *reinterpret_cast<const f32x4*>(S.a2[t][q][lane]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int s = 4 * q + e;  // units 2s and 2s + 1 of the first layer
+#pragma unroll
+                for (int rt = 0; rt < 2; ++rt) h2[rt] = mfma32(a[e], h1[s >> 4][rt][s & 15], h2[rt]);
+            }
+        }
+        // Exchanging halves puts one unit of all 64 rows into a register
+        // (row = lane), and the last layer's sum runs over the units in order.
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const float v0 = fmaxf(h2[0][r], 0.0f), v1 = fmaxf(h2[1][r], 0.0f);
+            const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(v0), __float_as_uint(v1), false, false);
+            const float u0 = __uint_as_float(sw[0]), u1 = __uint_as_float(sw[1]);
+            const int j = 32 * t + 2 * r;
+            if (STORE) {
+                const uint32_t i = row0 + lane;
+                if (i < n) {
+                    h2t[(uint64_t)j * n + i] = u0;
+                    h2t[(uint64_t)(j + 1) * n + i] = u1;
+                }
+            }
+            y += u0 * params[OFF_W3 + j];
+            y += u1 * params[OFF_W3 + j + 1];
+        }
     }
     return y;
 }
 
-__global__ __launch_bounds__(MLP_ROWS) void mlp_forward_kernel(const float* __restrict__ params,
-                                                               const float* __restrict__ norm,
-                                                               const float* __restrict__ x, uint32_t n,
-                                                               float* __restrict__ y, float* h1t, float* h2t) {
-    __shared__ float P[NP];
-    __shared__ float nm[2 * DIN];
-    stage_params(P, params);
-    if (threadIdx.x < 2 * DIN) nm[threadIdx.x] = norm[threadIdx.x];
+// A wave per 64 rows, four to a block.  STORE: also the activations.  Bound by
+// the matrix cores (152 of their 64-cycle steps per 64 rows, 4 us) behind the
+// start of the launch and the staging of the weights: 60 000 rows with stores
+// 20.1 us, against 49.8 us with a thread per row on the vector unit.
+template <bool STORE>
+__global__ __launch_bounds__(256) void mlp_forward_kernel(const float* __restrict__ params,
+                                                          const float* __restrict__ norm,
+                                                          const float* __restrict__ x, uint32_t n,
+                                                          float* __restrict__ y, float* h1t, float* h2t) {
+    __shared__ MlpWeights S;
+    stage_weights(S, params);
+    const int lane = (int)lane64(), half = lane >> 5;
+    const uint32_t row0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * MLP_ROWS;
+    float xn[2][DIN / 2];
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt) {
+        const uint32_t i = row0 + 32u * rt + (lane & 31);
+        const float* xr = x + (uint64_t)(i < n ? i : n - 1) * DIN;  // past the end: the last row, not stored
+#pragma unroll
+        for (int s = 0; s < DIN / 2; ++s) xn[rt][s] = (xr[2 * s + half] - norm[2 * s + half]) * norm[DIN + 2 * s + half];
+    }
     __syncthreads();
-    const uint32_t i = blockIdx.x * MLP_ROWS + threadIdx.x;
-    if (i >= n) return;
-    const float* xrow = x + (uint64_t)i * DIN;
-    y[i] = h1t ? row_forward<true>(P, nm, xrow, i, n, h1t, h2t) : row_forward<false>(P, nm, xrow, i, n, h1t, h2t);
+    if (row0 >= n) return;
+    const float v = forward64<STORE>(S, params, xn, row0, n, h1t, h2t);
+    if (row0 + lane < n) y[row0 + lane] = v;
 }
 
-// Block partials: part[b * (NP + 1) + p] for parameter p, the block's sum
-// of squared errors at p = NP.
-__global__ __launch_bounds__(MLP_ROWS) void mlp_backward_kernel(
+// ---- backward ----
+//
+// A block of four waves takes chunks of 64 rows (block b: chunks b, b + G, ...)
+// and keeps its partial gradients in accumulators over all of them.  Per chunk:
+//   stage   h1, h2 (unit-major), the normalised inputs and dy = 2 (y - t) / n
+//           go to LDS; the next chunk's loads are in flight meanwhile;
+//   back    d1 = (W2 d2) where h1 > 0, d2 = dy w3 where h2 > 0: a wave owns
+//           32 units x 32 rows;
+//   grads   dW2 = h1 d2^T: a wave owns one 32 x 32 tile of it, over the
+//           chunk's rows; dW1 = xn d1^T with a row of ones below xn (its
+//           product is db1): a wave takes 16 of the rows, and the four are
+//           added at the end; db2 and dw3 as a unit's sums per lane.
+// LDS rows are 68 floats, so 16-byte reads with one unit per lane hit all
+// banks evenly.  60 000 rows: 28.3 us and 5.7 us for the sum of the partials;
+// with a thread per row and each weight's sum over its rows serial in one
+// thread it took 387 us, and one thread per parameter adding the 938 partials of
+// 64 rows 220 us.  Block partials go to the workspace, part[b * (NP + 1) + p]
+// for parameter p and the sum of squared errors at p = NP.
+constexpr int BW_LD = MLP_ROWS + 4;
+constexpr int BW_XROWS = DIN + 2;         // inputs, ones, zeros
+// Two blocks per CU.  60 000 rows: 938 chunks.
+constexpr uint32_t BW_MAX_BLOCKS = 512;
+
+__host__ __device__ inline uint32_t bw_blocks(uint32_t n) {
+    const uint32_t chunks = (n + MLP_ROWS - 1) / MLP_ROWS;
+    return chunks < BW_MAX_BLOCKS ? chunks : BW_MAX_BLOCKS;
+}
+
+struct BackwardLds {
+    alignas(16) float w2[2][HID / 8][64][4];  // A operand: W2[32 t + lane%32][2 (4q + e) + lane/32]
+    alignas(16) float h1[HID][BW_LD];
+    alignas(16) float h2[HID][BW_LD];
+    alignas(16) float d1[HID][BW_LD];
+    alignas(16) float xs[BW_XROWS][BW_LD];
+    alignas(16) float dy[MLP_ROWS];
+    float w3[HID];
+};
+static_assert(sizeof(float) * 4 * (DIN + 1) * HID <= sizeof(float) * HID * BW_LD, "dW1 partials fit the h1 area");
+
+// Four consecutive rows of a unit's activations, zero past n.
+__device__ __forceinline__ f32x4 load_rows4(const float* __restrict__ p, uint32_t i, uint32_t n) {
+    if (i + 4 <= n) return *reinterpret_cast<const f32x4u*>(p + i);
+    f32x4 v = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        if (i + e < n) v[e] = p[i + e];
+    return v;
+}
+
+__global__ __launch_bounds__(256, 2) void mlp_backward_kernel(
     const float* __restrict__ params, const float* __restrict__ norm, const float* __restrict__ x,
     const float* __restrict__ t, uint32_t n, const float* __restrict__ y, const float* __restrict__ h1t,
     const float* __restrict__ h2t, float* __restrict__ part) {
-#pragma clang fp contract(fast)
-    __shared__ float W2[HID * HID];
-    __shared__ float w3[HID];
-    __shared__ float xs[MLP_ROWS][DIN];
-    __shared__ float h1s[MLP_ROWS][HID + 1];
-    __shared__ float h2s[MLP_ROWS][HID + 1];
-    __shared__ float d2s[MLP_ROWS][HID + 1];
-    __shared__ float d1s[MLP_ROWS][HID + 1];
-    __shared__ float dys[MLP_ROWS];
-    __shared__ float e2s[MLP_ROWS];
-    const uint32_t r = threadIdx.x;
-    for (int q = r; q < HID * HID; q += MLP_ROWS) W2[q] = params[OFF_W2 + q];
-    w3[r] = params[OFF_W3 + r];
-    __syncthreads();
-    const uint32_t i = blockIdx.x * MLP_ROWS + r;
-    const bool ok = i < n;
-    const float err = ok ? y[i] - t[i] : 0.0f;
-    const float dy = 2.0f * err / (float)n;
-    dys[r] = dy;
-    e2s[r] = err * err;
-#pragma unroll
-    for (int k = 0; k < DIN; ++k) xs[r][k] = ok ? (x[(uint64_t)i * DIN + k] - norm[k]) * norm[DIN + k] : 0.0f;
-    float d2[HID];
-#pragma unroll
-    for (int j = 0; j < HID; ++j) {
-        const float h1 = ok ? h1t[(uint64_t)j * n + i] : 0.0f;
-        const float h2 = ok ? h2t[(uint64_t)j * n + i] : 0.0f;
-        h1s[r][j] = h1;
-        h2s[r][j] = h2;
-        d2[j] = h2 > 0.0f ? dy * w3[j] : 0.0f;
-        d2s[r][j] = d2[j];
+    __shared__ BackwardLds L;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5, l32 = lane & 31;
+    const uint32_t chunks = (n + MLP_ROWS - 1) / MLP_ROWS;
+    float* w2 = &L.w2[0][0][0][0];
+    for (int i = tid; i < HID * HID; i += 256) {
+        const int e = i & 3, ln = (i >> 2) & 63, q = (i >> 8) & 7, tt = i >> 11;
+        w2[i] = params[OFF_W2 + (32 * tt + (ln & 31)) * HID + 2 * (4 * q + e) + (ln >> 5)];
     }
-    for (int a = 0; a < HID; ++a) {
-        float s = 0.0f;
-#pragma unroll
-        for (int j = 0; j < HID; ++j) s += d2[j] * W2[a * HID + j];
-        d1s[r][a] = h1s[r][a] > 0.0f ? s : 0.0f;
+    if (tid < HID) L.w3[tid] = params[OFF_W3 + tid];
+    if (tid < BW_LD) {
+        L.xs[DIN][tid] = 1.0f;
+        L.xs[DIN + 1][tid] = 0.0f;
     }
-    __syncthreads();
-    float* out = part + (uint64_t)blockIdx.x * (NP + 1);
-    for (int p = r; p <= NP; p += MLP_ROWS) {
-        float s = 0.0f;
-        if (p < OFF_B1) {  // W1[k][a]
-            const int k = p / HID, a = p % HID;
-            for (int q = 0; q < MLP_ROWS; ++q) s += xs[q][k] * d1s[q][a];
-        } else if (p < OFF_W2) {
-            const int a = p - OFF_B1;
-            for (int q = 0; q < MLP_ROWS; ++q) s += d1s[q][a];
-        } else if (p < OFF_B2) {  // W2[a][j]
-            const int a = (p - OFF_W2) / HID, j = (p - OFF_W2) % HID;
-            for (int q = 0; q < MLP_ROWS; ++q) s += h1s[q][a] * d2s[q][j];
-        } else if (p < OFF_W3) {
-            const int j = p - OFF_B2;
-            for (int q = 0; q < MLP_ROWS; ++q) s += d2s[q][j];
-        } else if (p < OFF_B3) {
-            const int j = p - OFF_W3;
-            for (int q = 0; q < MLP_ROWS; ++q) s += dys[q] * h2s[q][j];
-        } else if (p == OFF_B3) {
-            for (int q = 0; q < MLP_ROWS; ++q) s += dys[q];
-        } else {
-            for (int q = 0; q < MLP_ROWS; ++q) s += e2s[q];
+
+    // Thread's share of a chunk: rows 4 (tid % 16) .. + 3 of units tid / 16 + 16 q.
+    f32x4 p1[4], p2[4], px;
+    float py = 0.0f, pt = 0.0f;
+    auto load = [&](uint32_t c) {
+        const uint32_t i = c * MLP_ROWS + 4 * (tid & 15);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            p1[q] = load_rows4(h1t + (uint64_t)(16 * q + (tid >> 4)) * n, i, n);
+            p2[q] = load_rows4(h2t + (uint64_t)(16 * q + (tid >> 4)) * n, i, n);
         }
-        out[p] = s;
+        px = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        if (tid < MLP_ROWS * DIN / 4) {
+            const uint32_t r = c * MLP_ROWS + tid / (DIN / 4);
+            if (r < n) px = *reinterpret_cast<const f32x4u*>(x + (uint64_t)r * DIN + 4 * (tid % (DIN / 4)));
+        }
+        if (tid < MLP_ROWS) {
+            const uint32_t r = c * MLP_ROWS + tid;
+            py = r < n ? y[r] : 0.0f;
+            pt = r < n ? t[r] : 0.0f;
+        }
+    };
+    float nmu[4], nsd[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        nmu[e] = norm[4 * (tid % (DIN / 4)) + e];
+        nsd[e] = norm[DIN + 4 * (tid % (DIN / 4)) + e];
     }
+
+    const int ta = wave >> 1, tj = wave & 1;  // this wave's tile of dW2, and of d1 (units, rows)
+    f32x16 g2, g1[2];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) g2[r] = g1[0][r] = g1[1][r] = 0.0f;
+    float gb2 = 0.0f, gw3 = 0.0f, gb3 = 0.0f, e2 = 0.0f;
+    uint32_t c = blockIdx.x;
+    load(c);
+    for (; c < chunks; c += gridDim.x) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            *reinterpret_cast<f32x4*>(&L.h1[16 * q + (tid >> 4)][4 * (tid & 15)]) = p1[q];
+            *reinterpret_cast<f32x4*>(&L.h2[16 * q + (tid >> 4)][4 * (tid & 15)]) = p2[q];
+        }
+        if (tid < MLP_ROWS * DIN / 4) {
+            const int r = tid / (DIN / 4), k = 4 * (tid % (DIN / 4));
+            const bool in = c * MLP_ROWS + r < n;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) L.xs[k + e][r] = in ? (px[e] - nmu[e]) * nsd[e] : 0.0f;
+        }
+        if (tid < MLP_ROWS) {
+            const float err = py - pt;
+            const float dy = 2.0f * err / (float)n;
+            L.dy[tid] = dy;
+            gb3 += dy;
+            e2 += err * err;
+        }
+        __syncthreads();
+        if (c + gridDim.x < chunks) load(c + gridDim.x);
+
+        {  // d1, units 32 ta .. + 31 of rows 32 tj .. + 31
+            f32x16 acc;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+            const int row = 32 * tj + l32;
+            const float dy = L.dy[row];
+#pragma unroll
+            for (int q = 0; q < HID / 8; ++q) {
+                const f32x4 a = *reinterpret_cast<const f32x4*>(L.w2[ta][q][lane]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int j = 2 * (4 * q + e) + half;
+                    acc = mfma32(a[e], L.h2[j][row] > 0.0f ? dy * L.w3[j] : 0.0f, acc);
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int a = 32 * ta + acc_row(r, half);
+                L.d1[a][row] = L.h1[a][row] > 0.0f ? acc[r] : 0.0f;
+            }
+        }
+        // dW2 needs no d1: it runs before the barrier
+        {
+            const float w3 = L.w3[32 * tj + l32];
+#pragma unroll
+            for (int q = 0; q < MLP_ROWS / 8; ++q) {
+                const int row = 8 * q + 4 * half;  // k steps take rows 8q + e and 8q + 4 + e
+                const f32x4 a = *reinterpret_cast<const f32x4*>(&L.h1[32 * ta + l32][row]);
+                const f32x4 h = *reinterpret_cast<const f32x4*>(&L.h2[32 * tj + l32][row]);
+                const f32x4 dy = *reinterpret_cast<const f32x4*>(&L.dy[row]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float d2 = h[e] > 0.0f ? dy[e] * w3 : 0.0f;
+                    g2 = mfma32(a[e], d2, g2);
+                    gb2 += d2;
+                    gw3 += dy[e] * h[e];
+                }
+            }
+        }
+        __syncthreads();
+        const int xr = l32 < DIN + 1 ? l32 : DIN + 1;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int row = 16 * wave + 8 * q + 4 * half;
+            const f32x4 a = *reinterpret_cast<const f32x4*>(&L.xs[xr][row]);
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const f32x4 d = *reinterpret_cast<const f32x4*>(&L.d1[32 * u + l32][row]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) g1[u] = mfma32(a[e], d[e], g1[u]);
+            }
+        }
+        __syncthreads();  // the next chunk reuses the LDS
+    }
+
+    float* out = part + (uint64_t)blockIdx.x * (NP + 1);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) out[OFF_W2 + (32 * ta + acc_row(r, half)) * HID + 32 * tj + l32] = g2[r];
+    gb2 += __shfl_xor(gb2, 32);
+    gw3 += __shfl_xor(gw3, 32);
+    if (ta == 0 && half == 0) {
+        out[OFF_B2 + 32 * tj + l32] = gb2;
+        out[OFF_W3 + 32 * tj + l32] = gw3;
+    }
+    if (wave == 0) {
+#pragma unroll
+        for (int m = 1; m < 64; m <<= 1) {
+            gb3 += __shfl_xor(gb3, m);
+            e2 += __shfl_xor(e2, m);
+        }
+        if (lane == 0) {
+            out[OFF_B3] = gb3;
+            out[NP] = e2;
+        }
+    }
+    float* w1 = &L.h1[0][0];  // [wave][input or ones][unit]
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int m = acc_row(r, half);
+            if (m <= DIN) w1[(wave * (DIN + 1) + m) * HID + 32 * u + l32] = g1[u][r];
+        }
+    __syncthreads();
+    for (int i = tid; i < (DIN + 1) * HID; i += 256)  // W1, then b1 right after it
+        out[i] = ((w1[i] + w1[(DIN + 1) * HID + i]) + w1[2 * (DIN + 1) * HID + i]) + w1[3 * (DIN + 1) * HID + i];
 }
 
-__global__ __launch_bounds__(256) void mlp_reduce_kernel(const float* __restrict__ part, uint32_t nblocks,
-                                                         uint32_t n, float* __restrict__ grad,
-                                                         float* __restrict__ loss) {
-    const int p = blockIdx.x * 256 + threadIdx.x;
-    if (p > NP) return;
+// Sum of the block partials: 64 parameters per block, 16 waves each adding
+// every 16th partial (their loads independent of each other), then the waves'
+// sums in wave order.
+__global__ __launch_bounds__(1024) void mlp_reduce_kernel(const float* __restrict__ part, uint32_t nblocks,
+                                                          uint32_t n, float* __restrict__ grad,
+                                                          float* __restrict__ loss) {
+    __shared__ float sums[16][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int p = blockIdx.x * 64 + lane;
     float s = 0.0f;
-    for (uint32_t b = 0; b < nblocks; ++b) s += part[(uint64_t)b * (NP + 1) + p];
-    if (p < NP) grad[p] = s;
-    else *loss = s / (float)n;
+    if (p <= NP) {
+        uint32_t b = wave;
+        for (; b + 112 < nblocks; b += 128) {
+            float v[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] = part[(uint64_t)(b + 16 * q) * (NP + 1) + p];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) s += v[q];
+        }
+        for (; b < nblocks; b += 16) s += part[(uint64_t)b * (NP + 1) + p];
+    }
+    sums[wave][lane] = s;
+    __syncthreads();
+    if (wave == 0 && p <= NP) {
+        float v = 0.0f;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) v += sums[w][lane];
+        if (p < NP) grad[p] = v;
+        else *loss = v / (float)n;
+    }
 }
 
 __global__ __launch_bounds__(256) void mlp_adam_kernel(float* __restrict__ p, const float* __restrict__ g,
@@ -161,100 +442,173 @@ __global__ __launch_bounds__(256) void mlp_adam_kernel(float* __restrict__ p, co
     p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
 }
 
-// One launch per loop iteration of a block; thread j evaluates candidate j
-// under every model.
-__global__ __launch_bounds__(SPMD_MLP_MAX_CANDS) void mlp_choose_kernel(
+// ---- choose ----
+//
+// A block owns a contiguous share of the launches and takes them up to 16 at a
+// time: the valid (launch, candidate) pairs of the group are packed into one
+// list (in any order: a pair's prediction does not depend on its place), the
+// waves evaluate the list 64 pairs at a time under every model, and a wave per
+// launch then picks the least mean.  Packing is what keeps the matrix cores on
+// real pairs: 96 to 144 of 144 candidates are valid by class, and a launch alone
+// would fill its last 64-row tile by a quarter to a half.  Bound by the matrix
+// cores: 10 000 launches of 144 candidates under 3 models, 335 us (106 TFLOP/s of
+// the valid pairs), against 4260 us with a thread per candidate on the vector
+// unit; the predictions are the same bits.
+constexpr int CH_GROUP = 16, CH_THREADS = 512, CH_WAVES = CH_THREADS / 64;
+constexpr int CH_CANDS = SPMD_MLP_MAX_CANDS;
+constexpr uint32_t CH_MAX_BLOCKS = 256;  // one per CU: two waves per SIMD
+
+struct ChooseLds {
+    float mean[CH_GROUP][CH_CANDS];
+    float sd[CH_GROUP][CH_CANDS];
+    uint16_t list[CH_GROUP * CH_CANDS];  // launch of the group * CH_CANDS + candidate
+    uint32_t rows;
+    // followed by MlpWeights[k_models]
+};
+static_assert(CH_CANDS == 256 && sizeof(ChooseLds) % 4 == 0, "tree shape and LDS layout");
+constexpr size_t CH_WEIGHTS_OFF = (sizeof(ChooseLds) + 15) / 16 * 16;
+
+__global__ __launch_bounds__(CH_THREADS) void mlp_choose_kernel(
     const float* __restrict__ params, uint32_t k_models, const float* __restrict__ norm,
     const float* __restrict__ feats, uint32_t m, const float* __restrict__ cands, uint32_t c,
     const uint8_t* __restrict__ valid, const uint32_t* __restrict__ chunks, float log_slack,
     uint32_t* __restrict__ best, float* __restrict__ best_pred, float* __restrict__ best_sd) {
-    extern __shared__ float P[];  // k_models * NP
-    __shared__ float nm[2 * DIN];
-    __shared__ float red_v[SPMD_MLP_MAX_CANDS];
-    __shared__ uint32_t red_i[SPMD_MLP_MAX_CANDS];
-    __shared__ float red_s[SPMD_MLP_MAX_CANDS];
-    __shared__ uint32_t red_c[SPMD_MLP_MAX_CANDS];
-    for (uint32_t q = threadIdx.x; q < k_models * NP; q += blockDim.x) P[q] = params[q];
-    if (threadIdx.x < 2 * DIN) nm[threadIdx.x] = norm[threadIdx.x];
-    __syncthreads();
-    const uint32_t j = threadIdx.x;
-    for (uint32_t li = blockIdx.x; li < m; li += gridDim.x) {
-        float mean = INFINITY, sd = 0.0f;
-        const bool ok = j < c && valid[(uint64_t)li * c + j] != 0;
-        if (ok) {
-            float xrow[DIN];
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    ChooseLds& L = *reinterpret_cast<ChooseLds*>(smem);
+    MlpWeights* W = reinterpret_cast<MlpWeights*>(smem + CH_WEIGHTS_OFF);
+    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    for (uint32_t k = 0; k < k_models; ++k) stage_weights(W[k], params + k * NP);
+    float nmu[DIN / 2], nsd[DIN / 2];
 #pragma unroll
-            for (int q = 0; q < SPMD_MLP_NFEAT; ++q) xrow[q] = feats[(uint64_t)li * SPMD_MLP_NFEAT + q];
+    for (int s = 0; s < DIN / 2; ++s) {
+        nmu[s] = norm[2 * s + half];
+        nsd[s] = norm[DIN + 2 * s + half];
+    }
+    const uint32_t lo = (uint32_t)((uint64_t)m * blockIdx.x / gridDim.x);
+    const uint32_t hi = (uint32_t)((uint64_t)m * (blockIdx.x + 1) / gridDim.x);
+    for (uint32_t l0 = lo; l0 < hi; l0 += CH_GROUP) {
+        const uint32_t nl = hi - l0 < CH_GROUP ? hi - l0 : CH_GROUP;
+        if (tid == 0) L.rows = 0;
+        __syncthreads();
+        for (uint32_t g = wave; g < nl; g += CH_WAVES)
 #pragma unroll
-            for (int q = 0; q < SPMD_MLP_NSCHED; ++q) xrow[SPMD_MLP_NFEAT + q] = cands[j * SPMD_MLP_NSCHED + q];
+            for (int q = 0; q < CH_CANDS / 64; ++q) {
+                const uint32_t j = 64 * q + lane;
+                const bool ok = j < c && valid[(uint64_t)(l0 + g) * c + j] != 0;
+                const uint64_t mask = __builtin_amdgcn_ballot_w64(ok);
+                uint32_t at = 0;
+                if (lane == 0) at = atomicAdd(&L.rows, (uint32_t)__builtin_popcountll(mask));
+                at = __builtin_amdgcn_readfirstlane(at);
+                const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+                if (ok) L.list[at + below] = (uint16_t)(g * CH_CANDS + j);
+            }
+        __syncthreads();
+        const uint32_t rows = L.rows;
+        for (uint32_t r0 = wave * MLP_ROWS; r0 < rows; r0 += CH_WAVES * MLP_ROWS) {
+            float xn[2][DIN / 2];
+#pragma unroll
+            for (int rt = 0; rt < 2; ++rt) {
+                const uint32_t i = r0 + 32 * rt + (lane & 31);
+                const uint32_t id = L.list[i < rows ? i : rows - 1];  // past the end: evaluated, not kept
+                const float* f = feats + (uint64_t)(l0 + id / CH_CANDS) * SPMD_MLP_NFEAT;
+                const float* s3 = cands + (id % CH_CANDS) * SPMD_MLP_NSCHED;
+#pragma unroll
+                for (int s = 0; s < DIN / 2; ++s) {
+                    const int k = 2 * s + half;
+                    const float v = k < SPMD_MLP_NFEAT ? f[k] : s3[k - SPMD_MLP_NFEAT];
+                    xn[rt][s] = (v - nmu[s]) * nsd[s];
+                }
+            }
             // two passes (mean, then squared deviations): the spread of
             // nearly equal predictions keeps its precision
             float pr[SPMD_MLP_MAX_MODELS];
             float s1 = 0.0f;
 #pragma unroll
             for (uint32_t mk = 0; mk < SPMD_MLP_MAX_MODELS; ++mk) {
-                pr[mk] = mk < k_models ? row_forward<false>(P + mk * NP, nm, xrow, 0, 0, nullptr, nullptr) : 0.0f;
+                pr[mk] = mk < k_models ? forward64<false>(W[mk], params + mk * NP, xn, 0, 0, nullptr, nullptr) : 0.0f;
                 s1 += pr[mk];
             }
-            mean = s1 / (float)k_models;
+            const float mean = s1 / (float)k_models;
             float s2 = 0.0f;
 #pragma unroll
             for (uint32_t mk = 0; mk < SPMD_MLP_MAX_MODELS; ++mk) {
                 const float d = pr[mk] - mean;
                 s2 += mk < k_models ? d * d : 0.0f;
             }
-            sd = sqrtf(s2 / (float)k_models);
-        }
-        red_v[j] = mean;
-        red_i[j] = ok ? j : 0xFFFFFFFFu;
-        red_s[j] = sd;
-        __syncthreads();
-        for (uint32_t w = blockDim.x / 2; w > 0; w >>= 1) {
-            if (j < w) {
-                const float a = red_v[j], b = red_v[j + w];
-                const uint32_t ia = red_i[j], ib = red_i[j + w];
-                // smaller mean wins; equal means go to the lower index
-                if (b < a || (b == a && ib < ia)) {
-                    red_v[j] = b;
-                    red_i[j] = ib;
-                    red_s[j] = red_s[j + w];
-                }
-            }
-            __syncthreads();
-        }
-        if (chunks) {
-            // Batch-aware second pass: among the candidates whose mean is
-            // within log_slack of the least, the fewest chunks wins (then
-            // the smaller mean, then the lower index).
-            const float thr = red_v[0] + log_slack;
-            __syncthreads();  // every thread has read red_v[0]
-            const bool near = ok && mean <= thr;
-            red_c[j] = near ? chunks[(uint64_t)li * c + j] : 0xFFFFFFFFu;
-            red_v[j] = near ? mean : INFINITY;
-            red_i[j] = near ? j : 0xFFFFFFFFu;
-            red_s[j] = sd;
-            __syncthreads();
-            for (uint32_t w = blockDim.x / 2; w > 0; w >>= 1) {
-                if (j < w) {
-                    const uint32_t ca = red_c[j], cb = red_c[j + w];
-                    const float a = red_v[j], b = red_v[j + w];
-                    const uint32_t ia = red_i[j], ib = red_i[j + w];
-                    if (cb < ca || (cb == ca && (b < a || (b == a && ib < ia)))) {
-                        red_c[j] = cb;
-                        red_v[j] = b;
-                        red_i[j] = ib;
-                        red_s[j] = red_s[j + w];
-                    }
-                }
-                __syncthreads();
+            if (r0 + lane < rows) {
+                const uint32_t id = L.list[r0 + lane];
+                (&L.mean[0][0])[id] = mean;
+                (&L.sd[0][0])[id] = sqrtf(s2 / (float)k_models);
             }
         }
-        if (j == 0) {
-            best[li] = red_i[0];
-            best_pred[li] = red_v[0];
-            best_sd[li] = red_s[0];
-        }
         __syncthreads();
+        for (uint32_t g = wave; g < nl; g += CH_WAVES) {
+            // candidate 64 q + lane in slot q; the tree halves 256 places
+            float v[4], sd[4];
+            uint32_t id[4], ch[4];
+            bool ok[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const uint32_t j = 64 * q + lane;
+                ok[q] = j < c && valid[(uint64_t)(l0 + g) * c + j] != 0;
+                v[q] = ok[q] ? L.mean[g][j] : INFINITY;
+                sd[q] = ok[q] ? L.sd[g][j] : 0.0f;
+                id[q] = ok[q] ? j : 0xFFFFFFFFu;
+                ch[q] = 0;
+            }
+            // a place keeps itself unless the other has fewer chunks, or as
+            // many and a smaller mean, or that too and a lower index (in the
+            // first pass every chunk count is 0); selects, no branches
+            auto take = [](uint32_t& ca, float& a, uint32_t& ia, float& sa, uint32_t cb, float b, uint32_t ib, float sb) {
+                const bool other = (cb < ca) | ((cb == ca) & ((b < a) | ((b == a) & (ib < ia))));
+                ca = other ? cb : ca;
+                a = other ? b : a;
+                ia = other ? ib : ia;
+                sa = other ? sb : sa;
+            };
+            auto tree = [&](uint32_t (&tc)[4], float (&tv)[4], uint32_t (&ti)[4], float (&ts)[4]) {
+                take(tc[0], tv[0], ti[0], ts[0], tc[2], tv[2], ti[2], ts[2]);
+                take(tc[1], tv[1], ti[1], ts[1], tc[3], tv[3], ti[3], ts[3]);
+                take(tc[0], tv[0], ti[0], ts[0], tc[1], tv[1], ti[1], ts[1]);
+                for (int w = 32; w > 0; w >>= 1)
+                    take(tc[0], tv[0], ti[0], ts[0], __shfl_down(tc[0], w), __shfl_down(tv[0], w),
+                         __shfl_down(ti[0], w), __shfl_down(ts[0], w));
+            };
+            float tv[4], ts[4];
+            uint32_t ti[4], tc[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                tv[q] = v[q];
+                ts[q] = sd[q];
+                ti[q] = id[q];
+                tc[q] = 0;
+            }
+            tree(tc, tv, ti, ts);
+            if (chunks) {
+                // Batch-aware second pass: among the candidates whose mean is
+                // within log_slack of the least, the fewest chunks wins (then
+                // the smaller mean, then the lower index).
+                const float thr = __shfl(tv[0], 0) + log_slack;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const uint32_t j = 64 * q + lane;
+                    const bool near = ok[q] && v[q] <= thr;
+                    tc[q] = near ? chunks[(uint64_t)(l0 + g) * c + j] : 0xFFFFFFFFu;
+                    tv[q] = near ? v[q] : INFINITY;
+                    ti[q] = near ? j : 0xFFFFFFFFu;
+                    ts[q] = sd[q];
+                }
+                tree(tc, tv, ti, ts);
+            }
+            if (lane == 0) {
+                best[l0 + g] = ti[0];
+                best_pred[l0 + g] = tv[0];
+                best_sd[l0 + g] = ts[0];
+            }
+        }
+        __syncthreads();  // the next group reuses the LDS
     }
 }
 
@@ -275,8 +629,10 @@ int spmd_mlp_forward(const float* params, const float* norm, const float* x, uin
     if (!params || !norm || (n && (!x || !y)) || (!h1t) != (!h2t)) return SPMD_ERR_ARGS;
     if (!n) return SPMD_OK;
     clear_stale_error();
-    hipLaunchKernelGGL(mlp_forward_kernel, dim3((n + MLP_ROWS - 1) / MLP_ROWS), dim3(MLP_ROWS), 0,
-                       static_cast<hipStream_t>(stream), params, norm, x, n, y, h1t, h2t);
+    const dim3 g((uint32_t)(((uint64_t)n + 4 * MLP_ROWS - 1) / (4 * MLP_ROWS))), b(256);
+    const hipStream_t s = static_cast<hipStream_t>(stream);
+    if (h1t) hipLaunchKernelGGL(mlp_forward_kernel<true>, g, b, 0, s, params, norm, x, n, y, h1t, h2t);
+    else hipLaunchKernelGGL(mlp_forward_kernel<false>, g, b, 0, s, params, norm, x, n, y, h1t, h2t);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? SPMD_OK : hip_fail(e);
 }
@@ -291,12 +647,12 @@ int spmd_mlp_backward(const float* params, const float* norm, const float* x, co
                       size_t ws_bytes, void* stream) {
     if (!params || !norm || !x || !t || !y || !h1t || !h2t || !grad || !loss || n == 0) return SPMD_ERR_ARGS;
     if (!workspace || ws_bytes < spmd_mlp_workspace_size(n)) return SPMD_ERR_WORKSPACE;
-    const uint32_t nb = (n + MLP_ROWS - 1) / MLP_ROWS;
+    const uint32_t nb = bw_blocks(n);
     hipStream_t s = static_cast<hipStream_t>(stream);
     float* part = static_cast<float*>(workspace);
     clear_stale_error();
-    hipLaunchKernelGGL(mlp_backward_kernel, dim3(nb), dim3(MLP_ROWS), 0, s, params, norm, x, t, n, y, h1t, h2t, part);
-    hipLaunchKernelGGL(mlp_reduce_kernel, dim3((NP + 1 + 255) / 256), dim3(256), 0, s, part, nb, n, grad, loss);
+    hipLaunchKernelGGL(mlp_backward_kernel, dim3(nb), dim3(256), 0, s, params, norm, x, t, n, y, h1t, h2t, part);
+    hipLaunchKernelGGL(mlp_reduce_kernel, dim3((NP + 1 + 63) / 64), dim3(1024), 0, s, part, nb, n, grad, loss);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? SPMD_OK : hip_fail(e);
 }
@@ -338,15 +694,15 @@ int choose_impl(const float* params, uint32_t k_models, const float* norm, const
     if (c == 0 || c > SPMD_MLP_MAX_CANDS || !cands) return SPMD_ERR_ARGS;
     if (m && (!feats || !valid || !best || !best_pred || !best_sd)) return SPMD_ERR_ARGS;
     if (!m) return SPMD_OK;
-    const size_t shm = (size_t)k_models * NP * sizeof(float);
-    if (shm > 65536) {  // up to 4 models: 81 KB of the 160 KB LDS, opted in explicitly
+    const size_t shm = CH_WEIGHTS_OFF + (size_t)k_models * sizeof(MlpWeights);
+    if (shm > 65536) {  // up to 4 models: 121 KB of the 160 KB LDS, opted in explicitly
         hipError_t ea = hipFuncSetAttribute(reinterpret_cast<const void*>(&mlp_choose_kernel),
                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
         if (ea != hipSuccess) return hip_fail(ea);
     }
-    const uint32_t grid = m < 1024 ? m : 1024;
+    const uint32_t grid = m < CH_MAX_BLOCKS ? m : CH_MAX_BLOCKS;
     clear_stale_error();
-    hipLaunchKernelGGL(mlp_choose_kernel, dim3(grid), dim3(SPMD_MLP_MAX_CANDS), shm, static_cast<hipStream_t>(stream),
+    hipLaunchKernelGGL(mlp_choose_kernel, dim3(grid), dim3(CH_THREADS), shm, static_cast<hipStream_t>(stream),
                        params, k_models, norm, feats, m, cands, c, valid, chunks, log_slack, best, best_pred,
                        best_sd);
     hipError_t e = hipGetLastError();

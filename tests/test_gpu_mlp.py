@@ -346,3 +346,60 @@ def test_choose_batch_matches_oracle(L, slack):
                 assert j == ob[i], i
                 strict += 1
     assert strict > m // 2
+
+
+@pytest.mark.parametrize("n", [65, 255, 257, 64 * 512 + 1])
+def test_training_kernels_at_tile_edges(L, n):
+    """Row counts around the forward block (256 rows), the backward chunk (64)
+    and the chunk after the last block's first (512 blocks)."""
+    import torch
+
+    say("mlp tile edges", n)
+    X, t, p, mu, inv_sd = _problem(n, 300 + n)
+    dp, dn, dx, dt = cuda(p), cuda(np.concatenate([mu, inv_sd])), cuda(X), cuda(t)
+    y, h1, h2 = _fwd(L, dp, dn, dx)
+    ws = torch.full((int(L._lib.spmd_mlp_workspace_size(n)),), 0xFF, dtype=torch.uint8, device="cuda")
+    g = torch.empty(omlp.NPARAM, dtype=torch.float32, device="cuda")
+    loss = torch.empty(1, dtype=torch.float32, device="cuda")
+    ok(L._lib.spmd_mlp_backward(dp.data_ptr(), dn.data_ptr(), dx.data_ptr(), dt.data_ptr(), n, y.data_ptr(),
+                                h1.data_ptr(), h2.data_ptr(), g.data_ptr(), loss.data_ptr(), ws.data_ptr(),
+                                ws.numel(), None), "spmd_mlp_backward")
+    args = (p.astype(np.float64), X, t, mu.astype(np.float64), inv_sd.astype(np.float64))
+    yo, (_, _, h1o, _, h2o) = omlp.forward(args[0], X, args[3], args[4])
+    assert rel_norm(y.cpu().numpy(), yo) <= 1e-5
+    assert rel_norm(h1.cpu().numpy().reshape(64, n).T, h1o) <= 1e-5
+    assert rel_norm(h2.cpu().numpy().reshape(64, n).T, h2o) <= 1e-5
+    go, gu = omlp.unpack(omlp.grad(*args)), omlp.unpack(g.cpu().numpy())
+    for name in go:
+        assert rel_norm(gu[name], go[name]) <= 1e-4, name
+    assert abs(float(loss.item()) - omlp.loss(*args)) <= 1e-5 * omlp.loss(*args)
+
+
+@pytest.mark.parametrize("m,c,k", [(1, 256, 1), (255, 5, 3), (4100, 144, 3), (300, 65, 4)])
+def test_choose_is_the_least_forward_prediction(L, m, c, k):
+    """Every (launch, candidate) through the forward kernel, the models' mean
+    and the first least one on the host: choose gives the same bits, around
+    one launch per block, a block's second group of launches (more than 16)
+    and candidate counts off the wave's 64."""
+    import torch
+
+    say("mlp choose against forward", m, c, k)
+    rng = np.random.default_rng(10 * m + c)
+    feats = (rng.standard_normal((m, 9)) * 2.0).astype(np.float32)
+    cands = (rng.standard_normal((c, 3)) * 2.0).astype(np.float32)
+    valid = rng.random((m, c)) < 0.7
+    valid[0, c - 1] = True
+    params = [omlp.init_params(70 + q).astype(np.float32) for q in range(k)]
+    norm = np.concatenate([rng.standard_normal(12) * 0.1, 0.5 + rng.random(12)]).astype(np.float32)
+    best, pred, _ = _choose(L, params, norm, feats, cands, valid)
+    X = np.concatenate([np.repeat(feats, c, axis=0), np.tile(cands, (m, 1))], axis=1).astype(np.float32)
+    dx, dn = cuda(X), cuda(norm)
+    s = np.zeros(m * c, np.float32)
+    for q in params:
+        y, _, _ = _fwd(L, cuda(q), dn, dx, store=False)
+        s = s + y.cpu().numpy()
+    mean = np.where(valid, (s / np.float32(k)).reshape(m, c), np.float32(np.inf))
+    some = valid.any(axis=1)
+    assert np.array_equal(best[some], np.argmin(mean, axis=1)[some].astype(np.uint32))
+    assert np.array_equal(pred[some], mean.min(axis=1)[some])
+    assert np.all(best[~some] == 0xFFFFFFFF)
