@@ -1,28 +1,8 @@
 // cls_gemm.hpp -- block bodies of the GEMM_F32 class: C = A * B, fp32
-// row-major, fp32 accumulation on the matrix cores.  Shapes with 16-byte
-// rows (K and N multiples of 4, aligned bases) take the direct-to-LDS form
-// at the end of this file; the register-staged form below serves the rest.
-//
-// A block of 256 threads (4 waves, 2 x 2) owns a T x T tile of C; each wave
-// owns a (T/2) x (T/2) sub-tile made of (T/64)^2 tiles of 32 x 32, each
-// accumulated by v_mfma_f32_32x32x2f32 (A fragment 32 x 2, B fragment
-// 2 x 32, 16 fp32 accumulators per lane).  K is walked in KT = 16 deep
-// slices staged in LDS: A transposed (k-major) so that the 32 lanes that
-// need one k read 32 consecutive words, B as is.  The LDS has 64 banks of
-// 4 bytes and serves a whole wave per access; an MFMA operand read takes
-// k-rows kk (lanes 0-31) and kk + 1 (lanes 32-63), 4 banks apart with the
-// 4-word row pad, so 28 of their banks collide.  At T = 256 odd k-rows are
-// stored rotated by 28 columns (mod T): the two halves then land 32 banks
-// apart, the transposed stores of A stay conflict-free, and the kernel
-// gains 3.7%.  At T = 64 and 128 the rotation costs more in address
-// arithmetic and lost paired reads than the conflicts do, so those tiles
-// keep the plain layout.  Two LDS buffers and a register prefetch of the
-// next slice let one barrier per slice separate the writers of one buffer
-// from the readers of the other.  Outside the matrices the staged values
-// are zero.  At T >= 128 a wave raises its issue priority for the MFMA
-// part of each slice and drops it for the LDS stores and the barrier, so
-// waves that can feed the matrix cores go first (tile 128: 1110 -> 1029 us
-// at 4096^3; at T = 64 it measured no better).
+// row-major, fp32 accumulation on the matrix cores (v_mfma_f32_32x32x2f32: A
+// fragment 32 x 2, B fragment 2 x 32, 16 fp32 accumulators per lane).  Two
+// forms: K slices staged straight into LDS (whole T x T tiles, enough of them
+// to fill the device), and K split over a block's waves (few tiles).
 //
 // Operand layouts of v_mfma_f32_32x32x2f32 (64 lanes):
 //   A: lane l holds A[m = l % 32][k = l / 32]
@@ -37,146 +17,19 @@
 namespace spmd {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // any float's address
 
-constexpr int GEMM_KT = 16;
-constexpr int GEMM_PAD = 4;
-
-// Physical column of logical column c in k-row k of a T-wide LDS slice.
-template <int T>
-__device__ __forceinline__ int gemm_lds_col(int k, int c) {
-    if constexpr (T < 256) return c;
-    else return (k & 1) ? ((c + 28) & (T - 1)) : c;
-}
-
-template <int T>
-struct GemmLds {
-    alignas(16) float a[2][GEMM_KT][T + GEMM_PAD];
-    alignas(16) float b[2][GEMM_KT][T + GEMM_PAD];
-};
-
-template <int T>
-__device__ __forceinline__ void gemm_block(const float* __restrict__ A, const float* __restrict__ B,
-                                           float* __restrict__ C, uint32_t M, uint32_t N, uint32_t K, uint32_t bx,
-                                           uint32_t by, bool vecA, bool vecB, GemmLds<T>& L) {
-    constexpr int KT = GEMM_KT;
-    constexpr int RT = T / 64;           // 32 x 32 tiles per wave edge
-    constexpr int WT = T / 2;            // wave tile edge
-    constexpr int PT = T * KT / 1024;    // float4 loads per thread per operand
-    constexpr int KQ = KT / 4;           // float4 per row of an A slice
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
-    const int64_t m0 = (int64_t)by * T, n0 = (int64_t)bx * T;
-    const int64_t Mi = M, Ni = N, Ki = K;
-
-    f32x16 acc[RT][RT];
-#pragma unroll
-    for (int i = 0; i < RT; ++i)
-#pragma unroll
-        for (int j = 0; j < RT; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-
-    f32x4 ra[PT], rb[PT];
-    // Interior slices (the whole T x KT and KT x T slices inside the
-    // matrices, rows 16-byte aligned) are decided once per block and slice,
-    // so their loads issue back to back with no per-thread branches; edge
-    // slices take the element-wise path.
-    const bool inner_mn = vecA && vecB && m0 + T <= Mi && n0 + T <= Ni;
-    auto gload = [&](int kt) {
-        const int64_t k0 = (int64_t)kt * KT;
-        if (inner_mn && k0 + KT <= Ki) {
-#pragma unroll
-            for (int j = 0; j < PT; ++j) {
-                const int q = tid + 256 * j;
-                ra[j] = *reinterpret_cast<const f32x4*>(A + (m0 + q / KQ) * Ki + k0 + (q % KQ) * 4);
-            }
-#pragma unroll
-            for (int j = 0; j < PT; ++j) {
-                const int q = tid + 256 * j;
-                rb[j] = *reinterpret_cast<const f32x4*>(B + (k0 + q / (T / 4)) * Ni + n0 + (q % (T / 4)) * 4);
-            }
-            return;
-        }
-#pragma unroll
-        for (int j = 0; j < PT; ++j) {
-            const int q = tid + 256 * j;  // A slice: T rows x KT/4 float4
-            const int row = q / KQ, kq = (q % KQ) * 4;
-            const int64_t gm = m0 + row, gk = k0 + kq;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) ra[j][e] = (gm < Mi && gk + e < Ki) ? A[gm * Ki + gk + e] : 0.0f;
-        }
-#pragma unroll
-        for (int j = 0; j < PT; ++j) {
-            const int q = tid + 256 * j;  // B slice: KT rows x T/4 float4
-            const int row = q / (T / 4), c4 = (q % (T / 4)) * 4;
-            const int64_t gk = k0 + row, gn = n0 + c4;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) rb[j][e] = (gk < Ki && gn + e < Ni) ? B[gk * Ni + gn + e] : 0.0f;
-        }
-    };
-    auto lstore = [&](int buf) {
-#pragma unroll
-        for (int j = 0; j < PT; ++j) {
-            const int q = tid + 256 * j;
-            const int row = q / KQ, kq = (q % KQ) * 4;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) L.a[buf][kq + e][gemm_lds_col<T>(kq + e, row)] = ra[j][e];
-        }
-#pragma unroll
-        for (int j = 0; j < PT; ++j) {
-            const int q = tid + 256 * j;
-            const int row = q / (T / 4), c4 = (q % (T / 4)) * 4;
-            *reinterpret_cast<f32x4*>(&L.b[buf][row][gemm_lds_col<T>(row, c4)]) = rb[j];
-        }
-    };
-
-    const int nk = (int)((Ki + KT - 1) / KT);
-    gload(0);
-    lstore(0);
-    __syncthreads();
-    const int kl = lane >> 5, ml = lane & 31;
-    for (int kt = 0; kt < nk; ++kt) {
-        const int cur = kt & 1;
-        if (kt + 1 < nk) gload(kt + 1);
-#pragma unroll
-        for (int kk = 0; kk < KT; kk += 2) {
-            float a[RT], b[RT];
-#pragma unroll
-            for (int i = 0; i < RT; ++i) a[i] = L.a[cur][kk + kl][gemm_lds_col<T>(kk + kl, wm * WT + i * 32 + ml)];
-#pragma unroll
-            for (int j = 0; j < RT; ++j) b[j] = L.b[cur][kk + kl][gemm_lds_col<T>(kk + kl, wn * WT + j * 32 + ml)];
-            if constexpr (T >= 128) __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-            for (int i = 0; i < RT; ++i)
-#pragma unroll
-                for (int j = 0; j < RT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
-        }
-        if constexpr (T >= 128) __builtin_amdgcn_s_setprio(0);
-        if (kt + 1 < nk) lstore(cur ^ 1);
-        __syncthreads();
-    }
-
-#pragma unroll
-    for (int i = 0; i < RT; ++i)
-#pragma unroll
-        for (int j = 0; j < RT; ++j) {
-            const int64_t col = n0 + wn * WT + j * 32 + ml;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int64_t row = m0 + wm * WT + i * 32 + (r >> 2) * 8 + kl * 4 + (r & 3);
-                if (row < Mi && col < Ni) C[row * Ni + col] = acc[i][j][r];
-            }
-        }
-}
-
-
-// ---- Direct-to-LDS form (16-byte aligned rows: K % 4 == 0, N % 4 == 0) ----
+// ---- Direct-to-LDS form ----
 //
-// Each K slice (16 deep) goes from HBM to LDS with global_load_lds_dwordx4:
-// a lane's 16 bytes land at the instruction's LDS base + 16 * lane, so no
-// register holds the slice and no LDS store is issued, and NS slices are in
-// flight at once (a stage each).  Both operands are laid out for that:
+// A block of 256 threads (4 waves, 2 x 2) owns a T x T tile of C, each wave a
+// (T/2) x (T/2) part of it.  Each K slice (16 deep) goes from HBM to LDS with
+// global_load_lds: a lane's V floats land at the instruction's LDS base +
+// 4 V * lane, so no register holds the slice and no LDS store is issued, and NS
+// slices are in flight at once (a stage each).  V = 4 (16-byte loads) where
+// the rows are 16-byte aligned; V = 1 at any other width and alignment, four
+// times the loads for the same bytes: 4095^3 at T = 256 1184 us against 1100 for
+// 4096^3 with V = 4 (staged through registers element by element it took 1650
+// to 1900).  Both operands are laid out for that:
 //   A as [m][k] (k contiguous, 64-byte rows); the four 16-byte chunks of
 //     row m sit at positions c ^ ((m / 4) % 4), so the 16-lane groups of a
 //     16-byte read hit 16 distinct 4-bank groups;
@@ -197,13 +50,20 @@ constexpr int GEMM_DMA_KT = 16;
 typedef __attribute__((address_space(1))) void gemm_gvoid;
 typedef __attribute__((address_space(3))) void gemm_lvoid;
 
-// s_waitcnt: vmcnt <= n, lgkmcnt 0, expcnt not waited (n < 16)
-#define GEMM_WAIT_VM(n) __builtin_amdgcn_s_waitcnt(0x70 | (n))
+// s_waitcnt: vmcnt <= n, lgkmcnt 0, expcnt not waited (n < 64)
+#define GEMM_WAIT_VM(n) __builtin_amdgcn_s_waitcnt(0x70 | ((n) & 15) | (((n) >> 4) << 14))
 
 // The stages are separate LDS arrays passed in by the kernel: the
 // compiler then tells a refill from the reads of another stage and does
 // not wait for the refill before those reads.
-template <int T, int NS>
+// One load of V floats per lane from `src` to the wave's V * 64 floats at `dst`.
+template <int V>
+__device__ __forceinline__ void gemm_load_lds(const float* src, float* dst) {
+    if constexpr (V == 4) __builtin_amdgcn_global_load_lds((gemm_gvoid*)src, (gemm_lvoid*)dst, 16, 0, 0);
+    else __builtin_amdgcn_global_load_lds((gemm_gvoid*)src, (gemm_lvoid*)dst, 4, 0, 0);
+}
+
+template <int T, int NS, int V>
 __device__ __forceinline__ void gemm_block_dma(const float* __restrict__ A, const float* __restrict__ B,
                                                float* __restrict__ C, uint32_t M, uint32_t N, uint32_t K,
                                                uint32_t bx, uint32_t by, float* S0, float* S1, float* S2,
@@ -212,17 +72,17 @@ __device__ __forceinline__ void gemm_block_dma(const float* __restrict__ A, cons
     constexpr int RT = T / 64, WT = T / 2;
     constexpr int CPR = KT / 4;          // 16-byte chunks per A row
     constexpr int RPS = 64 / KT;         // A rows per 64-bank span
-    constexpr int NI = T * KT / 1024;    // loads per wave per operand per slice
+    constexpr int NI = T * KT / (256 * V);  // loads per wave per operand per slice
     constexpr int LPW = 2 * NI;          // loads per wave per slice
     constexpr int BCH = T / 4;           // 16-byte chunks per B row
     constexpr int SA = T * KT;           // floats per operand per stage
-    static_assert(NS >= 2 && NS <= 4 && LPW * (NS - 2) < 16, "stage count");
+    static_assert(V == 1 || V == 4, "floats per load");
+    static_assert(NS >= 2 && NS <= 4 && LPW * (NS - 2) < 64, "stage count");
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1;
     const int64_t m0 = (int64_t)by * T, n0 = (int64_t)bx * T;
     const int64_t Mi = M, Ni = N, Ki = K;
-    if (m0 >= Mi || n0 >= Ni) return;  // a block wholly outside C (grids may be larger)
     const int nk = (int)(Ki / KT);
 
     // Per-lane source offsets from the block's slice-0 corner (the launcher
@@ -232,25 +92,22 @@ __device__ __forceinline__ void gemm_block_dma(const float* __restrict__ A, cons
     int srcA[NI], srcB[NI];
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
-        const int ci = 64 * (wave + 4 * i) + lane;
-        const int r = ci / CPR, c = (ci % CPR) ^ ((r / RPS) % CPR);
+        const int p = V * (64 * (wave + 4 * i) + lane);  // the lane's first float in the stage
+        const int r = p / KT, c = ((p % KT) / 4) ^ ((r / RPS) % CPR);
         const int rr = m0 + r < Mi ? r : (int)(Mi - 1 - m0);  // past M: the last row
-        srcA[i] = rr * (int)K + 4 * c;
-        const int k = ci / BCH;
-        const int col = (4 * (ci % BCH) - ((k & 4) ? 32 : 0) + T) % T;
-        const int cc = n0 + col < Ni ? col : (int)(Ni - 4 - n0);  // past N: the last chunk
+        srcA[i] = rr * (int)K + 4 * c + p % 4;
+        const int k = p / T;
+        const int col = (p % T - ((k & 4) ? 32 : 0) + T) % T;
+        const int cc = n0 + col < Ni ? col : (int)(Ni - V - n0);  // past N: the last chunk
         srcB[i] = k * (int)N + cc;
     }
     auto issue = [&](int kt, float* st) {
         const float* a = Ab + (int64_t)kt * KT;
         const float* b = Bb + (int64_t)kt * KT * Ni;
 #pragma unroll
-        for (int i = 0; i < NI; ++i)
-            __builtin_amdgcn_global_load_lds((gemm_gvoid*)(a + srcA[i]), (gemm_lvoid*)(st + 256 * (wave + 4 * i)), 16, 0, 0);
+        for (int i = 0; i < NI; ++i) gemm_load_lds<V>(a + srcA[i], st + 64 * V * (wave + 4 * i));
 #pragma unroll
-        for (int i = 0; i < NI; ++i)
-            __builtin_amdgcn_global_load_lds((gemm_gvoid*)(b + srcB[i]), (gemm_lvoid*)(st + SA + 256 * (wave + 4 * i)),
-                                             16, 0, 0);
+        for (int i = 0; i < NI; ++i) gemm_load_lds<V>(b + srcB[i], st + SA + 64 * V * (wave + 4 * i));
     };
 
     f32x16 acc[RT][RT];
@@ -357,20 +214,21 @@ __device__ __forceinline__ void gemm_block_dma(const float* __restrict__ A, cons
         __syncthreads();  // every wave is done reading the stages
     }
     if (Ki % KT) {
-        // The K tail (4, 8 or 12 deep, since K % 4 == 0) through registers,
-        // zero outside the matrices, into stage 0 in the same layouts.
+        // The K tail through registers, zero outside the matrices, into
+        // stage 0 in the same layouts.
         const int64_t k0 = (int64_t)nk * KT;
-        for (int ci = tid; ci < T * CPR; ci += 256) {
-            const int r = ci / CPR, c = ci % CPR;
-            f32x4 v = {0.0f, 0.0f, 0.0f, 0.0f};
-            if (m0 + r < Mi && k0 + 4 * c < Ki) v = *reinterpret_cast<const f32x4*>(A + (m0 + r) * Ki + k0 + 4 * c);
-            *reinterpret_cast<f32x4*>(S0 + r * KT + 4 * (c ^ ((r / RPS) % CPR))) = v;
+        using vec = std::conditional_t<V == 4, f32x4, float>;
+        for (int p = V * tid; p < T * KT; p += 256 * V) {
+            const int r = p / KT, k = p % KT;
+            vec v = {};
+            if (m0 + r < Mi && k0 + k < Ki) v = *reinterpret_cast<const vec*>(A + (m0 + r) * Ki + k0 + k);
+            *reinterpret_cast<vec*>(S0 + r * KT + 4 * ((k / 4) ^ ((r / RPS) % CPR)) + k % 4) = v;
         }
-        for (int ci = tid; ci < KT * BCH; ci += 256) {
-            const int k = ci / BCH, col = 4 * (ci % BCH);
-            f32x4 v = {0.0f, 0.0f, 0.0f, 0.0f};
-            if (k0 + k < Ki && n0 + col < Ni) v = *reinterpret_cast<const f32x4*>(B + (k0 + k) * Ni + n0 + col);
-            *reinterpret_cast<f32x4*>(S0 + SA + k * T + (col + ((k & 4) ? 32 : 0)) % T) = v;
+        for (int p = V * tid; p < KT * T; p += 256 * V) {
+            const int k = p / T, col = p % T;
+            vec v = {};
+            if (k0 + k < Ki && n0 + col < Ni) v = *reinterpret_cast<const vec*>(B + (k0 + k) * Ni + n0 + col);
+            *reinterpret_cast<vec*>(S0 + SA + k * T + (col + ((k & 4) ? 32 : 0)) % T) = v;
         }
         __syncthreads();
         compute(S0);
@@ -387,6 +245,147 @@ __device__ __forceinline__ void gemm_block_dma(const float* __restrict__ A, cons
                 if (row < Mi && col < Ni) C[row * Ni + col] = acc[i][j][r];
             }
         }
+}
+
+
+// ---- K-split form (any shape and alignment; few tiles) ----
+//
+// A block of W waves owns one T x T tile of C, T = 32 RT; every wave computes
+// the whole tile over its share of K (8-deep groups dealt round-robin, so the
+// waves read neighbouring 32-byte pieces of the same rows of A at the same
+// time), and the W partial tiles are added in wave order through LDS at the
+// end.  Operands go from global memory straight into registers, D groups
+// ahead: no LDS, no barrier and no alignment in the main loop.  Lane l takes
+// row l % 32 of A as one 16-byte load of k = 8g + 4 (l / 32) .. + 3 and
+// column l % 32 of B as four 4-byte loads (128 bytes contiguous per half-wave);
+// k step s multiplies k = 8g + s (lanes 0-31) and 8g + 4 + s.
+// Bound by what a CU's vector cache delivers (about 9 bytes a cycle of these
+// strided pieces, half to two thirds of what the matrix cores could take), not
+// by latency: one, two and four groups ahead and four or eight waves measure
+// within 10% of each other.  1000 x 901 x 1111 on 64 x 64 tiles: 25.4 us,
+// against 174 us on 128 x 128 tiles staged through registers; 512^3 on 32 x 32
+// tiles 5.9 us against 12.1 us on 64 x 64 staged in LDS (64 of 256 CUs busy).
+// Rows past M and columns past N are read from the last row or column (their
+// products fall outside C and are not stored).
+template <int RT, int W>
+struct GemmKsplitLds {
+    float part[W][16 * RT * RT][64];
+};
+
+template <int RT, int W, int D, typename Off>
+__device__ __forceinline__ void gemm_block_ksplit(const float* __restrict__ A, const float* __restrict__ B,
+                                                  float* __restrict__ C, uint32_t M, uint32_t N, uint32_t K,
+                                                  uint32_t bx, uint32_t by, GemmKsplitLds<RT, W>& L) {
+    constexpr int T = 32 * RT;
+    constexpr int R = 16 * RT * RT;  // accumulators per lane
+    static_assert(R % W == 0, "each wave adds R / W of them");
+    const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int64_t m0 = (int64_t)by * T, n0 = (int64_t)bx * T;
+    const int64_t Mi = M, Ni = N, Ki = K;
+    // Addresses are a wave-uniform base plus the lane's offset from the tile's
+    // corner, 32 bits wide where the launcher has checked that they fit.
+    const float* Ab = A + m0 * Ki;
+    const float* Bb = B + n0;
+    Off oa[RT], ob[RT];
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
+        const int64_t row = m0 + 32 * i + l32 < Mi ? 32 * i + l32 : Mi - 1 - m0;
+        const int64_t col = n0 + 32 * i + l32 < Ni ? 32 * i + l32 : Ni - 1 - n0;
+        oa[i] = (Off)(4 * (row * Ki + 4 * half));
+        ob[i] = (Off)(4 * (col + 4 * half * Ni));
+    }
+    f32x16 acc[RT][RT];
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int j = 0; j < RT; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+
+    f32x4 av[D][RT];
+    float bv[D][RT][4];
+    auto at = [](const float* base, Off off) {
+        return reinterpret_cast<const float*>(reinterpret_cast<const char*>(base) + off);
+    };
+    auto load = [&](const float* pa, const float* pb, f32x4 (&va)[RT], float (&vb)[RT][4]) {
+#pragma unroll
+        for (int i = 0; i < RT; ++i) va[i] = *reinterpret_cast<const f32x4u*>(at(pa, oa[i]));
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int j = 0; j < RT; ++j) vb[j][s] = *at(pb + s * Ni, ob[j]);
+    };
+    auto mul = [&](const f32x4 (&va)[RT], const float (&vb)[RT][4]) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int i = 0; i < RT; ++i)
+#pragma unroll
+                for (int j = 0; j < RT; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(va[i][s], vb[j][s], acc[i][j], 0, 0, 0);
+    };
+    const int64_t full = Ki / 8;                                     // whole groups
+    const int64_t mine = full > wave ? (full - wave + W - 1) / W : 0;  // this wave's: wave, wave + W, ...
+    if (mine > 0) {
+        const float* pa = Ab + 8 * wave;  // the next group to load
+        const float* pb = Bb + 8 * wave * Ni;
+        int64_t left = mine - 1;  // groups after it: past the wave's last, that one is loaded again
+        auto next = [&](f32x4 (&va)[RT], float (&vb)[RT][4]) {
+            load(pa, pb, va, vb);
+            if (left > 0) {
+                pa += 8 * W;
+                pb += 8 * W * Ni;
+                --left;
+            }
+        };
+#pragma unroll
+        for (int d = 0; d < D; ++d) next(av[d], bv[d]);
+        int64_t q = 0;
+        for (; q + D <= mine; q += D) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                mul(av[d], bv[d]);
+                next(av[d], bv[d]);
+                __builtin_amdgcn_sched_barrier(0);  // or the loads of all D groups move behind the products
+            }
+        }
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+            if (q + d < mine) mul(av[d], bv[d]);
+    }
+    if (Ki % 8 && full % W == wave) {  // the last K % 8, zero past K
+        const int64_t k0 = 8 * full + 4 * half;
+        f32x4 va[RT];
+        float vb[RT][4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const bool in = k0 + s < Ki;
+#pragma unroll
+            for (int i = 0; i < RT; ++i) {
+                va[i][s] = in ? *at(Ab + 8 * full + s, oa[i]) : 0.0f;
+                vb[i][s] = in ? *at(Bb + (8 * full + s) * Ni, ob[i]) : 0.0f;
+            }
+        }
+        mul(va, vb);
+    }
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int j = 0; j < RT; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) L.part[wave][(i * RT + j) * 16 + r][lane] = acc[i][j][r];
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < R / W; ++e) {
+        const int q = wave * (R / W) + e, r = q & 15, ij = q >> 4;
+        float v = L.part[0][q][lane];
+#pragma unroll
+        for (int w = 1; w < W; ++w) v += L.part[w][q][lane];
+        const int64_t row = m0 + (ij / RT) * 32 + (r >> 2) * 8 + half * 4 + (r & 3);
+        const int64_t col = n0 + (ij % RT) * 32 + l32;
+        if (row < Mi && col < Ni) C[row * Ni + col] = v;
+    }
 }
 
 }  // namespace spmd

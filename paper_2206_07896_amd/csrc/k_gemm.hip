@@ -1,28 +1,85 @@
-// k_gemm.hip -- GEMM_F32 kernel and launcher.
+// k_gemm.hip -- GEMM_F32 kernels and launcher.
 #include "cls_gemm.hpp"
+#include "cls_jacobi.hpp"  // xcd_tile
 
 namespace spmd {
 
-template <int T>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ B,
-                                                        float* __restrict__ C, uint32_t M, uint32_t N, uint32_t K,
-                                                        bool vecA, bool vecB) {
-    __shared__ GemmLds<T> L;
-    gemm_block<T>(A, B, C, M, N, K, blockIdx.x, blockIdx.y, vecA, vecB, L);
-}
-
 // Direct-to-LDS form: NS slices in flight (4 at tiles 64 and 128; 3 at
 // tile 256, whose stages are twice as large).
-template <int T, int NS>
+template <int T, int NS, int V>
 __global__ __launch_bounds__(256) void gemm_f32_dma_kernel(const float* __restrict__ A, const float* __restrict__ B,
-                                                            float* __restrict__ C, uint32_t M, uint32_t N, uint32_t K) {
+                                                            float* __restrict__ C, uint32_t M, uint32_t N, uint32_t K,
+                                                            uint32_t gx) {
     constexpr int SZ = 2 * T * GEMM_DMA_KT;
     __shared__ __attribute__((aligned(16))) float S0[SZ];
     __shared__ __attribute__((aligned(16))) float S1[SZ];
     __shared__ __attribute__((aligned(16))) float S2[NS > 2 ? SZ : 4];
     __shared__ __attribute__((aligned(16))) float S3[NS > 3 ? SZ : 4];
-    gemm_block_dma<T, NS>(A, B, C, M, N, K, blockIdx.x, blockIdx.y, S0, S1, S2, S3);
+    gemm_block_dma<T, NS, V>(A, B, C, M, N, K, blockIdx.x % gx, blockIdx.x / gx, S0, S1, S2, S3);
 }
+
+template <int RT, int W, int D, typename Off>
+__global__ __launch_bounds__(64 * W) void gemm_f32_ksplit_kernel(const float* __restrict__ A,
+                                                                 const float* __restrict__ B, float* __restrict__ C,
+                                                                 uint32_t M, uint32_t N, uint32_t K, uint32_t gx,
+                                                                 uint32_t tiles) {
+    __shared__ GemmKsplitLds<RT, W> L;
+    for (uint32_t id = blockIdx.x; id < tiles; id += gridDim.x) {
+        const uint32_t t = xcd_tile(id, tiles);  // a range of tiles per XCD: their rows of A meet in its L2
+        gemm_block_ksplit<RT, W, D, Off>(A, B, C, M, N, K, t % gx, t / gx, L);
+        __syncthreads();  // the next tile reuses the LDS
+    }
+}
+
+namespace {
+
+// The forms, and what one tile takes on a CU per unit of K, in 0.1 ns,
+// measured at shapes that fill the 256 CUs with one or more of them: 4096^3,
+// 2048^3, 3000^3 and 1536^3 with 16-byte rows; 4095^3, 2047 x 2049 x 2047 and
+// 3001 x 2999 x 3001 without; 512 x 512 x 4096 and 1023 x 1025 x 1027 for the
+// 32 x 32 tiles.  The larger the tile, the nearer it runs to the matrix
+// cores' rate, and the more a shape that does not fill a round of tiles
+// leaves idle.
+enum class GemmForm { SPLIT32, SPLIT64, DMA64, DMA128, DMA256 };
+struct GemmCost {
+    GemmForm form;
+    uint32_t tile, cost;
+};
+constexpr GemmCost GEMM_ALIGNED[] = {
+    {GemmForm::DMA256, 256, 2620}, {GemmForm::DMA128, 128, 690}, {GemmForm::DMA64, 64, 194}, {GemmForm::SPLIT32, 32, 75}};
+constexpr GemmCost GEMM_ANY[] = {
+    {GemmForm::DMA256, 256, 2890}, {GemmForm::DMA128, 128, 770}, {GemmForm::SPLIT64, 64, 224}, {GemmForm::SPLIT32, 32, 80}};
+
+uint64_t tiles_of(uint32_t M, uint32_t N, uint32_t t) {
+    return (((uint64_t)M + t - 1) / t) * (((uint64_t)N + t - 1) / t);
+}
+
+// A launch's grid says which tiles its blocks own, but not on how many CUs
+// they run: the form is chosen by the shape alone, the least (rounds of tiles
+// over the CUs) x (time of a tile).  1000 x 901 x 1111 at the 128 x 128 tiles of
+// its launch kept 64 CUs busy for 174 us (64 x 64 split: 25.4 us); 4096^3 at 64 x 64
+// tiles took 1059 us (256 x 256: 958 us).  Ties go to the larger tile.  Forms
+// whose offsets (32 bits) or grid (32 bits of threads) a shape exceeds are left
+// out; the 32 x 32 split form has a 64-bit build and strides over its tiles.
+GemmForm gemm_form(uint32_t M, uint32_t N, uint32_t K, bool vec, int num_cus) {
+    GemmForm best = GemmForm::SPLIT32;
+    uint64_t least = ~0ull;
+    for (const GemmCost& f : vec ? GEMM_ALIGNED : GEMM_ANY) {
+        const uint64_t tiles = tiles_of(M, N, f.tile);
+        if (f.form != GemmForm::SPLIT32) {
+            if (4ull * f.tile * K >= (1ull << 31) || 4ull * GEMM_DMA_KT * N >= (1ull << 31)) continue;
+            if (tiles >= (1ull << 24)) continue;
+        }
+        const uint64_t c = (tiles + num_cus - 1) / num_cus * f.cost;
+        if (c < least) {
+            least = c;
+            best = f.form;
+        }
+    }
+    return best;
+}
+
+}  // namespace
 
 int launch_gemm_f32(const LaunchCtx& c) {
     if (c.block.x != 256 || c.block.y != 1 || c.block.z != 1 || c.grid.z != 1) return SPMD_ERR_INVALID_DIM;
@@ -33,31 +90,38 @@ int launch_gemm_f32(const LaunchCtx& c) {
     auto N = arg<uint32_t>(c.args, 4);
     auto K = arg<uint32_t>(c.args, 5);
     if (!A || !B || !C || M == 0 || N == 0 || K == 0) return SPMD_ERR_ARGS;
-    int T = 0;
-    for (int t : {64, 128, 256})
-        if ((uint64_t)c.grid.x * t >= N && (uint64_t)c.grid.y * t >= M) {
-            T = t;
-            break;
-        }
-    if (!T) return SPMD_ERR_INVALID_DIM;
-    const bool vecA = aligned(A, 16) && (K % 4 == 0);
-    const bool vecB = aligned(B, 16) && (N % 4 == 0);
-    dim3 g(c.grid.x, c.grid.y), b(256);
-    // The direct-to-LDS form needs 16-byte rows and 32-bit per-lane offsets.
-    const bool dma = vecA && vecB && (uint64_t)T * K < (1ull << 31) && (uint64_t)GEMM_DMA_KT * N < (1ull << 31);
-    if (dma) {
-        if (T == 64)
-            dispatch((gemm_f32_dma_kernel<64, 4>), g, b, c.dyn_shmem, c.stream, A, B, C, M, N, K);
-        else if (T == 128)
-            dispatch((gemm_f32_dma_kernel<128, 4>), g, b, c.dyn_shmem, c.stream, A, B, C, M, N, K);
+    bool covered = false;  // by tiles of 64, 128 or 256
+    for (int t : {64, 128, 256}) covered = covered || ((uint64_t)c.grid.x * t >= N && (uint64_t)c.grid.y * t >= M);
+    if (!covered) return SPMD_ERR_INVALID_DIM;
+    const bool vec = aligned(A, 16) && K % 4 == 0 && aligned(B, 16) && N % 4 == 0;
+    const hipStream_t s = c.stream;
+    // The class declares no dynamic shared memory and its kernels use none.
+    auto dma = [&](auto kernel, uint32_t t) {
+        dispatch(kernel, dim3((uint32_t)tiles_of(M, N, t)), dim3(256), 0, s, A, B, C, M, N, K, (N + t - 1) / t);
+    };
+    auto split = [&](auto kernel, uint32_t t, uint32_t threads) {
+        const uint64_t tiles = tiles_of(M, N, t);
+        dispatch(kernel, dim3((uint32_t)(tiles < (1u << 22) ? tiles : (1u << 22))), dim3(threads), 0, s, A, B, C, M, N,
+                 K, (uint32_t)(((uint64_t)N + t - 1) / t), (uint32_t)tiles);
+    };
+    switch (gemm_form(M, N, K, vec, c.dev->num_cus)) {
+    case GemmForm::DMA256:
+        if (vec) dma(gemm_f32_dma_kernel<256, 3, 4>, 256);
+        else dma(gemm_f32_dma_kernel<256, 3, 1>, 256);
+        break;
+    case GemmForm::DMA128:
+        if (vec) dma(gemm_f32_dma_kernel<128, 4, 4>, 128);
+        else dma(gemm_f32_dma_kernel<128, 4, 1>, 128);
+        break;
+    case GemmForm::DMA64: dma(gemm_f32_dma_kernel<64, 4, 4>, 64); break;
+    case GemmForm::SPLIT64: split(gemm_f32_ksplit_kernel<2, 4, 4, uint32_t>, 64, 256); break;
+    case GemmForm::SPLIT32:
+        if (4ull * 32 * K < (1ull << 31) && 4ull * 8 * N < (1ull << 31))
+            split(gemm_f32_ksplit_kernel<1, 8, 2, uint32_t>, 32, 512);
         else
-            dispatch((gemm_f32_dma_kernel<256, 3>), g, b, c.dyn_shmem, c.stream, A, B, C, M, N, K);
-    } else if (T == 64)
-        dispatch(gemm_f32_kernel<64>, g, b, c.dyn_shmem, c.stream, A, B, C, M, N, K, vecA, vecB);
-    else if (T == 128)
-        dispatch(gemm_f32_kernel<128>, g, b, c.dyn_shmem, c.stream, A, B, C, M, N, K, vecA, vecB);
-    else  // 128 x 128 per wave: 256 accumulators in AGPRs, one wave per SIMD
-        dispatch(gemm_f32_kernel<256>, g, b, c.dyn_shmem, c.stream, A, B, C, M, N, K, vecA, vecB);
+            split(gemm_f32_ksplit_kernel<1, 8, 2, uint64_t>, 32, 512);
+        break;
+    }
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? SPMD_OK : hip_fail(e);
 }

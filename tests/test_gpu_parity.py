@@ -467,6 +467,44 @@ def test_gemm_shapes(spmd, tile, M, N, K):
     assert np.all(np.abs(C - c64) <= bound + 1e-30)
 
 
+@pytest.mark.parametrize("M,N,K,shift", [
+    # 32 x 32 tiles, K split over 8 waves: one group of 8 per wave, fewer, a tail of K % 8
+    (31, 33, 7, 0), (33, 35, 8, 0), (97, 61, 129, 0), (40, 40, 260, 1),
+    # 64 x 64 tiles, K split over 4 waves: rows at any alignment
+    (1000, 901, 6, 0), (997, 905, 35, 0), (1000, 904, 160, 3),
+    # staged in LDS, 16-byte rows: tiles of 64, 128 and 256, below one slice, with tails, past the pipeline's main loop
+    (1020, 1000, 4, 0), (1020, 1000, 100, 0), (1023, 1004, 256, 0), (2040, 2044, 12, 0), (2041, 2036, 132, 0),
+    (4092, 4088, 24, 0), (4089, 4096, 120, 0),
+    # the same without 16-byte rows (4-byte loads): tiles of 128 and 256
+    (2045, 2047, 5, 0), (2046, 2045, 131, 0), (4090, 4095, 19, 0), (4090, 4093, 113, 0), (4096, 4096, 64, 1)])
+def test_gemm_forms(spmd, M, N, K, shift):
+    """Each form at sizes that its rule takes, at the edges of tiles, slices
+    and groups; bases off by `shift` floats, C between guard words."""
+    import torch
+
+    say("gemm forms", M, N, K, shift)
+    A = synth.normal_f32(M * 3 + K, M * K).reshape(M, K)
+    B = synth.normal_f32(N * 5 + K, K * N).reshape(K, N)
+
+    def shifted(a):
+        t = torch.empty(a.size + shift, dtype=torch.float32, device="cuda")[shift:]
+        return t.copy_(torch.from_numpy(a.reshape(-1)))
+
+    guard = 1 << 10
+    buf = torch.full((M * N + 2 * guard,), 7.0, dtype=torch.float32, device="cuda")
+    spmd.launch(spmd.GEMM_F32, (-(-N // 64), -(-M // 64)), 256, 0,
+                [shifted(A), shifted(B), buf[guard:guard + M * N], M, N, K])
+    spmd.sync()
+    got = host(buf)
+    assert np.all(got[:guard] == 7.0) and np.all(got[guard + M * N:] == 7.0)
+    C = got[guard:guard + M * N].reshape(M, N)
+    c64 = A.astype(np.float64) @ B.astype(np.float64)
+    assert _gemm_gate(C, c64, K)
+    gamma = K * 2.0**-24 / (1 - K * 2.0**-24)
+    bound = gamma * (np.abs(A).astype(np.float64) @ np.abs(B).astype(np.float64))
+    assert np.all(np.abs(C - c64) <= bound + 1e-30)
+
+
 @pytest.mark.parametrize("tile", [64, 128, 256])
 def test_gemm_exact_cases(spmd, tile):
     say("gemm exact", tile)
