@@ -172,10 +172,11 @@ enum {
      * (temporal blocking; the roofline discussion of Section VI-B: a
      * one-sweep stencil is bound by memory, so more sweeps per byte moved
      * is the way past that bound).  u_next = S sweeps of u, every cell
-     * computed exactly as by S one-sweep launches (bit-identical).  Each
-     * workgroup holds a 256-column region -- a (256 - 2H) x 64 interior
-     * tile plus a halo of H = 4 cells (S <= 4) or H = 8 cells (S <= 8) --
-     * in registers, sweeps there, and stores the interior.
+     * computed exactly as by S one-sweep launches (bit-identical).  A
+     * block owns a tile of (256 - 2H) x 64 cells, H = 4 (S <= 4) or 8; the
+     * library cuts the grid into regions of its own choice by its size,
+     * each held in registers with its halo, swept there and its interior
+     * stored.
      * args: const float* u, float* u_next, uint32_t nx, uint32_t ny,
      *       uint32_t sweeps (S, 1..8)
      * block (256,1,1); grid (GX,GY,1) with GX*(256 - 2H) >= nx and

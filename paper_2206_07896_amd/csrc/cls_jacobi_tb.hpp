@@ -3,17 +3,17 @@
 //
 // One sweep reads and writes every cell once, so a sweep-per-launch stencil
 // is bound at 8 bytes per cell by HBM.  Here a workgroup loads a region of
-// 256 columns x (64 + 2H) rows -- its (256 - 2H) x 64 interior tile and an
-// H-cell halo, H >= S -- runs S sweeps on it, and writes back only the
-// interior: HBM moves about 8 bytes per cell per S sweeps, plus the halo.
+// 256 columns x RS * WV rows -- its interior tile and a halo of S rows and
+// HC >= S columns on each side -- runs S sweeps on it, and writes back only
+// the interior: HBM moves about 8 bytes per cell per S sweeps, plus the halo.
 //
 // The region lives in registers.  A wave spans a whole region row (64
-// lanes x 4 columns); the 4 waves own bands of RS = (64 + 2H) / 4
-// consecutive rows, each lane its 4 columns of every row of its band.  In a
-// sweep, north and south neighbours come from the lane's own registers, west
-// and east from the adjacent lanes (a full-wave shuffle), and only the first
-// and last row of each band go through LDS to the neighbouring waves (two
-// slots per sweep parity, one barrier per sweep).
+// lanes x 4 columns); the WV waves own bands of RS consecutive rows, each
+// lane its 4 columns of every row of its band.  In a sweep, north and south
+// neighbours come from the lane's own registers, west and east from the
+// adjacent lanes (DPP wave shifts, folded into the additions), and only the
+// first and last row of each band go through LDS to the neighbouring waves
+// (two slots per sweep parity, one barrier per sweep).
 //
 // Phases:
 //   load   the region row by row, 16 bytes per lane; cells outside the grid
@@ -22,103 +22,183 @@
 //          neighbours' edge rows; update the band top-down.  A cell is
 //          updated as 0.25f * ((N + S) + (W + E)), each operation rounded
 //          to fp32 in that order (no contraction), exactly as the one-sweep
-//          class; border cells of the grid keep their value.  Sweep s only
-//          needs region rows [s, 64 + 2H - s), so the others are skipped;
-//          the region's outer columns go stale one per sweep (their outer
-//          neighbours do not exist), and after S sweeps the stale ring is
-//          still outside the interior (H >= S);
+//          class; border cells of the grid keep their value.  Every row of
+//          the region is updated in every sweep: the outer ring, whose outer
+//          neighbours do not exist, goes stale by one cell per sweep and
+//          after S sweeps is still outside the interior;
 //   store  the interior, cells inside the grid.
 // Results are bit-identical to S sweeps of the one-sweep class.
+//
+// Four vector operations per cell and sweep and nothing else in the loop: the
+// region inside the grid has a body of its own without border tests, and rows
+// are kept apart (sched_barrier), which holds a 12-row band at 71 registers
+// and three blocks of eight waves on a CU.  8 sweeps of 8192^2: 106 us, 5.0
+// TB/s of the bytes that one pass needs (the bound is HBM, 87 us, behind it
+// the vector unit, 70 us); 169 us with neighbours exchanged through the LDS
+// pipe, a border test per cell, and 64-row tiles of 152 registers.  8 sweeps
+// of a small grid (192 x 74): 5.2 us, 18.8 before.
 #pragma once
+#include <type_traits>
+#include <utility>
+
 #include "cls_jacobi.hpp"
 
 namespace spmd {
 
-constexpr int JT_H = 64, JT_THREADS = 256, JT_WAVES = JT_THREADS / 64;
+constexpr int JT_W = 256;         // columns of a region
+constexpr int JT_MAX_SWEEPS = 11;  // fused at most (the smallest region is 24 rows)
 
-// interior tile width for halo H
-__host__ __device__ constexpr int jt_width(int h) { return 256 - 2 * h; }
+typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));  // 16 bytes at any float's address
 
+template <int WV>
 struct JacobiTbLds {
-    f32x4 edge[2][2][JT_WAVES][64];  // [sweep parity][first row, last row][wave][lane]
+    f32x4 edge[2][2][WV][64];  // [sweep parity][first row, last row][wave][lane]
 };
 
-template <int H>
-__device__ __forceinline__ void jacobi_tb_block(const float* __restrict__ u, float* __restrict__ v, uint32_t nx,
-                                                uint32_t ny, uint32_t sweeps, uint32_t bx, uint32_t by,
-                                                JacobiTbLds& L) {
+// f(0), ..., f(N - 1) with the index a constant.  A loop over the band's rows
+// is unrolled late, after an array of up to 32 registers has been taken for
+// one vector and copied whole on every write (bands of 8 rows or fewer spilled).
+template <typename F, int... I>
+__device__ __forceinline__ void each_row(F f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void each_row(F f) {
+    each_row(f, std::make_integer_sequence<int, N>{});
+}
+
+// The value of the lane to the left (right); lane 0 (63) gets zero.
+__device__ __forceinline__ float lane_left(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x138, 0xf, 0xf, true));  // wave_shr:1
+}
+__device__ __forceinline__ float lane_right(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x130, 0xf, 0xf, true));  // wave_shl:1
+}
+
+// S sweeps of the band in `c`.  EDGE: the region holds border cells of the
+// grid: `keep` marks this lane's border columns, and rows `top` and `bottom`
+// of the band (outside 0..RS-1 if not in it) are border rows.
+template <int RS, int WV, bool EDGE>
+__device__ __forceinline__ void jacobi_tb_sweeps(f32x4 (&c)[RS], uint32_t sweeps, int w, int lane,
+                                                 const bool (&keep)[4], int top, int bottom, JacobiTbLds<WV>& L) {
 #pragma clang fp contract(off)
-    constexpr int ROWS = JT_H + 2 * H;
-    constexpr int RS = ROWS / JT_WAVES;
-    static_assert(ROWS % JT_WAVES == 0 && H % 4 == 0, "bands of whole rows, 16-byte groups");
-    const int lane = (int)(threadIdx.x & 63u), w = (int)(threadIdx.x >> 6);
-    const int64_t NX = nx, NY = ny;
-    const int64_t x0 = (int64_t)bx * jt_width(H) - H, y0 = (int64_t)by * JT_H - H;  // region origin
-    const int64_t gx = x0 + 4 * lane;  // this lane's first column
-    const int r0 = w * RS;             // this wave's first region row
-    const f32x4 z = {0.0f, 0.0f, 0.0f, 0.0f};
-
-    f32x4 c[RS];
-    const bool col_in = gx >= 0 && gx < NX;  // all four columns (NX % 4 == 0)
-#pragma unroll
-    for (int i = 0; i < RS; ++i) {
-        const int64_t gy = y0 + r0 + i;
-        c[i] = (col_in && gy >= 0 && gy < NY) ? __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(u + gy * NX + gx))
-                                              : z;
-    }
-    bool col_upd[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) col_upd[j] = gx + j >= 1 && gx + j <= NX - 2;
-
-    for (int s = 1; s <= (int)sweeps; ++s) {
-        const int par = s & 1;
+    const int wu = w > 0 ? w - 1 : 0, wd = w < WV - 1 ? w + 1 : w;  // the outer bands read a row that nothing needs
+#pragma unroll 1
+    for (uint32_t s = 0; s < sweeps; ++s) {
+        const int par = (int)(s & 1u);
         L.edge[par][0][w][lane] = c[0];
         L.edge[par][1][w][lane] = c[RS - 1];
         __syncthreads();
-        const f32x4 up = w > 0 ? L.edge[par][1][w - 1][lane] : z;
-        const f32x4 dn = w < JT_WAVES - 1 ? L.edge[par][0][w + 1][lane] : z;
-        f32x4 prev = up;  // this sweep's input of the row above
-#pragma unroll
-        for (int i = 0; i < RS; ++i) {
-            const int r = r0 + i;
+        const f32x4 up = L.edge[par][1][wu][lane], dn = L.edge[par][0][wd][lane];
+        f32x4 ns = up + c[1];
+        each_row<RS>([&](auto row) __attribute__((always_inline)) {
+            constexpr int i = row;
             const f32x4 cur = c[i];
-            const f32x4 below = i + 1 < RS ? c[i + 1] : dn;
-            if (r >= s && r < ROWS - s) {  // wave-uniform
-                const float wl = __shfl_up(cur.w, 1u);
-                const float er = __shfl_down(cur.x, 1u);
-                const int64_t gy = y0 + r;
-                if (gy >= 1 && gy <= NY - 2) {  // wave-uniform
-                    const float ww[4] = {wl, cur.x, cur.y, cur.z};
-                    const float ee[4] = {cur.y, cur.z, cur.w, er};
-                    const float nn[4] = {prev.x, prev.y, prev.z, prev.w};
-                    const float ss[4] = {below.x, below.y, below.z, below.w};
-                    const float cc[4] = {cur.x, cur.y, cur.z, cur.w};
-                    float o[4];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const float ns = nn[j] + ss[j];
-                        const float we = ww[j] + ee[j];
-                        const float sum = ns + we;
-                        o[j] = col_upd[j] ? 0.25f * sum : cc[j];
-                    }
-                    c[i].x = o[0];
-                    c[i].y = o[1];
-                    c[i].z = o[2];
-                    c[i].w = o[3];
-                }
+            f32x4 ns_next = cur;
+            if constexpr (i + 2 < RS) ns_next += c[i + 2];
+            else ns_next += dn;
+            f32x4 we;
+            we.x = lane_left(cur.w) + cur.y;
+            we.y = cur.x + cur.z;
+            we.z = cur.y + cur.w;
+            we.w = cur.z + lane_right(cur.x);
+            f32x4 o = 0.25f * (ns + we);
+            if constexpr (EDGE) {
+                const bool same = i == top || i == bottom;  // wave-uniform
+                o.x = keep[0] || same ? cur.x : o.x;
+                o.y = keep[1] || same ? cur.y : o.y;
+                o.z = keep[2] || same ? cur.z : o.z;
+                o.w = keep[3] || same ? cur.w : o.w;
             }
-            prev = cur;
+            c[i] = o;
+            ns = ns_next;
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    }
+}
+
+// One region whose first row and column are y0 and x0.  EDGE: part of it may
+// lie outside the grid or on its border.
+template <int RS, int WV, bool VEC, bool NT, bool EDGE>
+__device__ __forceinline__ void jacobi_tb_region(const float* __restrict__ u, float* __restrict__ v, int64_t NX,
+                                                 int64_t NY, uint32_t sweeps, uint32_t hc, int64_t x0, int64_t y0,
+                                                 JacobiTbLds<WV>& L) {
+    const int lane = (int)(threadIdx.x & 63u);
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int64_t yw = y0 + w * RS;    // this wave's first row
+    const int64_t gx = x0 + 4 * lane;  // this lane's first column
+    // rows r0 <= i < r1 of the band are rows of the grid
+    const int r0 = EDGE && yw < 0 ? (int)(-yw < RS ? -yw : RS) : 0;
+    const int r1 = EDGE && NY - yw < RS ? (int)(NY > yw ? NY - yw : 0) : RS;
+    const int64_t origin = yw * NX + x0;
+    const f32x4 z = {0.0f, 0.0f, 0.0f, 0.0f};
+
+    f32x4 c[RS];
+    const bool cols = !EDGE || (gx >= 0 && gx + 4 <= NX);  // all four columns are inside
+    each_row<RS>([&](auto row) __attribute__((always_inline)) {
+        constexpr int i = row;
+        c[i] = z;
+        if (i >= r0 && i < r1 && cols) {
+            const float* p = u + (origin + i * NX) + 4 * lane;
+            using vec = std::conditional_t<VEC, f32x4, f32x4_a4>;
+            c[i] = *reinterpret_cast<const vec*>(p);
         }
+    });
+    if (EDGE && !VEC && gx < NX && gx + 4 > NX) {  // the last columns of an odd width
+        each_row<RS>([&](auto row) __attribute__((always_inline)) {
+            constexpr int i = row;
+            if (i >= r0 && i < r1) {
+                const float* p = u + (origin + i * NX) + 4 * lane;
+                c[i].x = p[0];
+                if (gx + 1 < NX) c[i].y = p[1];
+                if (gx + 2 < NX) c[i].z = p[2];
+            }
+        });
     }
 
-    if (lane >= H / 4 && lane < 64 - H / 4 && gx < NX) {
+    bool keep[4];
 #pragma unroll
-        for (int i = 0; i < RS; ++i) {
-            const int r = r0 + i;
-            const int64_t gy = y0 + r;
-            if (r >= H && r < H + JT_H && gy < NY) *reinterpret_cast<f32x4*>(v + gy * NX + gx) = c[i];
+    for (int j = 0; j < 4; ++j) keep[j] = gx + j <= 0 || gx + j >= NX - 1;
+    const int top = yw <= 0 && -yw < RS ? (int)-yw : -1;
+    const int bottom = NY - 1 >= yw && NY - 1 - yw < RS ? (int)(NY - 1 - yw) : -1;
+    jacobi_tb_sweeps<RS, WV, EDGE>(c, sweeps, w, lane, keep, top, bottom, L);
+
+    const int hl = (int)hc / 4;
+    if (lane < hl || lane >= 64 - hl || (EDGE && gx >= NX)) return;
+    // the interior's rows of the band
+    const int lo = (int)sweeps - w * RS, end = lo + RS * WV - 2 * (int)sweeps, hi = end < r1 ? end : r1;
+    each_row<RS>([&](auto row) __attribute__((always_inline)) {
+        constexpr int i = row;
+        if (i >= lo && i < hi) {
+            float* p = v + (origin + i * NX) + 4 * lane;
+            if (VEC && NT) {
+                __builtin_nontemporal_store(c[i], reinterpret_cast<f32x4*>(p));
+            } else if (VEC) {
+                *reinterpret_cast<f32x4*>(p) = c[i];
+            } else if (!EDGE || gx + 4 <= NX) {
+                *reinterpret_cast<f32x4_a4*>(p) = c[i];
+            } else {
+                p[0] = c[i].x;
+                if (gx + 1 < NX) p[1] = c[i].y;
+                if (gx + 2 < NX) p[2] = c[i].z;
+            }
         }
-    }
+    });
+}
+
+// Tile (bx, by) of the grid cut into tiles of 256 - 2 hc columns and
+// RS * WV - 2 sweeps rows.  hc is a multiple of 4, sweeps <= hc.  VEC: nx is a
+// multiple of 4 and the rows are 16-byte aligned.  NT: whole-line stores that
+// pass the L2 by (for grids far larger than it).
+template <int RS, int WV, bool VEC, bool NT>
+__device__ __forceinline__ void jacobi_tb_block(const float* __restrict__ u, float* __restrict__ v, uint32_t nx,
+                                                uint32_t ny, uint32_t sweeps, uint32_t hc, uint32_t bx, uint32_t by,
+                                                JacobiTbLds<WV>& L) {
+    const int64_t x0 = (int64_t)bx * (JT_W - 2 * hc) - hc, y0 = (int64_t)by * (RS * WV - 2 * sweeps) - sweeps;
+    if (x0 <= 0 || x0 + JT_W >= (int64_t)nx || y0 <= 0 || y0 + RS * WV >= (int64_t)ny)
+        jacobi_tb_region<RS, WV, VEC, NT, true>(u, v, nx, ny, sweeps, hc, x0, y0, L);
+    else
+        jacobi_tb_region<RS, WV, VEC, NT, false>(u, v, nx, ny, sweeps, hc, x0, y0, L);
 }
 
 }  // namespace spmd

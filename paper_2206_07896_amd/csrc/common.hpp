@@ -127,6 +127,11 @@ int launch_reverse_i32(const LaunchCtx& c);
 int launch_compact_i32(const LaunchCtx& c);
 int launch_jacobi5t_f32(const LaunchCtx& c);
 
+// `sweeps` (1..11) fused stencil sweeps of any grid, u to v (no overlap); one
+// kernel (k_jacobi_tb.hip).
+int jacobi_tb_enqueue(const float* u, float* v, uint32_t nx, uint32_t ny, uint32_t sweeps, size_t dyn_shmem,
+                      const DevInfo* dev, hipStream_t stream);
+
 size_t ws_reduce_i32(spmd_dim3 grid, spmd_dim3 block, uint64_t n);
 
 }  // namespace spmd

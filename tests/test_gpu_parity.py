@@ -406,6 +406,29 @@ def test_jacobi_fused_bit_exact(spmd, sweeps):
         assert np.array_equal(got, oracle.jacobi5_f32_sweeps(u, sweeps)), (ny, nx)
 
 
+@pytest.mark.parametrize("ny,nx,sweeps", [
+    (8, 240, 8), (9, 244, 8), (16, 240, 4), (17, 248, 4),      # 24-row regions, at and past one tile
+    (600, 1204, 5), (595, 1208, 5),                            # 32
+    (5000, 4, 8), (1024, 1024, 7), (1023, 1028, 7),            # 40
+    (2100, 484, 8), (2049, 480, 8),                            # 48
+    (900, 2000, 8), (2048, 2048, 8),                           # 64
+    (1800, 8192, 8), (1761, 8188, 7), (2048, 8192, 1),         # 96, where its tiles fill the device
+])
+def test_jacobi_fused_regions(spmd, ny, nx, sweeps):
+    """Every region height, with whole and ragged tiles, against the oracle's
+    sweeps; cells past the grid stay as they were."""
+    import torch
+
+    say("jacobi fused regions", ny, nx, sweeps)
+    u = synth.uniform_f32(0x7B + nx + ny, ny * nx).reshape(ny, nx)
+    out = torch.full((ny + 2, nx), -3.0, device="cuda")
+    spmd.ops.jacobi5t_f32(dev(u), sweeps, out[1:-1])
+    spmd.sync()
+    got = host(out)
+    assert np.array_equal(got[1:-1], oracle.jacobi5_f32_sweeps(u, sweeps))
+    assert (got[0] == -3.0).all() and (got[-1] == -3.0).all()
+
+
 def test_jacobi_fused_chain_and_closed_form(spmd):
     """27 sweeps as 8 + 8 + 8 + 3 fused launches against the oracle, and the
     linear field u = i + 2j, a fixed point of the stencil, through 8."""
