@@ -99,7 +99,10 @@ int spmd_batch_create(const spmd_batch_item* items, const spmd_schedule* sched, 
  * means none.  Instance i then sits one dependency level above dep[i]; each
  * run executes the levels one after another, every level as one persistent
  * kernel per (class, block size) queue present in it, so a chain such as
- * 100 Jacobi sweeps is one batch, one graph, and no host round trip.  An
+ * 100 Jacobi sweeps is one batch, one graph, and no host round trip.  Sweeps
+ * that take turns between two buffers, each alone in its level, run several to
+ * a kernel (a buffer then holds no sweep in between, only what the last one of
+ * the batch to write it leaves there).  An
  * instance may read from several earlier instances as long as they all sit
  * below its level (levels are ordered as a whole).  A HIST instance's bins
  * are cleared in stream order just before its own level, so an instance of
@@ -114,9 +117,9 @@ size_t spmd_batch_workspace_size_dep(const spmd_batch_item* items, const spmd_sc
 int spmd_batch_create_dep(const spmd_batch_item* items, const spmd_schedule* sched, const uint32_t* dep, int n,
                           void* workspace, size_t ws_bytes, uint32_t workers_per_cu, spmd_batch** out);
 
-/* Run the batch on `stream`: a prologue kernel clears the per-run state,
- * then, level by level, one persistent kernel per non-empty (class, block
- * size) queue drains it. */
+/* Run the batch on `stream`: a prologue kernel clears the queues' state, if
+ * there are any, then, level by level, one persistent kernel per non-empty
+ * (class, block size) queue drains it. */
 int spmd_batch_launch(spmd_batch* b, void* stream);
 
 /* The same work as spmd_batch_launch, replayed from a hipGraph captured on

@@ -408,6 +408,81 @@ def test_dependent_jacobi_chain_in_one_batch(spmd, sched, nx):
     b.close()
 
 
+@pytest.mark.parametrize("nx,ny", [(64, 65), (233, 300), (301, 299), (1024, 700), (2047, 601), (1, 40), (2, 2)])
+def test_stencil_chains_share_kernels(spmd, nx, ny):
+    """Chains of every length that cuts into other groups of fused sweeps
+    leave both buffers as the sweeps one by one do, rows at any alignment,
+    and nothing around the grids changes."""
+    import torch
+
+    u = synth.uniform_f32(0xC4A1 + nx, ny * nx).reshape(ny, nx)
+    n = nx * ny
+    for sweeps in (1, 2, 3, 4, 5, 12, 13, 24, 25, 100):
+        say("stencil chain", nx, ny, sweeps)
+        store = [torch.full((n + 2,), -2.0, device="cuda") for _ in range(2)]
+        bufs = [s[1:-1] for s in store]
+        bufs[0].copy_(torch.from_numpy(u.ravel()))
+        items = [(spmd.JACOBI5_F32, nx, ny, 256, bufs[t % 2], bufs[(t + 1) % 2]) for t in range(sweeps)]
+        bpf = sweeps % 2 * 8
+        b = spmd.batch.Batch(items, [(256, 4, bpf)] * sweeps, deps=[None] + list(range(sweeps - 1)))
+        b.launch() if sweeps % 3 else b.graph_launch()
+        spmd.sync()
+        assert b.stats()["persistent_launches"] <= 1 + sweeps
+        b.close()
+        for back in (0, 1):  # the last sweep, and the one before it
+            want = oracle.jacobi5_f32_sweeps(u, sweeps - back)
+            got = host(store[(sweeps - back) % 2])
+            assert np.array_equal(got[1:-1].reshape(ny, nx), want), (sweeps, back)
+            assert got[0] == -2.0 and got[-1] == -2.0
+
+
+def test_stencil_chains_read_in_between(spmd):
+    """Sweeps whose buffers someone else reads, that keep a buffer out of the
+    turn, or that change the grid stay single where that shows."""
+    import torch
+
+    nx, ny = 130, 77
+    n = nx * ny
+    u = synth.uniform_f32(0xC4A2, n).reshape(ny, nx)
+    say("stencil chain with readers")
+    a, b, c = (torch.full((ny, nx), -2.0, device="cuda") for _ in range(3))
+    total = torch.empty(1, dtype=torch.int32, device="cuda")
+    J = spmd.JACOBI5_F32
+    items, deps, sched = [], [], []
+
+    def add(item, dep, bpf=0):
+        items.append(item)
+        deps.append(dep)
+        sched.append((256, 4, bpf))
+        return len(items) - 1
+
+    last, bufs = None, [a, b]
+    for t in range(9):  # sweeps 1..9, b holds 9 and a holds 8
+        last = add((J, nx, ny, 256, bufs[t % 2], bufs[(t + 1) % 2]), last)
+        if t == 4:  # a reader of sweep 5 beside sweep 6, which reads it too
+            add((spmd.REDUCE_I32, n, 1, 256, b.view(-1).view(torch.int32), total), last, 4)
+    last = add((J, nx, ny, 256, b, c), last)      # 10, into a third buffer
+    for t in range(5):                            # 11..15, c and a take turns
+        last = add((J, nx, ny, 256, [c, a][t % 2], [a, c][t % 2]), last)
+    last = add((J, nx, ny - 5, 256, a, c), last)  # another grid
+    b9 = spmd.batch.Batch(items, sched, deps=deps)
+    for mode in ("eager", "graph", "graph"):
+        a.copy_(torch.from_numpy(u))
+        b.fill_(-1.0)
+        c.fill_(-1.0)
+        b9.launch() if mode == "eager" else b9.graph_launch()
+        spmd.sync()
+        sweeps = {k: oracle.jacobi5_f32_sweeps(u, k) for k in (5, 9, 14, 15)}
+        want = sweeps[14].copy()
+        want[: ny - 5] = oracle.jacobi5_f32_sweeps(np.ascontiguousarray(sweeps[15][: ny - 5]), 1)
+        assert np.array_equal(host(b), sweeps[9]), mode
+        assert np.array_equal(host(a), sweeps[15]), mode
+        assert np.array_equal(host(c), want), mode
+        bits = sweeps[5].ravel().view(np.int32)
+        assert int(host(total)[0]) == int(np.int64(bits.astype(np.int64).sum()).astype(np.int32)), mode
+    b9.close()
+
+
 def test_dependency_across_queues(spmd):
     """Three levels over queues in both orders: a Jacobi sweep, a scan of
     its output bits (the SCAN queue comes before the JACOBI queue in the
