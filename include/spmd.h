@@ -107,8 +107,8 @@ enum {
     /* One sweep of the 5-point Laplace-Jacobi stencil on an ny x nx
      * row-major fp32 grid: interior u'[i][j] = 0.25f*((u[i-1][j] +
      * u[i+1][j]) + (u[i][j-1] + u[i][j+1])), each operation rounded to
-     * fp32 in that order; border cells copied.  Each block stages its tile
-     * and a one-cell halo in LDS, barrier, then computes.
+     * fp32 in that order; border cells copied.  Waves hold their cells and
+     * the neighbours' rows in registers.
      * args: const float* u, float* u_next, uint32_t nx, uint32_t ny
      * block (BX,BY,1) with (BX,BY) in {(16,16), (32,8), (64,1), (64,2),
      * (64,4), (64,8), (128,2), (128,4), (256,1)}; grid (GX,GY,1) with GX*BX >= nx; each

@@ -106,22 +106,9 @@ template <int B>
 struct BatchLdsOf<SPMD_HIST256_U32, B> {
     HistLds<HIST_COPIES> h;
 };
-// the 256-column tile of blocks of 256 or 512 threads; nothing for smaller
-// blocks, which run only 64-column blocks
-template <int B, int C>
-using WideJacobiLds = std::conditional_t<(B >= 256), JacobiWLds<B / 64, C>, char>;
-
 template <int B>
 struct BatchLdsOf<SPMD_JACOBI5_F32, B> {
-    union {
-        JacobiLds<64, B / 64, 1> j1;
-        JacobiLds<64, B / 64, 2> j2;
-        JacobiLds<64, B / 64, 4> j4;
-        JacobiLds<64, B / 64, 8> j8;
-        WideJacobiLds<B, 1> w1;  // 256-column groups (blocks of 256 and 512 threads only)
-        WideJacobiLds<B, 2> w2;
-        WideJacobiLds<B, 4> w4;
-    };
+    char none;  // strips live in registers
 };
 
 template <int CLS, int B, typename Hook = NoHook>
@@ -156,76 +143,30 @@ __device__ __forceinline__ void run_logical_block(const BatchDesc& d, uint32_t b
         const uint64_t hi = lo + d.aux < (uint64_t)d.n ? lo + d.aux : (uint64_t)d.n;
         hist_block<B, HIST_COPIES>(reinterpret_cast<const uint32_t*>(d.in), reinterpret_cast<uint32_t*>(d.out), lo,
                                    hi, d.vec != 0u, L.h);
-    } else {
-        const float* u = reinterpret_cast<const float*>(d.in);
-        float* v = reinterpret_cast<float*>(d.out);
-        const uint32_t bx = b % d.aux, by = b / d.aux;
-        const int tx = (int)(t & 63u), ty = (int)(t >> 6);
-        switch (d.items) {
-        case 1: jacobi_block<64, B / 64, 1>(u, v, d.n, d.ny, bx, by, tx, ty, L.j1); break;
-        case 2: jacobi_block<64, B / 64, 2>(u, v, d.n, d.ny, bx, by, tx, ty, L.j2); break;
-        case 4: jacobi_block<64, B / 64, 4>(u, v, d.n, d.ny, bx, by, tx, ty, L.j4); break;
-        default: jacobi_block<64, B / 64, 8>(u, v, d.n, d.ny, bx, by, tx, ty, L.j8); break;
-        }
     }
 }
 
-// JACOBI: the logical blocks of one chunk as a two-stage pipeline -- block
-// b+1's global loads are issued before block b's are waited on, so a
-// workgroup keeps two tiles' loads in flight.  (Two named register sets,
-// not an indexed pair, so nothing goes to scratch.)  Every cell is computed
-// as in jacobi_block.
+// JACOBI: the logical blocks (64 columns x B/64 * C rows) of one chunk, up to
+// four neighbours of a row at a time, as far as a multiple of 256 columns; wave
+// w runs rows w * C on of theirs as one strip.  Every cell is computed as in its
+// own block.  Against LDS tiles with a barrier per tile: 400 mixed launches of
+// up to 2^22 elements 340 us (375), 2000 of up to 2^20 419 us (454), 2000 of up
+// to 2^22 the same 1180; the stencil queue of those, 2.2 GB in 0.50 ms, is held
+// by HBM's rate for many rows of odd widths at once (4.6 TB/s), not by its
+// traffic (1.1 of the least).
 template <int B, int C>
-__device__ __forceinline__ void jacobi_chunk(const BatchDesc& d, uint32_t first, uint32_t last,
-                                             JacobiLds<64, B / 64, C>& L) {
-    constexpr int BY = B / 64;
+__device__ __forceinline__ void jacobi_chunk(const BatchDesc& d, uint32_t first, uint32_t last) {
     const float* u = reinterpret_cast<const float*>(d.in);
     float* v = reinterpret_cast<float*>(d.out);
-    const int tx = (int)(threadIdx.x & 63u), ty = (int)(threadIdx.x >> 6);
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t w = d.aux;  // blocks per row
-    JacobiRegs<64, BY, C> R0, R1;
-    jacobi_load<64, BY, C>(u, d.n, d.ny, first % w, first / w, tx, ty, R0);
-    for (uint32_t b = first; b < last; b += 2) {
-        if (b + 1 < last) jacobi_load<64, BY, C>(u, d.n, d.ny, (b + 1) % w, (b + 1) / w, tx, ty, R1);
-        jacobi_commit<64, BY, C>(tx, ty, R0, L);
-        __syncthreads();
-        jacobi_compute<64, BY, C>(v, d.n, d.ny, b % w, b / w, tx, ty, L);
-        __syncthreads();  // the next commit reuses the LDS tile
-        if (b + 1 >= last) break;
-        if (b + 2 < last) jacobi_load<64, BY, C>(u, d.n, d.ny, (b + 2) % w, (b + 2) / w, tx, ty, R0);
-        jacobi_commit<64, BY, C>(tx, ty, R1, L);
-        __syncthreads();
-        jacobi_compute<64, BY, C>(v, d.n, d.ny, (b + 1) % w, (b + 1) / w, tx, ty, L);
-        __syncthreads();
-    }
-}
-
-// JACOBI, blocks of 256 or 512 threads: inside a chunk, every run of up to
-// four 64-column blocks of one row that starts at a multiple of four
-// columns-of-blocks and lies wholly in the chunk runs as one 256-column
-// tile of the general-width form (jacobi_block_w: each thread four columns
-// 64 apart, a wave's loads of a row 1 KiB contiguous); other blocks run one
-// by one.  Every cell is computed as in jacobi_block.
-template <int B, int C>
-__device__ __forceinline__ void jacobi_chunk_grouped(const BatchDesc& d, uint32_t first, uint32_t last,
-                                                     JacobiLds<64, B / 64, C>& L64, JacobiWLds<B / 64, C>& LW) {
-    constexpr int BY = B / 64;
-    const float* u = reinterpret_cast<const float*>(d.in);
-    float* v = reinterpret_cast<float*>(d.out);
-    const int tx = (int)(threadIdx.x & 63u), ty = (int)(threadIdx.x >> 6);
-    const uint32_t w = d.aux;  // 64-column blocks per row
-    uint32_t b = first;
-    while (b < last) {
+    uint32_t run;
+    for (uint32_t b = first; b < last; b += run) {
         const uint32_t bx = b % w, by = b / w;
-        const uint32_t run = min(4u, w - bx);  // blocks of this 256-column group in the row
-        if ((bx & 3u) == 0u && b + run <= last) {
-            jacobi_block_w<BY, C>(u, v, d.n, d.ny, bx >> 2, by, tx, ty, LW);
-            b += run;
-        } else {
-            jacobi_block<64, BY, C>(u, v, d.n, d.ny, bx, by, tx, ty, L64);
-            b += 1;
-        }
-        __syncthreads();  // the next tile reuses the LDS
+        run = min(min(4u - (bx & 3u), w - bx), last - b);
+        const int64_t y0 = ((int64_t)by * (B / 64) + wave) * C;
+        const int64_t x0 = 64 * (int64_t)bx, xe = x0 + 64 * run;
+        if (y0 < (int64_t)d.ny) jacobi_strip<C>(u, v, d.n, d.ny, x0, xe < (int64_t)d.n ? xe : (int64_t)d.n, y0);
     }
 }
 
@@ -466,30 +407,11 @@ __global__ __launch_bounds__(B) void batch_persistent_kernel(const BatchDesc* __
                 run_fused_chunk<CLS, B>(d, c - d.chunk0, first, last, L, err);
                 __syncthreads();
             } else {
-                if constexpr (B >= 256) {
-                    switch (d.items) {
-                    case 1: jacobi_chunk_grouped<B, 1>(d, first, last, L.j1, L.w1); break;
-                    case 2: jacobi_chunk_grouped<B, 2>(d, first, last, L.j2, L.w2); break;
-                    case 4: jacobi_chunk_grouped<B, 4>(d, first, last, L.j4, L.w4); break;
-                    default:
-                        for (uint32_t b = first; b < last; ++b) {
-                            run_logical_block<CLS, B>(d, b, L, err, NoHook());
-                            __syncthreads();  // the next logical block reuses the LDS
-                        }
-                        break;
-                    }
-                } else switch (d.items) {
-                case 1: jacobi_chunk<B, 1>(d, first, last, L.j1); break;
-                case 2: jacobi_chunk<B, 2>(d, first, last, L.j2); break;
-                case 4: jacobi_chunk<B, 4>(d, first, last, L.j4); break;
-                default:
-                    // 8 cells per thread already keep about 10 loads in flight
-                    // per thread; a second register set would cost occupancy
-                    for (uint32_t b = first; b < last; ++b) {
-                        run_logical_block<CLS, B>(d, b, L, err, NoHook());
-                        __syncthreads();  // the next logical block reuses the LDS
-                    }
-                    break;
+                switch (d.items) {
+                case 1: jacobi_chunk<B, 1>(d, first, last); break;
+                case 2: jacobi_chunk<B, 2>(d, first, last); break;
+                case 4: jacobi_chunk<B, 4>(d, first, last); break;
+                default: jacobi_chunk<B, 8>(d, first, last); break;
                 }
             }
             if (t < 64) {
@@ -824,8 +746,8 @@ constexpr uint32_t JACOBI_FUSE_MAX = 11;
 
 void fuse_chains(const spmd_batch_item* items, std::vector<BatchSegment>& seg) {
     const size_t nseg = seg.size();
-    auto alone = [&](size_t k) {  // segment k is its level's only one and holds one stencil instance
-        return seg[k].only >= 0 && items[seg[k].only].kernel_id == SPMD_JACOBI5_F32 &&
+    auto alone = [&](size_t k) {  // its level's only segment, one stencil instance in it
+        return seg[k].only >= 0 && items[seg[k].only].kernel_id == SPMD_JACOBI5_F32 && items[seg[k].only].n >= 4 &&
                (k == 0 || seg[k - 1].level != seg[k].level) && (k + 1 == nseg || seg[k + 1].level != seg[k].level);
     };
     for (size_t lo = 0; lo < nseg;) {

@@ -38,9 +38,6 @@
 // pipe, a border test per cell, and 64-row tiles of 152 registers.  8 sweeps
 // of a small grid (192 x 74): 5.2 us, 18.8 before.
 #pragma once
-#include <type_traits>
-#include <utility>
-
 #include "cls_jacobi.hpp"
 
 namespace spmd {
@@ -48,32 +45,10 @@ namespace spmd {
 constexpr int JT_W = 256;         // columns of a region
 constexpr int JT_MAX_SWEEPS = 11;  // fused at most (the smallest region is 24 rows)
 
-typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));  // 16 bytes at any float's address
-
 template <int WV>
 struct JacobiTbLds {
     f32x4 edge[2][2][WV][64];  // [sweep parity][first row, last row][wave][lane]
 };
-
-// f(0), ..., f(N - 1) with the index a constant.  A loop over the band's rows
-// is unrolled late, after an array of up to 32 registers has been taken for
-// one vector and copied whole on every write (bands of 8 rows or fewer spilled).
-template <typename F, int... I>
-__device__ __forceinline__ void each_row(F f, std::integer_sequence<int, I...>) {
-    (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, typename F>
-__device__ __forceinline__ void each_row(F f) {
-    each_row(f, std::make_integer_sequence<int, N>{});
-}
-
-// The value of the lane to the left (right); lane 0 (63) gets zero.
-__device__ __forceinline__ float lane_left(float v) {
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x138, 0xf, 0xf, true));  // wave_shr:1
-}
-__device__ __forceinline__ float lane_right(float v) {
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x130, 0xf, 0xf, true));  // wave_shl:1
-}
 
 // S sweeps of the band in `c`.  EDGE: the region holds border cells of the
 // grid: `keep` marks this lane's border columns, and rows `top` and `bottom`
@@ -98,10 +73,10 @@ __device__ __forceinline__ void jacobi_tb_sweeps(f32x4 (&c)[RS], uint32_t sweeps
             if constexpr (i + 2 < RS) ns_next += c[i + 2];
             else ns_next += dn;
             f32x4 we;
-            we.x = lane_left(cur.w) + cur.y;
+            we.x = lane_left(cur.w, 0.0f) + cur.y;
             we.y = cur.x + cur.z;
             we.z = cur.y + cur.w;
-            we.w = cur.z + lane_right(cur.x);
+            we.w = cur.z + lane_right(cur.x, 0.0f);
             f32x4 o = 0.25f * (ns + we);
             if constexpr (EDGE) {
                 const bool same = i == top || i == bottom;  // wave-uniform
@@ -134,27 +109,25 @@ __device__ __forceinline__ void jacobi_tb_region(const float* __restrict__ u, fl
     const f32x4 z = {0.0f, 0.0f, 0.0f, 0.0f};
 
     f32x4 c[RS];
-    const bool cols = !EDGE || (gx >= 0 && gx + 4 <= NX);  // all four columns are inside
+    const bool cols = !EDGE || (gx >= 0 && gx < NX);
+    const bool cut = EDGE && !VEC && gx < NX && gx + 4 > NX;  // by the row's end: reads the row's last 16 bytes
+    const int at = (int)(cut ? NX - 4 - x0 : 4 * lane);
     each_row<RS>([&](auto row) __attribute__((always_inline)) {
         constexpr int i = row;
         c[i] = z;
         if (i >= r0 && i < r1 && cols) {
-            const float* p = u + (origin + i * NX) + 4 * lane;
+            const float* p = u + (origin + i * NX) + at;
             using vec = std::conditional_t<VEC, f32x4, f32x4_a4>;
             c[i] = *reinterpret_cast<const vec*>(p);
         }
     });
-    if (EDGE && !VEC && gx < NX && gx + 4 > NX) {  // the last columns of an odd width
+    if (EDGE && !VEC && (NX & 3) && x0 + JT_W > NX)  // block-uniform
         each_row<RS>([&](auto row) __attribute__((always_inline)) {
             constexpr int i = row;
-            if (i >= r0 && i < r1) {
-                const float* p = u + (origin + i * NX) + 4 * lane;
-                c[i].x = p[0];
-                if (gx + 1 < NX) c[i].y = p[1];
-                if (gx + 2 < NX) c[i].z = p[2];
-            }
+            const f32x4 e = row_end(c[i], gx + 4 - NX);
+            c[i] = cut ? e : c[i];
+            __builtin_amdgcn_sched_barrier(0);
         });
-    }
 
     bool keep[4];
 #pragma unroll
@@ -187,7 +160,7 @@ __device__ __forceinline__ void jacobi_tb_region(const float* __restrict__ u, fl
 }
 
 // Tile (bx, by) of the grid cut into tiles of 256 - 2 hc columns and
-// RS * WV - 2 sweeps rows.  hc is a multiple of 4, sweeps <= hc.  VEC: nx is a
+// RS * WV - 2 sweeps rows.  nx >= 4, hc is a multiple of 4, sweeps <= hc.  VEC: nx is a
 // multiple of 4 and the rows are 16-byte aligned.  NT: whole-line stores that
 // pass the L2 by (for grids far larger than it).
 template <int RS, int WV, bool VEC, bool NT>

@@ -127,7 +127,7 @@ int launch_reverse_i32(const LaunchCtx& c);
 int launch_compact_i32(const LaunchCtx& c);
 int launch_jacobi5t_f32(const LaunchCtx& c);
 
-// `sweeps` (1..11) fused stencil sweeps of any grid, u to v (no overlap); one
+// `sweeps` (1..11) fused stencil sweeps of a grid of nx >= 4, u to v (no overlap); one
 // kernel (k_jacobi_tb.hip).
 int jacobi_tb_enqueue(const float* u, float* v, uint32_t nx, uint32_t ny, uint32_t sweeps, size_t dyn_shmem,
                       const DevInfo* dev, hipStream_t stream);

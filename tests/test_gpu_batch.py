@@ -408,6 +408,35 @@ def test_dependent_jacobi_chain_in_one_batch(spmd, sched, nx):
     b.close()
 
 
+@pytest.mark.parametrize("block", [64, 128, 256, 512])
+@pytest.mark.parametrize("bpf", [1, 2, 3, 5, 7, 32])
+def test_stencil_chunks_of_any_run(spmd, block, bpf):
+    """Chunks that begin and end anywhere in a row of blocks, every cells
+    count, widths around multiples of 64 and 256, odd addresses."""
+    import torch
+
+    say("stencil chunks", block, bpf)
+    items, sched, want, outs = [], [], [], []
+    for cells in (1, 2, 4, 8):
+        for ny, nx in ((37, 63), (19, 257), (70, 321), (66, 449), (9, 1030)):
+            u = synth.uniform_f32(0xB10 + nx + cells, ny * nx).reshape(ny, nx)
+            src = torch.empty(ny * nx + 3, device="cuda")
+            src[3:].copy_(torch.from_numpy(u.ravel()))
+            out = torch.full((ny * nx + 2,), -4.0, device="cuda")
+            items.append((spmd.JACOBI5_F32, nx, ny, block, src[3:], out[1:-1]))
+            sched.append((block, cells, bpf))
+            want.append(oracle.jacobi5_f32(u, 16, 16).ravel())
+            outs.append(out)
+    b = spmd.batch.Batch(items, sched)
+    b.launch()
+    spmd.sync()
+    for o, w, it, s in zip(outs, want, items, sched):
+        got = host(o)
+        assert np.array_equal(got[1:-1], w), (it[1:3], s)
+        assert got[0] == -4.0 and got[-1] == -4.0, (it[1:3], s)
+    b.close()
+
+
 @pytest.mark.parametrize("nx,ny", [(64, 65), (233, 300), (301, 299), (1024, 700), (2047, 601), (1, 40), (2, 2)])
 def test_stencil_chains_share_kernels(spmd, nx, ny):
     """Chains of every length that cuts into other groups of fused sweeps

@@ -346,6 +346,23 @@ def test_jacobi_one_sweep(spmd, block, cells):
         assert np.array_equal(got, want)
 
 
+@pytest.mark.parametrize("ny,nx", [(5, 255), (5, 256), (6, 258), (7, 259), (9, 511), (8, 513), (70001, 3), (300000, 4),
+                                   (4097, 8190), (4096, 8192), (4100, 8191)])  # the last: one row per wave
+def test_jacobi_strips(spmd, ny, nx):
+    """Strip ends at every remainder of a lane's four columns, tall grids and
+    both row counts; cells past the grid stay as they were."""
+    import torch
+
+    say("jacobi strips", ny, nx)
+    u = synth.uniform_f32(0x57B + nx, ny * nx).reshape(ny, nx)
+    out = torch.full((ny * nx + 8,), -3.0, device="cuda")
+    spmd.ops.jacobi5_f32(dev(u), out=out[4:-4].view(ny, nx), block=(64, 4), cells=4)
+    spmd.sync()
+    got = host(out)
+    assert np.array_equal(got[4:-4].reshape(ny, nx), oracle.jacobi5_f32(u, 16, 16))
+    assert (got[:4] == -3.0).all() and (got[-4:] == -3.0).all()
+
+
 def test_jacobi_misaligned_rows(spmd):
     """nx a multiple of 4 but the grid one float into its buffer: rows are
     not 16-byte aligned, so the general-width form runs."""
