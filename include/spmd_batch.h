@@ -123,7 +123,7 @@ int spmd_batch_create_dep(const spmd_batch_item* items, const spmd_schedule* sch
 int spmd_batch_launch(spmd_batch* b, void* stream);
 
 /* The same work as spmd_batch_launch, replayed from a hipGraph captured on
- * the first call. */
+ * the first call; a run of a few kernels in a row is enqueued as it is. */
 int spmd_batch_graph_launch(spmd_batch* b, void* stream);
 
 /* The baseline: every instance as its own grid, one spmd_launch-equivalent

@@ -35,6 +35,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <mutex>
 #include <type_traits>
@@ -462,6 +463,8 @@ struct BatchSegment {
     RangeTable ranges;  // its chunk ranges (queues only)
 };
 
+constexpr uint32_t BATCH_STREAMS = 20;  // of one level at most, the caller's among them
+
 struct SegKey {
     uint32_t level;
     int group;
@@ -493,15 +496,19 @@ struct spmd_batch {
     std::vector<uint32_t> hist_lo;
     uint64_t total_blocks = 0, total_chunks = 0;
     uint32_t each_launches = 0, run_launches = 0;
+    bool few = false;     // a handful of kernels in a row: enqueued as they are
     bool queued = false;  // some segment runs from a queue (the prologue clears the run area)
     const DevInfo* dev = nullptr;
     hipStream_t cap_stream = nullptr;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
-    // fork/join of the segment kernels of one level over side streams
-    // (levels with two or more segments); per level / per segment, null
-    // where unused, all null when the segments run in order
-    std::vector<hipEvent_t> ev_fork, ev_join;
+    // the stream of each segment (0: the caller's, else a side stream) and
+    // the streams of each level
+    std::vector<uint32_t> lane, lanes;
+    // fork of a level onto its side streams and their joins, null where
+    // unused, empty when the segments run in order
+    std::vector<hipEvent_t> ev_fork;
+    std::vector<std::array<hipEvent_t, BATCH_STREAMS - 1>> ev_join;
 };
 
 namespace {
@@ -650,6 +657,46 @@ std::vector<uint32_t> launch_order(const std::vector<double>& cost, const Layout
         return cost[a] > cost[b];
     });
     return order;
+}
+
+// Streams of a level's segments, given in launch order with their estimated
+// bytes.  A stream of its own for each costs the host and the replay of a graph
+// about 25 us more for the second and 7 us for each further one, and pays where
+// there is that much to overlap: from about 150 MB on (200 mixed launches of
+// up to 2^22 elements, 300 MB: 136 us against 151 on four streams; 800 of up to
+// 2^20, 720 MB: 183 against 209).  Below, as few streams as the estimate of a
+// segment's time (5 us, then 4.5 MB/us) says, up to four, each segment on the
+// one that is free first: 5 launches of up to 2^16 30 us against 59, 50 75
+// against 96, 800 86 against 106.
+constexpr double SEG_START_US = 5.0, SEG_BYTES_PER_US = 4.5e6, ALL_BYTES_PER_US = 5.0e6, OWN_STREAM_BYTES = 150e6;
+
+uint32_t assign_streams(const std::vector<double>& bytes, std::vector<uint32_t>& lane) {
+    const uint32_t nseg = (uint32_t)bytes.size();
+    double total = 0.0;
+    for (double b : bytes) total += b;
+    lane.assign(nseg, 0);
+    if (total >= OWN_STREAM_BYTES) {
+        for (uint32_t k = 0; k < nseg; ++k) lane[k] = k % BATCH_STREAMS;
+        return std::min(nseg, BATCH_STREAMS);
+    }
+    uint32_t best = 1;
+    double least = INFINITY;
+    for (uint32_t n = 1; n <= 4 && n <= nseg; ++n) {
+        double load[4] = {};
+        std::vector<uint32_t> at(nseg);
+        for (uint32_t k = 0; k < nseg; ++k) {
+            at[k] = (uint32_t)(std::min_element(load, load + n) - load);
+            load[at[k]] += SEG_START_US + bytes[k] / SEG_BYTES_PER_US;
+        }
+        const double t = std::max(*std::max_element(load, load + n), total / ALL_BYTES_PER_US) +
+                         (n > 1 ? 18.0 + 7.0 * (n - 1) : 0.0);
+        if (t < least) {
+            least = t;
+            best = n;
+            lane = at;
+        }
+    }
+    return best;
 }
 
 // Dependency levels: dep[i] is an earlier instance (dep[i] < i) or NO_DEP;
@@ -819,20 +866,20 @@ void launch_group(uint32_t block, dim3 gr, hipStream_t s, const BatchDesc* descs
     }
 }
 
-// Side streams for the group kernels, per device, created once with the
+// Side streams for the segment kernels, per device, created once with the
 // device current and kept for the life of the process (default priority).
 // A run forks them from the caller's stream with an event and joins them
-// back with one event per group, so runs on one stream stay ordered and a
-// captured run becomes a graph with one branch per group.
+// back with one event each, so runs on one stream stay ordered and a
+// captured run becomes a graph with one branch per stream.
 std::mutex g_side_mu;
-hipStream_t g_side[64][NGROUPS];
+hipStream_t g_side[64][BATCH_STREAMS - 1];
 bool g_side_ready[64];
 
 int side_streams(const DevInfo* di, hipStream_t** out) {
     std::lock_guard<std::mutex> lk(g_side_mu);
     if (di->device < 0 || di->device >= 64) return SPMD_ERR_HIP;
     if (!g_side_ready[di->device]) {
-        for (int g = 0; g < NGROUPS; ++g) {
+        for (uint32_t g = 0; g < BATCH_STREAMS - 1; ++g) {
             hipError_t e = hipStreamCreateWithFlags(&g_side[di->device][g], hipStreamNonBlocking);
             if (e != hipSuccess) return hip_fail(e);
         }
@@ -931,27 +978,25 @@ int enqueue_run(spmd_batch* b, hipStream_t s) {
                                hist_list + b->hist_lo[lev]);
             if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e);
         }
-        const bool fork = hi - lo >= 2 && lev < b->ev_fork.size() && b->ev_fork[lev] != nullptr;
-        if (fork) {
+        const uint32_t lanes = lev < b->ev_fork.size() ? b->lanes[lev] : 1u;
+        if (lanes > 1) {
             int rc = side ? SPMD_OK : side_streams(b->dev, &side);
             if (rc) return rc;
             if ((e = hipEventRecord(b->ev_fork[lev], s)) != hipSuccess) return hip_fail(e);
+            for (uint32_t q = 1; q < lanes; ++q)
+                if ((e = hipStreamWaitEvent(side[q - 1], b->ev_fork[lev], 0)) != hipSuccess) return hip_fail(e);
         }
         for (size_t pos = lo; pos < hi; ++pos) {
             const size_t k = b->order[pos];  // the level's segments, longest first
-            hipStream_t gs = s;
-            if (fork) {
-                gs = side[pos - lo];
-                if ((e = hipStreamWaitEvent(gs, b->ev_fork[lev], 0)) != hipSuccess) return hip_fail(e);
-            }
+            hipStream_t gs = lanes > 1 && b->lane[k] ? side[b->lane[k] - 1] : s;
             const BatchSegment& g = b->seg[k];
             int rc = g.direct >= 0 ? launch_direct(b, g.direct, gs)
                                    : launch_segment(b, g, gs, descs, reinterpret_cast<uint32_t*>(b->ws + BATCH_SEG_CURSOR_BYTES * k), err);
             if (rc) return rc;
-            if (fork) {
-                if ((e = hipEventRecord(b->ev_join[k], gs)) != hipSuccess) return hip_fail(e);
-                if ((e = hipStreamWaitEvent(s, b->ev_join[k], 0)) != hipSuccess) return hip_fail(e);
-            }
+        }
+        for (uint32_t q = 1; q < lanes; ++q) {
+            if ((e = hipEventRecord(b->ev_join[lev][q - 1], side[q - 1])) != hipSuccess) return hip_fail(e);
+            if ((e = hipStreamWaitEvent(s, b->ev_join[lev][q - 1], 0)) != hipSuccess) return hip_fail(e);
         }
         lo = hi;
     }
@@ -961,8 +1006,9 @@ int enqueue_run(spmd_batch* b, hipStream_t s) {
 void destroy_events(spmd_batch* b) {
     for (hipEvent_t ev : b->ev_fork)
         if (ev) hipEventDestroy(ev);
-    for (hipEvent_t ev : b->ev_join)
-        if (ev) hipEventDestroy(ev);
+    for (const auto& join : b->ev_join)
+        for (hipEvent_t ev : join)
+            if (ev) hipEventDestroy(ev);
     b->ev_fork.clear();
     b->ev_join.clear();
 }
@@ -1127,21 +1173,39 @@ int spmd_batch_create_dep(const spmd_batch_item* items, const spmd_schedule* sch
         g.ranges = ordered_cls(cls) ? range_table_ordered(g.grid, cmap[k], seg_elems[k])
                                     : range_table(g.grid, g.chunks);
     }
-    // events for the levels that fork over two or more segments
+    // each level's streams, and the events of those that fork
     const uint32_t nlevels = b->seg.back().level + 1;
+    b->lane.assign(nseg, 0);
+    b->lanes.assign(nlevels, 1);
     b->ev_fork.assign(nlevels, nullptr);
-    b->ev_join.assign(nseg, nullptr);
+    b->ev_join.assign(nlevels, {});
     e = hipSuccess;
     for (size_t lo = 0; lo < nseg && e == hipSuccess;) {
         size_t hi = lo;
         while (hi < nseg && b->seg[hi].level == b->seg[lo].level) ++hi;
         if (hi - lo >= 2) {
-            e = hipEventCreateWithFlags(&b->ev_fork[b->seg[lo].level], hipEventDisableTiming);
-            for (size_t k = lo; k < hi && e == hipSuccess; ++k)
-                e = hipEventCreateWithFlags(&b->ev_join[k], hipEventDisableTiming);
+            const uint32_t lev = b->seg[lo].level;
+            std::vector<double> bytes;
+            for (size_t pos = lo; pos < hi; ++pos) bytes.push_back(seg_cost[b->order[pos]]);
+            std::vector<uint32_t> lane;
+            b->lanes[lev] = assign_streams(bytes, lane);
+            for (size_t pos = lo; pos < hi; ++pos) b->lane[b->order[pos]] = lane[pos - lo];
+            if (b->lanes[lev] > 1) e = hipEventCreateWithFlags(&b->ev_fork[lev], hipEventDisableTiming);
+            for (uint32_t q = 1; q < b->lanes[lev] && e == hipSuccess; ++q)
+                e = hipEventCreateWithFlags(&b->ev_join[lev][q - 1], hipEventDisableTiming);
         }
         lo = hi;
     }
+    // A replayed graph costs the host about 20 us and the device some between
+    // its kernels, a kernel's launch 4: two kernels in a row take 10 us against
+    // 21, alone to their end 22 against 41; eight short ones are as fast as a
+    // graph (30 us) and end later (62 against 47).  Fused sweeps outlast their
+    // launch: ten kernels of 1024^2 89 us against 93, and the first run, which
+    // builds no graph, 107 against 186.
+    uint32_t fused = 0;
+    for (const BatchSegment& g : b->seg) fused += g.fused ? 1 : 0;
+    b->few = b->run_launches <= 16 && b->run_launches - fused <= 4 &&
+             *std::max_element(b->lanes.begin(), b->lanes.end()) == 1;
     if (e != hipSuccess) {
         spmd_batch_destroy(b);
         return hip_fail(e);
@@ -1158,6 +1222,12 @@ int spmd_batch_launch(spmd_batch* b, void* stream) {
 int spmd_batch_graph_launch(spmd_batch* b, void* stream) {
     if (!b) return SPMD_ERR_ARGS;
     hipError_t e;
+    if (b->few) {  // a stream being captured takes no graph launch, as ever
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        e = hipStreamIsCapturing(static_cast<hipStream_t>(stream), &capture);
+        if (e == hipSuccess && capture == hipStreamCaptureStatusNone)
+            return enqueue_run(b, static_cast<hipStream_t>(stream));
+    }
     if (!b->exec) {
         if ((e = hipStreamCreateWithFlags(&b->cap_stream, hipStreamNonBlocking)) != hipSuccess) return hip_fail(e);
         if ((e = hipStreamBeginCapture(b->cap_stream, hipStreamCaptureModeThreadLocal)) != hipSuccess) return hip_fail(e);

@@ -465,6 +465,27 @@ def test_stencil_chains_share_kernels(spmd, nx, ny):
             assert got[0] == -2.0 and got[-1] == -2.0
 
 
+@pytest.mark.parametrize("count,log2n", [(1, 10), (3, 10), (5, 12), (30, 10), (30, 21)])
+def test_grids_side_by_side(spmd, count, log2n):
+    """Independent instances that run as their own grids: in a row, on a few
+    streams, and (from 150 MB on) more of them than there are streams."""
+    import torch
+
+    say("grids side by side", count, log2n)
+    n = (1 << log2n) + 7
+    x = [dev(synth.uniform_int32(0x51D + i, n, -1000, 1000)) for i in range(count)]
+    out = torch.zeros(64 * count, dtype=torch.int32, device="cuda")
+    items = [(spmd.REDUCE_I32, n, 1, 256, x[i], out[64 * i:]) for i in range(count)]
+    b = spmd.batch.Batch(items, [(256, 16, 0)] * count)
+    want = [int(host(t).sum()) for t in x]
+    for mode in ("eager", "graph", "graph"):
+        out.zero_()
+        b.launch() if mode == "eager" else b.graph_launch()
+        spmd.sync()
+        assert host(out)[::64].tolist() == want, mode
+    b.close()
+
+
 def test_stencil_chains_read_in_between(spmd):
     """Sweeps whose buffers someone else reads, that keep a buffer out of the
     turn, or that change the grid stay single where that shows."""
