@@ -1,6 +1,7 @@
 """MI355X (gfx950) SPMD kernel-grid executor -- Python binding.
 
-A thin ctypes layer over ``libspmd.so`` (C ABI in ``include/spmd.h``): it
+A thin layer over ``libspmd.so`` (C ABI in ``include/spmd.h``), through ctypes
+and, for launches, the extension module ``_launch`` (``csrc/pylaunch.cpp``): it
 only marshals arguments (tensor -> device pointer, int -> uint32) and turns
 status codes into exceptions.  Every step of every kernel class runs in the
 library's HIP kernels; PyTorch provides device memory and streams.
@@ -18,16 +19,18 @@ import os
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libspmd.so")
 
-if not os.path.exists(LIB_PATH):
+if not os.path.exists(LIB_PATH) or not os.path.exists(os.path.join(_HERE, "_launch.so")):
     raise ImportError(
-        f"{LIB_PATH} is missing: build it with `python paper_2206_07896_amd/build.py` "
+        f"{LIB_PATH} or its launch module is missing: build it with `python paper_2206_07896_amd/build.py` "
         "(hipcc, gfx950); this package has no non-HIP implementation")
 
 # torch first: it ships its own HIP runtime under the same soname as the
 # system one the library links against, and the process shares whichever
 # is loaded first.  Loading torch's first keeps one runtime for both, so
 # device pointers and streams from torch are valid in the library.
-import torch  # noqa: E402,F401
+import torch  # noqa: E402
+
+from . import _launch  # noqa: E402  (csrc/pylaunch.cpp, built with the library)
 
 _lib = ctypes.CDLL(LIB_PATH)
 
@@ -95,8 +98,11 @@ _lib.spmd_error_string.restype = ctypes.c_char_p
 _lib.spmd_last_hip_error.argtypes = []
 _lib.spmd_last_hip_error.restype = ctypes.c_char_p
 
+_launch.bind(ctypes.cast(_lib.spmd_launch, _P).value, ctypes.cast(_lib.spmd_kernel_signature, _P).value)
+
 for _k in range(1, NUM_KERNELS + 1):
     KERNELS[_lib.spmd_kernel_name(_k).decode()] = _k
+_NARGS = {_k: len(_lib.spmd_kernel_signature(_k)) for _k in KERNELS.values()}
 
 
 def lib():
@@ -111,10 +117,15 @@ def _dim3(d) -> Dim3:
     return Dim3(*d)
 
 
+# the current stream's handle without a Stream object around it
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device
+
+
 def _stream_handle(stream) -> int | None:
     if stream is None:
-        import torch
-
+        if _raw_stream is not None and torch.cuda.is_initialized():
+            return _raw_stream(_current_device())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream
@@ -169,10 +180,16 @@ def launch(kernel, grid, block, dyn_shmem: int = 0, args=(), stream=None, events
     kernels.  ``start`` may be None: only ``stop`` is bound (free on the
     stream), to be measured from an earlier event."""
     kid = KERNELS[kernel] if isinstance(kernel, str) else int(kernel)
+    rc = None
+    if events is None and len(args) == _NARGS.get(kid):
+        rc = _launch.launch(kid, grid, block, dyn_shmem, args, _stream_handle(stream))
+        if rc == SPMD_OK:
+            return
     arr, keep = pack_args(kid, list(args))
     argv = ctypes.cast(arr, ctypes.POINTER(ctypes.c_void_p))
     if events is None:
-        rc = _lib.spmd_launch(kid, _dim3(grid), _dim3(block), dyn_shmem, argv, _stream_handle(stream))
+        if rc is None:  # not in the plain forms
+            rc = _lib.spmd_launch(kid, _dim3(grid), _dim3(block), dyn_shmem, argv, _stream_handle(stream))
         what = "spmd_launch"
     else:
         start, stop = (_event_handle(e) for e in events)

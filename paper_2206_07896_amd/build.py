@@ -1,4 +1,5 @@
-"""Build ``libspmd.so`` from the HIP sources in ``csrc/`` for gfx950.
+"""Build ``libspmd.so`` from the HIP sources in ``csrc/`` for gfx950, and
+``_launch.so``, the Python side's launch call, from ``csrc/pylaunch.cpp``.
 
 Every translation unit is compiled with hipcc for gfx950 only, with packed
 fp32 instructions disabled, then linked into one shared library next to this
@@ -13,12 +14,14 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 OUT = os.path.join(HERE, "libspmd.so")
+LAUNCH_OUT = os.path.join(HERE, "_launch.so")
 BUILD_DIR = os.path.join(ROOT, "_build")
 
 ARCH = "gfx950"
@@ -45,6 +48,20 @@ def compile_flags() -> list[str]:
     ]
 
 
+def build_launch(verbose: bool = False) -> str:
+    """The extension module of the Python launch path (host code only)."""
+    tmp = LAUNCH_OUT + f".tmp{os.getpid()}"
+    cmd = [os.environ.get("CXX") or shutil.which("g++") or "c++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           "-I", sysconfig.get_paths()["include"], "-I", INCLUDE, os.path.join(CSRC, "pylaunch.cpp"), "-o", tmp]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"the launch module failed to build:\n{r.stderr}")
+    os.replace(tmp, LAUNCH_OUT)
+    return LAUNCH_OUT
+
+
 def build(verbose: bool = False, jobs: int = 8) -> str:
     os.makedirs(BUILD_DIR, exist_ok=True)
     srcs = sorted(glob.glob(os.path.join(CSRC, "*.hip")))
@@ -61,7 +78,9 @@ def build(verbose: bool = False, jobs: int = 8) -> str:
         return obj
 
     with cf.ThreadPoolExecutor(max_workers=jobs) as ex:
+        launch = ex.submit(build_launch, verbose)
         objs = list(ex.map(one, srcs))
+        launch.result()
     tmp = OUT + f".tmp{os.getpid()}"
     cmd = [cc, "-shared", "-Wl,--no-undefined", f"--offload-arch={ARCH}", "-o", tmp] + objs
     r = subprocess.run(cmd, capture_output=True, text=True)

@@ -419,3 +419,51 @@ def test_batch_rejects_output_over_input(spmd):
         assert not ok(kid, n, ny, base + out_bytes - 4, base), kid            # input starts inside the output
         assert ok(kid, n, ny, base, base + in_bytes), kid                     # adjacent after
         assert ok(kid, n, ny, base + out_bytes, base), kid                    # adjacent before
+
+
+class _Ptr:
+    """A tensor's stand-in: what the launch path asks of one."""
+
+    def __init__(self, p):
+        self.p = p
+
+    def data_ptr(self):
+        return self.p
+
+
+@pytest.mark.parametrize("grid,block", [(7, 256), ((3,), (64, 2)), ((1, 2, 3), (16, 16, 1)), (2**32 + 5, -1),
+                                        ([4, 5], 64), (4.0, 64), ((1, 2, 3, 4), 64), (np.int64(3), 64), (True, 64)])
+@pytest.mark.parametrize("args", [[1 << 40, None, _Ptr(1 << 47), 12, _Ptr(0)], (0, 0, 0, 2**32 - 1, 0),
+                                  [-1, _Ptr(-8), 5, -1, None], [1, 2, 3, 2**33 + 9, 4], [1, 2, 3, 1.0, 4],
+                                  [1, 2, 3, np.int32(4), 5], [True, 2, 3, False, 5], [1, 2, 3, None, 5],
+                                  [1, 2, 3, 4], [1, 2, 3, 4, 5, 6]])
+def test_native_marshalling_equals_ctypes(spmd, grid, block, args):
+    """The launch module packs what the ctypes path packs, or declines (and
+    launch() then takes the ctypes path)."""
+    from paper_2206_07896_amd import _launch
+
+    seen = []
+    proto = ctypes.CFUNCTYPE(ctypes.c_int, ctypes.c_int, spmd.Dim3, spmd.Dim3, ctypes.c_size_t,
+                             ctypes.POINTER(ctypes.c_void_p), ctypes.c_void_p)
+
+    def record(kid, g, b, shm, argv, stream):
+        vals = [ctypes.c_uint64.from_address(argv[i]).value if k == "p" else ctypes.c_uint32.from_address(argv[i]).value
+                for i, k in enumerate("pppup")]
+        seen.append((kid, (g.x, g.y, g.z), (b.x, b.y, b.z), shm, vals, stream))
+        return 0
+
+    fake = proto(record)
+    real = [ctypes.cast(f, ctypes.c_void_p).value for f in (spmd._lib.spmd_launch, spmd._lib.spmd_kernel_signature)]
+    _launch.bind(ctypes.cast(fake, ctypes.c_void_p).value, real[1])
+    try:
+        rc = _launch.launch(spmd.REDUCE_I32, grid, block, 1024, args, 77)
+    finally:
+        _launch.bind(*real)
+    plain = all(type(d) is int or (type(d) is tuple and len(d) <= 3) for d in (grid, block))
+    plain = plain and len(args) == 5 and type(args[3]) is int and type(args[0]) is not bool
+    assert (rc == 0 and len(seen) == 1) if plain else (rc is None and not seen)
+    if plain:
+        arr, keep = spmd.pack_args(spmd.REDUCE_I32, list(args))
+        g, b = spmd._dim3(grid), spmd._dim3(block)
+        record(spmd.REDUCE_I32, g, b, 1024, arr, 77)
+        assert seen[0] == seen[1]
