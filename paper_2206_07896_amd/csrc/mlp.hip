@@ -87,31 +87,19 @@ __device__ __forceinline__ f32x16 load_bias(const float* p) {
     return v;
 }
 
-// 64 model rows of one wave: x[t][s] is normalised input 2s + lane/32 of row
-// 32 t + lane%32.  Returns the prediction of row `lane`.  With STORE, the
-// hidden activations go to h1t/h2t (feature-major), rows row0 + 0..63 below n.
-template <bool STORE>
-__device__ __forceinline__ float forward64(const MlpWeights& S, const float* __restrict__ params,
-                                           const float (&x)[2][DIN / 2], uint32_t row0, uint32_t n, float* h1t,
-                                           float* h2t) {
+// Layers after the first for 32 RT model rows of one wave, h1[t][rt] the first
+// layer's sums (unit tile, row tile).  Returns the prediction of row `lane`
+// (RT 1: of row lane % 32).  With STORE, the hidden activations go to h1t/h2t
+// (feature-major), rows row0 + 0..63 below n.
+template <bool STORE, int RT>
+__device__ __forceinline__ float upper_layers(const MlpWeights& S, const float* __restrict__ params,
+                                              f32x16 (&h1)[2][RT], uint32_t row0, uint32_t n, float* h1t, float* h2t) {
 #pragma clang fp contract(fast)
     const int lane = (int)lane64(), half = lane >> 5;
-    f32x16 h1[2][2];  // [unit tile][row tile]
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-        const f32x16 b = load_bias(S.b1[t][half]);
-        h1[t][0] = b;
-        h1[t][1] = b;
+    for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int q = 0; q < DIN / 4; ++q) {
-            const f32x2 a = *reinterpret_cast<const f32x2*>(S.a1[t][q][lane]);
-#pragma unroll
-            for (int e = 0; e < 2; ++e)
-#pragma unroll
-                for (int rt = 0; rt < 2; ++rt) h1[t][rt] = mfma32(a[e], x[rt][2 * q + e], h1[t][rt]);
-        }
-#pragma unroll
-        for (int rt = 0; rt < 2; ++rt)
+        for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 h1[t][rt][r] = fmaxf(h1[t][rt][r], 0.0f);
@@ -120,12 +108,13 @@ __device__ __forceinline__ float forward64(const MlpWeights& S, const float* __r
                     if (i < n) h1t[(uint64_t)(32 * t + 2 * r + half) * n + i] = h1[t][rt][r];
                 }
             }
-    }
     float y = params[OFF_B3];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
         const f32x16 b = load_bias(S.b2[t][half]);
-        f32x16 h2[2] = {b, b};
+        f32x16 h2[RT];
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) h2[rt] = b;
 #pragma unroll
         for (int q = 0; q < HID / 8; ++q) {
             const f32x4 a = *reinterpret_cast<const f32x4*>(S.a2[t][q][lane]);
@@ -133,14 +122,14 @@ __device__ __forceinline__ float forward64(const MlpWeights& S, const float* __r
             for (int e = 0; e < 4; ++e) {
                 const int s = 4 * q + e;  // units 2s and 2s + 1 of the first layer
 #pragma unroll
-                for (int rt = 0; rt < 2; ++rt) h2[rt] = mfma32(a[e], h1[s >> 4][rt][s & 15], h2[rt]);
+                for (int rt = 0; rt < RT; ++rt) h2[rt] = mfma32(a[e], h1[s >> 4][rt][s & 15], h2[rt]);
             }
         }
-        // Exchanging halves puts one unit of all 64 rows into a register
+        // Exchanging halves puts one unit of all rows into a register
         // (row = lane), and the last layer's sum runs over the units in order.
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            const float v0 = fmaxf(h2[0][r], 0.0f), v1 = fmaxf(h2[1][r], 0.0f);
+            const float v0 = fmaxf(h2[0][r], 0.0f), v1 = fmaxf(h2[RT - 1][r], 0.0f);
             const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(v0), __float_as_uint(v1), false, false);
             const float u0 = __uint_as_float(sw[0]), u1 = __uint_as_float(sw[1]);
             const int j = 32 * t + 2 * r;
@@ -156,6 +145,24 @@ __device__ __forceinline__ float forward64(const MlpWeights& S, const float* __r
         }
     }
     return y;
+}
+
+// The first layer's k steps 2 Q0 .. 5 on top of h1; x[rt][s] is normalised input
+// 4 Q0 + 2s + lane/32 of row 32 rt + lane%32.
+template <int Q0, int RT>
+__device__ __forceinline__ void first_layer(const MlpWeights& S, const float (&x)[RT][DIN / 2 - 2 * Q0],
+                                            f32x16 (&h1)[2][RT]) {
+    const int lane = (int)lane64();
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int q = Q0; q < DIN / 4; ++q) {
+            const f32x2 a = *reinterpret_cast<const f32x2*>(S.a1[t][q][lane]);
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) h1[t][rt] = mfma32(a[e], x[rt][2 * (q - Q0) + e], h1[t][rt]);
+        }
 }
 
 // A wave per 64 rows, four to a block.  STORE: also the activations.  Bound by
@@ -181,7 +188,11 @@ __global__ __launch_bounds__(256) void mlp_forward_kernel(const float* __restric
     }
     __syncthreads();
     if (row0 >= n) return;
-    const float v = forward64<STORE>(S, params, xn, row0, n, h1t, h2t);
+    f32x16 h1[2][2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) h1[t][0] = h1[t][1] = load_bias(S.b1[t][half]);
+    first_layer<0>(S, xn, h1);
+    const float v = upper_layers<STORE>(S, params, h1, row0, n, h1t, h2t);
     if (row0 + lane < n) y[row0 + lane] = v;
 }
 
@@ -444,53 +455,140 @@ __global__ __launch_bounds__(256) void mlp_adam_kernel(float* __restrict__ p, co
 
 // ---- choose ----
 //
-// A block owns a contiguous share of the launches and takes them up to 16 at a
-// time: the valid (launch, candidate) pairs of the group are packed into one
-// list (in any order: a pair's prediction does not depend on its place), the
-// waves evaluate the list 64 pairs at a time under every model, and a wave per
-// launch then picks the least mean.  Packing is what keeps the matrix cores on
-// real pairs: 96 to 144 of 144 candidates are valid by class, and a launch alone
-// would fill its last 64-row tile by a quarter to a half.  Bound by the matrix
-// cores: 10 000 launches of 144 candidates under 3 models, 335 us (106 TFLOP/s of
-// the valid pairs), against 4260 us with a thread per candidate on the vector
-// unit; the predictions are the same bits.
-constexpr int CH_GROUP = 16, CH_THREADS = 512, CH_WAVES = CH_THREADS / 64;
+// A block owns a contiguous share of the launches and takes them in groups of
+// one size, as few as fit the LDS (10 000 launches: 39 in one).  The valid
+// (launch, candidate) pairs of a group are packed into one list (in any order: a
+// pair's prediction does not depend on its place), the waves evaluate the list
+// 64 pairs at a time, the last 32 of an odd share by themselves, under every
+// model, and a wave per launch then picks the least mean.  Packing is what keeps
+// the matrix cores on real pairs: 96 to 144 of 144 candidates are valid by
+// class, and a launch alone would fill its last 64-row tile by a quarter to a
+// half.  The first layer's sum over the eight first features is the same for
+// all candidates of a launch: it is made once, as the same chain of FMAs, and
+// the matrix cores add only the last feature and the schedule (136 of their
+// steps per 64 pairs, not 152).  Bound by the matrix cores.
+constexpr int CH_THREADS = 512, CH_WAVES = CH_THREADS / 64;
 constexpr int CH_CANDS = SPMD_MLP_MAX_CANDS;
+constexpr int CH_SHARED = 8;             // features of the shared sum, whole pairs of k steps
 constexpr uint32_t CH_MAX_BLOCKS = 256;  // one per CU: two waves per SIMD
+constexpr uint32_t CH_GROUP_MAX = 64;
+static_assert(SPMD_MLP_NFEAT == CH_SHARED + 1 && DIN == SPMD_MLP_NFEAT + 3 && CH_SHARED % 4 == 0, "first layer's split");
+static_assert(CH_CANDS == 256 && CH_GROUP_MAX <= 256, "a list entry is launch * 256 + candidate");
 
-struct ChooseLds {
-    float mean[CH_GROUP][CH_CANDS];
-    float sd[CH_GROUP][CH_CANDS];
-    uint16_t list[CH_GROUP * CH_CANDS];  // launch of the group * CH_CANDS + candidate
-    uint32_t rows;
-    // followed by MlpWeights[k_models]
+// LDS: the models' weights, then shared sums [model][launch][unit tile][half][16],
+// the candidates' normalised inputs (4 floats each), means and spreads [launch][c],
+// the launches' last feature, the list and its length.
+struct ChooseLayout {
+    size_t shared, cand, mean, sd, last, list, total;
 };
-static_assert(CH_CANDS == 256 && sizeof(ChooseLds) % 4 == 0, "tree shape and LDS layout");
-constexpr size_t CH_WEIGHTS_OFF = (sizeof(ChooseLds) + 15) / 16 * 16;
+__host__ __device__ inline ChooseLayout choose_layout(uint32_t k_models, uint32_t c, uint32_t group) {
+    ChooseLayout L;
+    L.shared = (size_t)k_models * sizeof(MlpWeights);
+    L.cand = L.shared + (size_t)k_models * group * HID * 4;
+    L.mean = L.cand + 16 * (size_t)c;
+    L.sd = L.mean + 4 * (size_t)group * c;
+    L.last = L.sd + 4 * (size_t)group * c;
+    L.list = L.last + 4 * (size_t)group;
+    L.total = L.list + 2 * (size_t)group * c + 8;  // the length sits before the list
+    L.list += 4;
+    return L;
+}
+
+struct ChooseArgs {
+    const float* params;
+    uint32_t k_models, c;
+    const MlpWeights* W;
+    const float *shared, *cand, *last;
+    const uint16_t* list;
+    uint32_t group;  // launches the arrays are laid out for
+};
+
+// 32 RT pairs from place r0 of the list: the mean over the models of place
+// r0 + lane, and its spread.
+template <int RT>
+__device__ __forceinline__ void choose_rows(const ChooseArgs& A, uint32_t r0, uint32_t rows, float& mean, float& sd) {
+    const int lane = (int)lane64(), half = lane >> 5;
+    float xn[RT][2];
+    uint32_t g[RT];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+        const uint32_t i = r0 + 32 * rt + (lane & 31);
+        const uint32_t id = A.list[i < rows ? i : rows - 1];  // past the end: evaluated, not kept
+        g[rt] = id / CH_CANDS;
+        const float* s3 = A.cand + 4 * (id % CH_CANDS);
+        xn[rt][0] = half ? s3[0] : A.last[g[rt]];
+        xn[rt][1] = half ? s3[2] : s3[1];
+    }
+    // two passes (mean, then squared deviations): the spread of nearly equal
+    // predictions keeps its precision
+    float pr[SPMD_MLP_MAX_MODELS];
+    float s1 = 0.0f;
+#pragma unroll
+    for (uint32_t mk = 0; mk < SPMD_MLP_MAX_MODELS; ++mk) {
+        pr[mk] = 0.0f;
+        if (mk < A.k_models) {
+            f32x16 h1[2][RT];
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt)
+                    h1[t][rt] = load_bias(A.shared + (((size_t)mk * A.group + g[rt]) * 4 + 2 * t + half) * 16);
+            first_layer<CH_SHARED / 4>(A.W[mk], xn, h1);
+            pr[mk] = upper_layers<false>(A.W[mk], A.params + mk * NP, h1, 0, 0, nullptr, nullptr);
+        }
+        s1 += pr[mk];
+    }
+    mean = s1 / (float)A.k_models;
+    float s2 = 0.0f;
+#pragma unroll
+    for (uint32_t mk = 0; mk < SPMD_MLP_MAX_MODELS; ++mk) {
+        const float d = pr[mk] - mean;
+        s2 += mk < A.k_models ? d * d : 0.0f;
+    }
+    sd = sqrtf(s2 / (float)A.k_models);
+}
 
 __global__ __launch_bounds__(CH_THREADS) void mlp_choose_kernel(
     const float* __restrict__ params, uint32_t k_models, const float* __restrict__ norm,
     const float* __restrict__ feats, uint32_t m, const float* __restrict__ cands, uint32_t c,
-    const uint8_t* __restrict__ valid, const uint32_t* __restrict__ chunks, float log_slack,
+    const uint8_t* __restrict__ valid, const uint32_t* __restrict__ chunks, float log_slack, uint32_t group,
     uint32_t* __restrict__ best, float* __restrict__ best_pred, float* __restrict__ best_sd) {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    ChooseLds& L = *reinterpret_cast<ChooseLds*>(smem);
-    MlpWeights* W = reinterpret_cast<MlpWeights*>(smem + CH_WEIGHTS_OFF);
-    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5;
+    const ChooseLayout at = choose_layout(k_models, c, group);
+    MlpWeights* W = reinterpret_cast<MlpWeights*>(smem);
+    float* shared = reinterpret_cast<float*>(smem + at.shared);
+    float* cand = reinterpret_cast<float*>(smem + at.cand);
+    float* means = reinterpret_cast<float*>(smem + at.mean);
+    float* sds = reinterpret_cast<float*>(smem + at.sd);
+    float* last = reinterpret_cast<float*>(smem + at.last);
+    uint16_t* list = reinterpret_cast<uint16_t*>(smem + at.list);
+    uint32_t* length = reinterpret_cast<uint32_t*>(smem + at.list - 4);
+    const ChooseArgs A{params, k_models, c, W, shared, cand, last, list, group};
+    const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     for (uint32_t k = 0; k < k_models; ++k) stage_weights(W[k], params + k * NP);
-    float nmu[DIN / 2], nsd[DIN / 2];
-#pragma unroll
-    for (int s = 0; s < DIN / 2; ++s) {
-        nmu[s] = norm[2 * s + half];
-        nsd[s] = norm[DIN + 2 * s + half];
+    for (uint32_t i = tid; i < 3 * c; i += CH_THREADS) {
+        const uint32_t j = i / 3, e = i % 3;
+        cand[4 * j + e] = (cands[i] - norm[SPMD_MLP_NFEAT + e]) * norm[DIN + SPMD_MLP_NFEAT + e];
     }
     const uint32_t lo = (uint32_t)((uint64_t)m * blockIdx.x / gridDim.x);
     const uint32_t hi = (uint32_t)((uint64_t)m * (blockIdx.x + 1) / gridDim.x);
-    for (uint32_t l0 = lo; l0 < hi; l0 += CH_GROUP) {
-        const uint32_t nl = hi - l0 < CH_GROUP ? hi - l0 : CH_GROUP;
-        if (tid == 0) L.rows = 0;
+    for (uint32_t l0 = lo; l0 < hi; l0 += group) {
+        const uint32_t nl = hi - l0 < group ? hi - l0 : group;
+        if (tid == 0) *length = 0;
         __syncthreads();
+        for (uint32_t i = tid; i < nl * HID * k_models; i += CH_THREADS) {
+            const uint32_t u = i % HID, g = i / HID % nl, mk = i / (HID * nl);
+            const float* w = params + mk * NP;
+            const float* f = feats + (uint64_t)(l0 + g) * SPMD_MLP_NFEAT;
+            float s = w[OFF_B1 + u];
+#pragma unroll
+            for (int k = 0; k < CH_SHARED; ++k)
+                s = __builtin_fmaf(w[OFF_W1 + k * HID + u], (f[k] - norm[k]) * norm[DIN + k], s);
+            shared[(((size_t)mk * group + g) * 4 + 2 * (u >> 5) + (u & 1)) * 16 + ((u & 31) >> 1)] = s;
+        }
+        for (uint32_t g = tid; g < nl; g += CH_THREADS)
+            last[g] = (feats[(uint64_t)(l0 + g) * SPMD_MLP_NFEAT + CH_SHARED] - norm[CH_SHARED]) * norm[DIN + CH_SHARED];
         for (uint32_t g = wave; g < nl; g += CH_WAVES)
 #pragma unroll
             for (int q = 0; q < CH_CANDS / 64; ++q) {
@@ -498,50 +596,30 @@ __global__ __launch_bounds__(CH_THREADS) void mlp_choose_kernel(
                 const bool ok = j < c && valid[(uint64_t)(l0 + g) * c + j] != 0;
                 const uint64_t mask = __builtin_amdgcn_ballot_w64(ok);
                 uint32_t at = 0;
-                if (lane == 0) at = atomicAdd(&L.rows, (uint32_t)__builtin_popcountll(mask));
+                if (lane == 0) at = atomicAdd(length, (uint32_t)__builtin_popcountll(mask));
                 at = __builtin_amdgcn_readfirstlane(at);
                 const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
                                                                  __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-                if (ok) L.list[at + below] = (uint16_t)(g * CH_CANDS + j);
+                if (ok) list[at + below] = (uint16_t)(g * CH_CANDS + j);
             }
         __syncthreads();
-        const uint32_t rows = L.rows;
-        for (uint32_t r0 = wave * MLP_ROWS; r0 < rows; r0 += CH_WAVES * MLP_ROWS) {
-            float xn[2][DIN / 2];
-#pragma unroll
-            for (int rt = 0; rt < 2; ++rt) {
-                const uint32_t i = r0 + 32 * rt + (lane & 31);
-                const uint32_t id = L.list[i < rows ? i : rows - 1];  // past the end: evaluated, not kept
-                const float* f = feats + (uint64_t)(l0 + id / CH_CANDS) * SPMD_MLP_NFEAT;
-                const float* s3 = cands + (id % CH_CANDS) * SPMD_MLP_NSCHED;
-#pragma unroll
-                for (int s = 0; s < DIN / 2; ++s) {
-                    const int k = 2 * s + half;
-                    const float v = k < SPMD_MLP_NFEAT ? f[k] : s3[k - SPMD_MLP_NFEAT];
-                    xn[rt][s] = (v - nmu[s]) * nsd[s];
-                }
-            }
-            // two passes (mean, then squared deviations): the spread of
-            // nearly equal predictions keeps its precision
-            float pr[SPMD_MLP_MAX_MODELS];
-            float s1 = 0.0f;
-#pragma unroll
-            for (uint32_t mk = 0; mk < SPMD_MLP_MAX_MODELS; ++mk) {
-                pr[mk] = mk < k_models ? forward64<false>(W[mk], params + mk * NP, xn, 0, 0, nullptr, nullptr) : 0.0f;
-                s1 += pr[mk];
-            }
-            const float mean = s1 / (float)k_models;
-            float s2 = 0.0f;
-#pragma unroll
-            for (uint32_t mk = 0; mk < SPMD_MLP_MAX_MODELS; ++mk) {
-                const float d = pr[mk] - mean;
-                s2 += mk < k_models ? d * d : 0.0f;
-            }
-            if (r0 + lane < rows) {
-                const uint32_t id = L.list[r0 + lane];
-                (&L.mean[0][0])[id] = mean;
-                (&L.sd[0][0])[id] = sqrtf(s2 / (float)k_models);
-            }
+        // 32 pairs are a unit of work; a wave's units lie together
+        const uint32_t rows = *length, units = (rows + 31) / 32;
+        const uint32_t u0 = units * wave / CH_WAVES, u1 = units * (wave + 1) / CH_WAVES;
+        auto keep = [&](uint32_t place, float mean, float sd) {
+            const uint32_t id = list[place], slot = id / CH_CANDS * c + id % CH_CANDS;
+            means[slot] = mean;
+            sds[slot] = sd;
+        };
+        float mean, sd;
+        uint32_t u = u0;
+        for (; u + 2 <= u1; u += 2) {
+            choose_rows<2>(A, 32 * u, rows, mean, sd);
+            if (32 * u + lane < rows) keep(32 * u + lane, mean, sd);
+        }
+        if (u < u1) {
+            choose_rows<1>(A, 32 * u, rows, mean, sd);
+            if (lane < 32 && 32 * u + lane < rows) keep(32 * u + lane, mean, sd);
         }
         __syncthreads();
         for (uint32_t g = wave; g < nl; g += CH_WAVES) {
@@ -553,8 +631,8 @@ __global__ __launch_bounds__(CH_THREADS) void mlp_choose_kernel(
             for (int q = 0; q < 4; ++q) {
                 const uint32_t j = 64 * q + lane;
                 ok[q] = j < c && valid[(uint64_t)(l0 + g) * c + j] != 0;
-                v[q] = ok[q] ? L.mean[g][j] : INFINITY;
-                sd[q] = ok[q] ? L.sd[g][j] : 0.0f;
+                v[q] = ok[q] ? means[g * c + j] : INFINITY;
+                sd[q] = ok[q] ? sds[g * c + j] : 0.0f;
                 id[q] = ok[q] ? j : 0xFFFFFFFFu;
                 ch[q] = 0;
             }
@@ -694,16 +772,22 @@ int choose_impl(const float* params, uint32_t k_models, const float* norm, const
     if (c == 0 || c > SPMD_MLP_MAX_CANDS || !cands) return SPMD_ERR_ARGS;
     if (m && (!feats || !valid || !best || !best_pred || !best_sd)) return SPMD_ERR_ARGS;
     if (!m) return SPMD_OK;
-    const size_t shm = CH_WEIGHTS_OFF + (size_t)k_models * sizeof(MlpWeights);
-    if (shm > 65536) {  // up to 4 models: 121 KB of the 160 KB LDS, opted in explicitly
+    const uint32_t grid = m < CH_MAX_BLOCKS ? m : CH_MAX_BLOCKS;
+    // groups of one size, as few as fit the 160 KB LDS (4 models of 256
+    // candidates still take 22 launches at a time)
+    const uint32_t share = (m + grid - 1) / grid;
+    uint32_t fit = CH_GROUP_MAX;
+    while (choose_layout(k_models, c, fit).total > 163840) --fit;
+    const uint32_t groups = (share + fit - 1) / fit, group = (share + groups - 1) / groups;
+    const size_t shm = choose_layout(k_models, c, group).total;
+    if (shm > 65536) {  // opted in explicitly
         hipError_t ea = hipFuncSetAttribute(reinterpret_cast<const void*>(&mlp_choose_kernel),
-                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
+                                            hipFuncAttributeMaxDynamicSharedMemorySize, 163840);
         if (ea != hipSuccess) return hip_fail(ea);
     }
-    const uint32_t grid = m < CH_MAX_BLOCKS ? m : CH_MAX_BLOCKS;
     clear_stale_error();
     hipLaunchKernelGGL(mlp_choose_kernel, dim3(grid), dim3(CH_THREADS), shm, static_cast<hipStream_t>(stream),
-                       params, k_models, norm, feats, m, cands, c, valid, chunks, log_slack, best, best_pred,
+                       params, k_models, norm, feats, m, cands, c, valid, chunks, log_slack, group, best, best_pred,
                        best_sd);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? SPMD_OK : hip_fail(e);
