@@ -52,25 +52,56 @@ struct MlpWeights {
     alignas(16) float a2[2][HID / 8][64][4];   // [unit tile][k step / 4][lane][k step % 4]
     alignas(16) float b1[2][2][16];            // [unit tile][half-wave][register]
     alignas(16) float b2[2][2][16];
+    alignas(16) float w3[HID];
 };
 
+// max(v, 0), NaN to 0, for v out of arithmetic: the middle of v, 0 and infinity
+// is one instruction, where fmaxf first quietens v (and the compiler makes an
+// fmaxf of it as soon as it sees the infinity).
+__device__ __forceinline__ float relu(float v) {
+    float inf;
+    asm("s_mov_b32 %0, 0x7f800000" : "=s"(inf));
+    return __builtin_amdgcn_fmed3f(v, 0.0f, inf);
+}
+
+// By T threads; every load is issued before the first is waited for (a round
+// trip a weight, 19 of them, was a third of the forward pass).
+template <int T>
 __device__ __forceinline__ void stage_weights(MlpWeights& S, const float* __restrict__ params) {
+    static_assert(HID * HID % T == 0, "whole rounds");
+    constexpr int N1 = (DIN * HID + T - 1) / T, N2 = HID * HID / T;
     float* a1 = &S.a1[0][0][0][0];
-    for (int i = threadIdx.x; i < DIN * HID; i += blockDim.x) {
-        const int e = i & 1, lane = (i >> 1) & 63, q = (i >> 7) % (DIN / 4), t = i / (DIN / 4 * 128);
-        const int k = 2 * (2 * q + e) + (lane >> 5);
-        a1[i] = params[OFF_W1 + k * HID + 32 * t + unit_of(lane & 31)];
-    }
     float* a2 = &S.a2[0][0][0][0];
-    for (int i = threadIdx.x; i < HID * HID; i += blockDim.x) {
-        const int e = i & 3, lane = (i >> 2) & 63, q = (i >> 8) & 7, t = i >> 11;
-        const int k = 2 * (4 * q + e) + (lane >> 5);
-        a2[i] = params[OFF_W2 + k * HID + 32 * t + unit_of(lane & 31)];
+    const int tid = threadIdx.x;
+    float v1[N1], v2[N2], vb[3] = {};
+#pragma unroll
+    for (int p = 0; p < N1; ++p) {
+        const int i = tid + p * T < DIN * HID ? tid + p * T : 0;
+        const int e = i & 1, lane = (i >> 1) & 63, q = (i >> 7) % (DIN / 4), t = i / (DIN / 4 * 128);
+        v1[p] = params[OFF_W1 + (2 * (2 * q + e) + (lane >> 5)) * HID + 32 * t + unit_of(lane & 31)];
     }
-    if (threadIdx.x < HID) {
-        const int r = threadIdx.x & 15, h = (threadIdx.x >> 4) & 1, t = threadIdx.x >> 5;
-        S.b1[t][h][r] = params[OFF_B1 + 32 * t + 2 * r + h];
-        S.b2[t][h][r] = params[OFF_B2 + 32 * t + 2 * r + h];
+#pragma unroll
+    for (int p = 0; p < N2; ++p) {
+        const int i = tid + p * T;
+        const int e = i & 3, lane = (i >> 2) & 63, q = (i >> 8) & 7, t = i >> 11;
+        v2[p] = params[OFF_W2 + (2 * (4 * q + e) + (lane >> 5)) * HID + 32 * t + unit_of(lane & 31)];
+    }
+    const int r = tid & 15, h = (tid >> 4) & 1, t = (tid >> 5) & 1;
+    if (tid < HID) {
+        vb[0] = params[OFF_B1 + 32 * t + 2 * r + h];
+        vb[1] = params[OFF_B2 + 32 * t + 2 * r + h];
+        vb[2] = params[OFF_W3 + tid];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int p = 0; p < N1; ++p)
+        if (tid + p * T < DIN * HID) a1[tid + p * T] = v1[p];
+#pragma unroll
+    for (int p = 0; p < N2; ++p) a2[tid + p * T] = v2[p];
+    if (tid < HID) {
+        S.b1[t][h][r] = vb[0];
+        S.b2[t][h][r] = vb[1];
+        S.w3[tid] = vb[2];
     }
 }
 
@@ -88,48 +119,61 @@ __device__ __forceinline__ f32x16 load_bias(const float* p) {
 }
 
 // Layers after the first for 32 RT model rows of one wave, h1[t][rt] the first
-// layer's sums (unit tile, row tile).  Returns the prediction of row `lane`
-// (RT 1: of row lane % 32).  With STORE, the hidden activations go to h1t/h2t
-// (feature-major), rows row0 + 0..63 below n.
+// layer's sums (unit tile, row tile) and b3 the last layer's bias.  Returns the
+// prediction of row `lane` (RT 1: of row lane % 32).  With STORE, the hidden
+// activations go to h1t/h2t (feature-major), rows row0 + 0..63 below n.
+// Weights are read from LDS one step of four k ahead of the 8 RT matrix steps
+// that they serve (the sched_barrier keeps them there: left to itself, the
+// compiler read each right before its use and both waves of a SIMD waited).
 template <bool STORE, int RT>
-__device__ __forceinline__ float upper_layers(const MlpWeights& S, const float* __restrict__ params,
-                                              f32x16 (&h1)[2][RT], uint32_t row0, uint32_t n, float* h1t, float* h2t) {
+__device__ __forceinline__ float upper_layers(const MlpWeights& S, float b3, f32x16 (&h1)[2][RT], uint32_t row0,
+                                              uint32_t n, float* h1t, float* h2t) {
 #pragma clang fp contract(fast)
     const int lane = (int)lane64(), half = lane >> 5;
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                h1[t][rt][r] = fmaxf(h1[t][rt][r], 0.0f);
-                if (STORE) {
-                    const uint32_t i = row0 + 32u * rt + (lane & 31);
-                    if (i < n) h1t[(uint64_t)(32 * t + 2 * r + half) * n + i] = h1[t][rt][r];
-                }
-            }
-    float y = params[OFF_B3];
+    f32x16 h2[2][RT];
+    f32x4 a[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-        const f32x16 b = load_bias(S.b2[t][half]);
-        f32x16 h2[RT];
+        a[t] = *reinterpret_cast<const f32x4*>(S.a2[t][0][lane]);
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) h2[rt] = b;
+        for (int rt = 0; rt < RT; ++rt) h2[t][rt] = load_bias(S.b2[t][half]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int q = 0; q < HID / 8; ++q) {
-            const f32x4 a = *reinterpret_cast<const f32x4*>(S.a2[t][q][lane]);
+    for (int q = 0; q < HID / 8; ++q) {
+        f32x4 next[2];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int s = 4 * q + e;  // units 2s and 2s + 1 of the first layer
+        for (int t = 0; t < 2; ++t) next[t] = *reinterpret_cast<const f32x4*>(S.a2[t][q < 7 ? q + 1 : q][lane]);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int rt = 0; rt < RT; ++rt) h2[rt] = mfma32(a[e], h1[s >> 4][rt][s & 15], h2[rt]);
+        for (int e = 0; e < 4; ++e) {
+            const int s = 4 * q + e;  // units 2s and 2s + 1 of the first layer
+            float v[RT];
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) {
+                v[rt] = relu(h1[s >> 4][rt][s & 15]);
+                if (STORE) {
+                    const uint32_t i = row0 + 32u * rt + (lane & 31);
+                    if (i < n) h1t[(uint64_t)(2 * s + half) * n + i] = v[rt];
+                }
             }
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) h2[t][rt] = mfma32(a[t][e], v[rt], h2[t][rt]);
         }
+        a[0] = next[0];
+        a[1] = next[1];
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    float y = b3;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
         // Exchanging halves puts one unit of all rows into a register
         // (row = lane), and the last layer's sum runs over the units in order.
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            const float v0 = fmaxf(h2[0][r], 0.0f), v1 = fmaxf(h2[RT - 1][r], 0.0f);
+            const float v0 = relu(h2[t][0][r]), v1 = relu(h2[t][RT - 1][r]);
             const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(v0), __float_as_uint(v1), false, false);
             const float u0 = __uint_as_float(sw[0]), u1 = __uint_as_float(sw[1]);
             const int j = 32 * t + 2 * r;
@@ -140,10 +184,9 @@ __device__ __forceinline__ float upper_layers(const MlpWeights& S, const float* 
                     h2t[(uint64_t)(j + 1) * n + i] = u1;
                 }
             }
-            y += u0 * params[OFF_W3 + j];
-            y += u1 * params[OFF_W3 + j + 1];
+            y += u0 * S.w3[j];
+            y += u1 * S.w3[j + 1];
         }
-    }
     return y;
 }
 
@@ -175,7 +218,7 @@ __global__ __launch_bounds__(256) void mlp_forward_kernel(const float* __restric
                                                           const float* __restrict__ x, uint32_t n,
                                                           float* __restrict__ y, float* h1t, float* h2t) {
     __shared__ MlpWeights S;
-    stage_weights(S, params);
+    stage_weights<256>(S, params);
     const int lane = (int)lane64(), half = lane >> 5;
     const uint32_t row0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * MLP_ROWS;
     float xn[2][DIN / 2];
@@ -192,7 +235,7 @@ __global__ __launch_bounds__(256) void mlp_forward_kernel(const float* __restric
 #pragma unroll
     for (int t = 0; t < 2; ++t) h1[t][0] = h1[t][1] = load_bias(S.b1[t][half]);
     first_layer<0>(S, xn, h1);
-    const float v = upper_layers<STORE>(S, params, h1, row0, n, h1t, h2t);
+    const float v = upper_layers<STORE>(S, params[OFF_B3], h1, row0, n, h1t, h2t);
     if (row0 + lane < n) y[row0 + lane] = v;
 }
 
@@ -476,21 +519,22 @@ static_assert(SPMD_MLP_NFEAT == CH_SHARED + 1 && DIN == SPMD_MLP_NFEAT + 3 && CH
 static_assert(CH_CANDS == 256 && CH_GROUP_MAX <= 256, "a list entry is launch * 256 + candidate");
 
 // LDS: the models' weights, then shared sums [model][launch][unit tile][half][16],
-// the candidates' normalised inputs (4 floats each), means and spreads [launch][c],
-// the launches' last feature, the list and its length.
+// the candidates' normalised inputs (4 floats each), the launches' valid
+// candidates (a bit each), means and spreads [launch][c], normalised features
+// [launch][9], the list's length and the list.
 struct ChooseLayout {
-    size_t shared, cand, mean, sd, last, list, total;
+    size_t shared, cand, mask, mean, sd, feat, list, total;
 };
 __host__ __device__ inline ChooseLayout choose_layout(uint32_t k_models, uint32_t c, uint32_t group) {
     ChooseLayout L;
     L.shared = (size_t)k_models * sizeof(MlpWeights);
     L.cand = L.shared + (size_t)k_models * group * HID * 4;
-    L.mean = L.cand + 16 * (size_t)c;
+    L.mask = L.cand + 16 * (size_t)c;
+    L.mean = L.mask + 8 * (size_t)group * (CH_CANDS / 64);
     L.sd = L.mean + 4 * (size_t)group * c;
-    L.last = L.sd + 4 * (size_t)group * c;
-    L.list = L.last + 4 * (size_t)group;
-    L.total = L.list + 2 * (size_t)group * c + 8;  // the length sits before the list
-    L.list += 4;
+    L.feat = L.sd + 4 * (size_t)group * c;
+    L.list = L.feat + 4 * (size_t)group * SPMD_MLP_NFEAT + 4;  // the length sits before the list
+    L.total = L.list + 2 * (size_t)group * c;
     return L;
 }
 
@@ -498,7 +542,7 @@ struct ChooseArgs {
     const float* params;
     uint32_t k_models, c;
     const MlpWeights* W;
-    const float *shared, *cand, *last;
+    const float *shared, *cand, *feat;
     const uint16_t* list;
     uint32_t group;  // launches the arrays are laid out for
 };
@@ -516,7 +560,7 @@ __device__ __forceinline__ void choose_rows(const ChooseArgs& A, uint32_t r0, ui
         const uint32_t id = A.list[i < rows ? i : rows - 1];  // past the end: evaluated, not kept
         g[rt] = id / CH_CANDS;
         const float* s3 = A.cand + 4 * (id % CH_CANDS);
-        xn[rt][0] = half ? s3[0] : A.last[g[rt]];
+        xn[rt][0] = half ? s3[0] : A.feat[g[rt] * SPMD_MLP_NFEAT + CH_SHARED];
         xn[rt][1] = half ? s3[2] : s3[1];
     }
     // two passes (mean, then squared deviations): the spread of nearly equal
@@ -534,7 +578,7 @@ __device__ __forceinline__ void choose_rows(const ChooseArgs& A, uint32_t r0, ui
                 for (int rt = 0; rt < RT; ++rt)
                     h1[t][rt] = load_bias(A.shared + (((size_t)mk * A.group + g[rt]) * 4 + 2 * t + half) * 16);
             first_layer<CH_SHARED / 4>(A.W[mk], xn, h1);
-            pr[mk] = upper_layers<false>(A.W[mk], A.params + mk * NP, h1, 0, 0, nullptr, nullptr);
+            pr[mk] = upper_layers<false>(A.W[mk], A.params[mk * NP + OFF_B3], h1, 0, 0, nullptr, nullptr);
         }
         s1 += pr[mk];
     }
@@ -560,13 +604,14 @@ __global__ __launch_bounds__(CH_THREADS) void mlp_choose_kernel(
     float* cand = reinterpret_cast<float*>(smem + at.cand);
     float* means = reinterpret_cast<float*>(smem + at.mean);
     float* sds = reinterpret_cast<float*>(smem + at.sd);
-    float* last = reinterpret_cast<float*>(smem + at.last);
+    float* feat = reinterpret_cast<float*>(smem + at.feat);
+    uint64_t* masks = reinterpret_cast<uint64_t*>(smem + at.mask);
     uint16_t* list = reinterpret_cast<uint16_t*>(smem + at.list);
     uint32_t* length = reinterpret_cast<uint32_t*>(smem + at.list - 4);
-    const ChooseArgs A{params, k_models, c, W, shared, cand, last, list, group};
+    const ChooseArgs A{params, k_models, c, W, shared, cand, feat, list, group};
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    for (uint32_t k = 0; k < k_models; ++k) stage_weights(W[k], params + k * NP);
+    for (uint32_t k = 0; k < k_models; ++k) stage_weights<CH_THREADS>(W[k], params + k * NP);
     for (uint32_t i = tid; i < 3 * c; i += CH_THREADS) {
         const uint32_t j = i / 3, e = i % 3;
         cand[4 * j + e] = (cands[i] - norm[SPMD_MLP_NFEAT + e]) * norm[DIN + SPMD_MLP_NFEAT + e];
@@ -576,32 +621,56 @@ __global__ __launch_bounds__(CH_THREADS) void mlp_choose_kernel(
     for (uint32_t l0 = lo; l0 < hi; l0 += group) {
         const uint32_t nl = hi - l0 < group ? hi - l0 : group;
         if (tid == 0) *length = 0;
-        __syncthreads();
-        for (uint32_t i = tid; i < nl * HID * k_models; i += CH_THREADS) {
-            const uint32_t u = i % HID, g = i / HID % nl, mk = i / (HID * nl);
-            const float* w = params + mk * NP;
-            const float* f = feats + (uint64_t)(l0 + g) * SPMD_MLP_NFEAT;
-            float s = w[OFF_B1 + u];
-#pragma unroll
-            for (int k = 0; k < CH_SHARED; ++k)
-                s = __builtin_fmaf(w[OFF_W1 + k * HID + u], (f[k] - norm[k]) * norm[DIN + k], s);
-            shared[(((size_t)mk * group + g) * 4 + 2 * (u >> 5) + (u & 1)) * 16 + ((u & 31) >> 1)] = s;
+        for (uint32_t i = tid; i < nl * SPMD_MLP_NFEAT; i += CH_THREADS) {
+            const uint32_t k = i % SPMD_MLP_NFEAT;
+            feat[i] = (feats[(uint64_t)l0 * SPMD_MLP_NFEAT + i] - norm[k]) * norm[DIN + k];
         }
-        for (uint32_t g = tid; g < nl; g += CH_THREADS)
-            last[g] = (feats[(uint64_t)(l0 + g) * SPMD_MLP_NFEAT + CH_SHARED] - norm[CH_SHARED]) * norm[DIN + CH_SHARED];
-        for (uint32_t g = wave; g < nl; g += CH_WAVES)
+        __syncthreads();
+        // a wave per launch: its list entries, a unit per lane of its shared sums
+        uint8_t bits[CH_CANDS / 64];
+        auto load_valid = [&](uint32_t g) {
 #pragma unroll
             for (int q = 0; q < CH_CANDS / 64; ++q) {
                 const uint32_t j = 64 * q + lane;
-                const bool ok = j < c && valid[(uint64_t)(l0 + g) * c + j] != 0;
-                const uint64_t mask = __builtin_amdgcn_ballot_w64(ok);
-                uint32_t at = 0;
-                if (lane == 0) at = atomicAdd(length, (uint32_t)__builtin_popcountll(mask));
-                at = __builtin_amdgcn_readfirstlane(at);
-                const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-                if (ok) list[at + below] = (uint16_t)(g * CH_CANDS + j);
+                bits[q] = j < c ? valid[(uint64_t)(l0 + g) * c + j] : 0;
             }
+        };
+        if (wave < (int)nl) load_valid(wave);
+        for (uint32_t mk = 0; mk < k_models; ++mk) {
+            const float* w = params + mk * NP + OFF_W1 + lane;
+            float wk[CH_SHARED];
+#pragma unroll
+            for (int k = 0; k < CH_SHARED; ++k) wk[k] = w[k * HID];
+            const float b = params[mk * NP + OFF_B1 + lane];
+            float* out = shared + (size_t)mk * group * HID + (2 * (lane >> 5) + (lane & 1)) * 16 + ((lane & 31) >> 1);
+            for (uint32_t g = wave; g < nl; g += CH_WAVES) {
+                float s = b;
+#pragma unroll
+                for (int k = 0; k < CH_SHARED; ++k) s = __builtin_fmaf(wk[k], feat[g * SPMD_MLP_NFEAT + k], s);
+                out[g * HID] = s;
+            }
+        }
+        for (uint32_t g = wave; g < nl; g += CH_WAVES) {
+            uint64_t mask[CH_CANDS / 64];
+            uint32_t count = 0;
+#pragma unroll
+            for (int q = 0; q < CH_CANDS / 64; ++q) {
+                mask[q] = __builtin_amdgcn_ballot_w64(bits[q] != 0);
+                count += (uint32_t)__builtin_popcountll(mask[q]);
+            }
+            if (g + CH_WAVES < nl) load_valid(g + CH_WAVES);
+            uint32_t at = 0;
+            if (lane == 0) at = atomicAdd(length, count);
+            at = __builtin_amdgcn_readfirstlane(at);
+#pragma unroll
+            for (int q = 0; q < CH_CANDS / 64; ++q) {
+                const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask[q] >> 32),
+                                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)mask[q], 0u));
+                if (mask[q] >> lane & 1u) list[at + below] = (uint16_t)(g * CH_CANDS + 64 * q + lane);
+                at += (uint32_t)__builtin_popcountll(mask[q]);
+                if (lane == 0) masks[g * (CH_CANDS / 64) + q] = mask[q];
+            }
+        }
         __syncthreads();
         // 32 pairs are a unit of work; a wave's units lie together
         const uint32_t rows = *length, units = (rows + 31) / 32;
@@ -630,7 +699,7 @@ __global__ __launch_bounds__(CH_THREADS) void mlp_choose_kernel(
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const uint32_t j = 64 * q + lane;
-                ok[q] = j < c && valid[(uint64_t)(l0 + g) * c + j] != 0;
+                ok[q] = (masks[g * (CH_CANDS / 64) + q] >> lane & 1u) != 0;
                 v[q] = ok[q] ? means[g * c + j] : INFINITY;
                 sd[q] = ok[q] ? sds[g * c + j] : 0.0f;
                 id[q] = ok[q] ? j : 0xFFFFFFFFu;
