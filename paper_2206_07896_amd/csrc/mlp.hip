@@ -53,6 +53,7 @@ struct MlpWeights {
     alignas(16) float b1[2][2][16];            // [unit tile][half-wave][register]
     alignas(16) float b2[2][2][16];
     alignas(16) float w3[HID];
+    float b3;
 };
 
 // max(v, 0), NaN to 0, for v out of arithmetic: the middle of v, 0 and infinity
@@ -102,6 +103,7 @@ __device__ __forceinline__ void stage_weights(MlpWeights& S, const float* __rest
         S.b1[t][h][r] = vb[0];
         S.b2[t][h][r] = vb[1];
         S.w3[tid] = vb[2];
+        if (tid == 0) S.b3 = params[OFF_B3];
     }
 }
 
@@ -118,32 +120,45 @@ __device__ __forceinline__ f32x16 load_bias(const float* p) {
     return v;
 }
 
-// Layers after the first for 32 RT model rows of one wave, h1[t][rt] the first
-// layer's sums (unit tile, row tile) and b3 the last layer's bias.  Returns the
-// prediction of row `lane` (RT 1: of row lane % 32).  With STORE, the hidden
-// activations go to h1t/h2t (feature-major), rows row0 + 0..63 below n.
-// Weights are read from LDS one step of four k ahead of the 8 RT matrix steps
-// that they serve (the sched_barrier keeps them there: left to itself, the
-// compiler read each right before its use and both waves of a SIMD waited).
-template <bool STORE, int RT>
-__device__ __forceinline__ float upper_layers(const MlpWeights& S, float b3, f32x16 (&h1)[2][RT], uint32_t row0,
-                                              uint32_t n, float* h1t, float* h2t) {
-#pragma clang fp contract(fast)
-    const int lane = (int)lane64(), half = lane >> 5;
+// What the second layer starts from: its biases and its first weights.
+template <int RT>
+struct Upper {
     f32x16 h2[2][RT];
     f32x4 a[2];
+    __device__ __forceinline__ void load(const MlpWeights& S) {
+        const int lane = (int)lane64(), half = lane >> 5;
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-        a[t] = *reinterpret_cast<const f32x4*>(S.a2[t][0][lane]);
+        for (int t = 0; t < 2; ++t) {
+            a[t] = *reinterpret_cast<const f32x4*>(S.a2[t][0][lane]);
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) h2[t][rt] = load_bias(S.b2[t][half]);
+            for (int rt = 0; rt < RT; ++rt) h2[t][rt] = load_bias(S.b2[t][half]);
+        }
     }
-    __builtin_amdgcn_sched_barrier(0);
+};
+
+// Layers after the first for 32 RT model rows of one wave: U loaded, h1[t][rt]
+// the first layer's sums (unit tile, row tile; used up), b3 the last layer's
+// bias.  Returns the prediction of row `lane` (RT 1: of row lane % 32).  With
+// STORE, the hidden activations go to h1t/h2t (feature-major), rows row0 + 0..63
+// below n.  Weights are read from LDS one step of four k ahead of the 8 RT matrix
+// steps that they serve (the sched_barriers keep them there: left to itself, the
+// compiler read each right before its use and both waves of a SIMD waited);
+// `then` runs when h1 is free, before the last layer, which needs no matrix step.
+template <bool STORE, int RT, typename Then>
+__device__ __forceinline__ float upper_layers(const MlpWeights& S, float b3, f32x16 (&h1)[2][RT], Upper<RT>& U,
+                                              uint32_t row0, uint32_t n, float* h1t, float* h2t, Then then) {
+#pragma clang fp contract(fast)
+    const int lane = (int)lane64(), half = lane >> 5;
+    f32x4 w3[HID / 4];
 #pragma unroll
     for (int q = 0; q < HID / 8; ++q) {
         f32x4 next[2];
 #pragma unroll
         for (int t = 0; t < 2; ++t) next[t] = *reinterpret_cast<const f32x4*>(S.a2[t][q < 7 ? q + 1 : q][lane]);
+        if (q == HID / 8 - 1) {
+#pragma unroll
+            for (int j = 0; j < HID / 4; ++j) w3[j] = *reinterpret_cast<const f32x4*>(S.w3 + 4 * j);
+        }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -160,12 +175,13 @@ __device__ __forceinline__ float upper_layers(const MlpWeights& S, float b3, f32
 #pragma unroll
             for (int t = 0; t < 2; ++t)
 #pragma unroll
-                for (int rt = 0; rt < RT; ++rt) h2[t][rt] = mfma32(a[t][e], v[rt], h2[t][rt]);
+                for (int rt = 0; rt < RT; ++rt) U.h2[t][rt] = mfma32(U.a[t][e], v[rt], U.h2[t][rt]);
         }
-        a[0] = next[0];
-        a[1] = next[1];
+        U.a[0] = next[0];
+        U.a[1] = next[1];
         __builtin_amdgcn_sched_barrier(0);
     }
+    then();
     float y = b3;
 #pragma unroll
     for (int t = 0; t < 2; ++t)
@@ -173,7 +189,7 @@ __device__ __forceinline__ float upper_layers(const MlpWeights& S, float b3, f32
         // (row = lane), and the last layer's sum runs over the units in order.
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            const float v0 = relu(h2[t][0][r]), v1 = relu(h2[t][RT - 1][r]);
+            const float v0 = relu(U.h2[t][0][r]), v1 = relu(U.h2[t][RT - 1][r]);
             const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(v0), __float_as_uint(v1), false, false);
             const float u0 = __uint_as_float(sw[0]), u1 = __uint_as_float(sw[1]);
             const int j = 32 * t + 2 * r;
@@ -184,28 +200,32 @@ __device__ __forceinline__ float upper_layers(const MlpWeights& S, float b3, f32
                     h2t[(uint64_t)(j + 1) * n + i] = u1;
                 }
             }
-            y += u0 * S.w3[j];
-            y += u1 * S.w3[j + 1];
+            y += u0 * w3[j / 4][j % 4];
+            y += u1 * w3[j / 4][j % 4 + 1];
         }
     return y;
 }
 
-// The first layer's k steps 2 Q0 .. 5 on top of h1; x[rt][s] is normalised input
-// 4 Q0 + 2s + lane/32 of row 32 rt + lane%32.
+// The first layer's k steps 2 Q0 .. 5 on top of h1, a[t][q - Q0] their weights;
+// x[rt][s] is normalised input 4 Q0 + 2s + lane/32 of row 32 rt + lane%32.
 template <int Q0, int RT>
-__device__ __forceinline__ void first_layer(const MlpWeights& S, const float (&x)[RT][DIN / 2 - 2 * Q0],
+__device__ __forceinline__ void first_layer(const f32x2 (&a)[2][DIN / 4 - Q0], const float (&x)[RT][DIN / 2 - 2 * Q0],
                                             f32x16 (&h1)[2][RT]) {
-    const int lane = (int)lane64();
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int q = Q0; q < DIN / 4; ++q) {
-            const f32x2 a = *reinterpret_cast<const f32x2*>(S.a1[t][q][lane]);
+        for (int q = Q0; q < DIN / 4; ++q)
 #pragma unroll
             for (int e = 0; e < 2; ++e)
 #pragma unroll
-                for (int rt = 0; rt < RT; ++rt) h1[t][rt] = mfma32(a[e], x[rt][2 * (q - Q0) + e], h1[t][rt]);
-        }
+                for (int rt = 0; rt < RT; ++rt) h1[t][rt] = mfma32(a[t][q - Q0][e], x[rt][2 * (q - Q0) + e], h1[t][rt]);
+}
+template <int Q0>
+__device__ __forceinline__ void first_weights(const MlpWeights& S, f32x2 (&a)[2][DIN / 4 - Q0]) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int q = Q0; q < DIN / 4; ++q) a[t][q - Q0] = *reinterpret_cast<const f32x2*>(S.a1[t][q][lane64()]);
 }
 
 // A wave per 64 rows, four to a block.  STORE: also the activations.  Bound by
@@ -234,8 +254,12 @@ __global__ __launch_bounds__(256) void mlp_forward_kernel(const float* __restric
     f32x16 h1[2][2];
 #pragma unroll
     for (int t = 0; t < 2; ++t) h1[t][0] = h1[t][1] = load_bias(S.b1[t][half]);
-    first_layer<0>(S, xn, h1);
-    const float v = upper_layers<STORE>(S, params[OFF_B3], h1, row0, n, h1t, h2t);
+    f32x2 a[2][DIN / 4];
+    first_weights<0>(S, a);
+    Upper<2> U;
+    U.load(S);
+    first_layer<0>(a, xn, h1);
+    const float v = upper_layers<STORE>(S, params[OFF_B3], h1, U, row0, n, h1t, h2t, [] {});
     if (row0 + lane < n) y[row0 + lane] = v;
 }
 
@@ -563,24 +587,34 @@ __device__ __forceinline__ void choose_rows(const ChooseArgs& A, uint32_t r0, ui
         xn[rt][0] = half ? s3[0] : A.feat[g[rt] * SPMD_MLP_NFEAT + CH_SHARED];
         xn[rt][1] = half ? s3[2] : s3[1];
     }
+    // A model's first sums and weights are read while the one before it ends.
+    f32x16 h1[2][RT];
+    f32x2 a[2][1];
+    auto begin = [&](uint32_t mk) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+                h1[t][rt] = load_bias(A.shared + (((size_t)mk * A.group + g[rt]) * 4 + 2 * t + half) * 16);
+        first_weights<CH_SHARED / 4>(A.W[mk], a);
+    };
     // two passes (mean, then squared deviations): the spread of nearly equal
     // predictions keeps its precision
-    float pr[SPMD_MLP_MAX_MODELS];
+    float pr[SPMD_MLP_MAX_MODELS] = {};
     float s1 = 0.0f;
+    begin(0);
+#pragma unroll 1
+    for (uint32_t mk = 0; mk < A.k_models; ++mk) {
+        Upper<RT> U;
+        U.load(A.W[mk]);
+        __builtin_amdgcn_sched_barrier(0);
+        first_layer<CH_SHARED / 4>(a, xn, h1);
+        const float y = upper_layers<false>(A.W[mk], A.W[mk].b3, h1, U, 0, 0, nullptr, nullptr, [&] {
+            begin(mk + 1 < A.k_models ? mk + 1 : mk);
+        });
 #pragma unroll
-    for (uint32_t mk = 0; mk < SPMD_MLP_MAX_MODELS; ++mk) {
-        pr[mk] = 0.0f;
-        if (mk < A.k_models) {
-            f32x16 h1[2][RT];
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int rt = 0; rt < RT; ++rt)
-                    h1[t][rt] = load_bias(A.shared + (((size_t)mk * A.group + g[rt]) * 4 + 2 * t + half) * 16);
-            first_layer<CH_SHARED / 4>(A.W[mk], xn, h1);
-            pr[mk] = upper_layers<false>(A.W[mk], A.params[mk * NP + OFF_B3], h1, 0, 0, nullptr, nullptr);
-        }
-        s1 += pr[mk];
+        for (uint32_t i = 0; i < SPMD_MLP_MAX_MODELS; ++i) pr[i] = i == mk ? y : pr[i];
+        s1 += y;
     }
     mean = s1 / (float)A.k_models;
     float s2 = 0.0f;
