@@ -61,7 +61,7 @@ struct alignas(16) BatchDesc {
     uint32_t aux;      // REDUCE/HIST: elements per block; JACOBI: blocks per row
     uint64_t in, out;
     uint64_t ws;       // run-area scratch of this instance
-    uint32_t vec;      // in/out 16-byte aligned
+    uint32_t vec;      // REDUCE/HIST: in 16-byte aligned
     uint32_t pad;
 };
 static_assert(sizeof(BatchDesc) == 64, "descriptor is 64 bytes");
@@ -125,20 +125,18 @@ __device__ __forceinline__ void run_logical_block(const BatchDesc& d, uint32_t b
         const int32_t* x = reinterpret_cast<const int32_t*>(d.in);
         int32_t* y = reinterpret_cast<int32_t*>(d.out);
         uint64_t* st = reinterpret_cast<uint64_t*>(d.ws);
-        const bool v = d.vec != 0u;
         switch (d.items) {
-        case 1: scan_tile<B, 1>(x, y, d.n, b, st, 0u, err, v, L.s1, hook); break;
-        case 2: scan_tile<B, 2>(x, y, d.n, b, st, 0u, err, v, L.s2, hook); break;
-        case 4: scan_tile<B, 4>(x, y, d.n, b, st, 0u, err, v, L.s4, hook); break;
-        case 8: scan_tile<B, 8>(x, y, d.n, b, st, 0u, err, v, L.s8, hook); break;
-        default: scan_tile<B, 16>(x, y, d.n, b, st, 0u, err, v, L.s16, hook); break;
+        case 1: scan_tile<B, 1>(x, y, d.n, b, st, 0u, err, L.s1, hook); break;
+        case 2: scan_tile<B, 2>(x, y, d.n, b, st, 0u, err, L.s2, hook); break;
+        case 4: scan_tile<B, 4>(x, y, d.n, b, st, 0u, err, L.s4, hook); break;
+        case 8: scan_tile<B, 8>(x, y, d.n, b, st, 0u, err, L.s8, hook); break;
+        default: scan_tile<B, 16>(x, y, d.n, b, st, 0u, err, L.s16, hook); break;
         }
     } else if constexpr (CLS == BATCH_SCAN_WIDE) {
         const int32_t* x = reinterpret_cast<const int32_t*>(d.in);
         int32_t* y = reinterpret_cast<int32_t*>(d.out);
         uint64_t* st = reinterpret_cast<uint64_t*>(d.ws);
-        const bool v = d.vec != 0u;
-        scan_tile<B, 32>(x, y, d.n, b, st, 0u, err, v, L.s32, hook);
+        scan_tile<B, 32>(x, y, d.n, b, st, 0u, err, L.s32, hook);
     } else if constexpr (CLS == SPMD_HIST256_U32) {
         const uint64_t lo = (uint64_t)b * d.aux;
         const uint64_t hi = lo + d.aux < (uint64_t)d.n ? lo + d.aux : (uint64_t)d.n;
@@ -1098,11 +1096,10 @@ int spmd_batch_create_dep(const spmd_batch_item* items, const spmd_schedule* sch
         d.out = (uint64_t)(uintptr_t)it.out;
         d.ws = (uint64_t)(uintptr_t)(b->ws + run);
         const bool va = ((uintptr_t)it.in % 16) == 0;
-        const bool vb = ((uintptr_t)it.out % 16) == 0;
         switch (it.kernel_id) {
         case SPMD_REDUCE_I32:
         case SPMD_HIST256_U32: d.aux = s.block * s.items; d.vec = va; break;
-        case SPMD_SCAN_I32: d.vec = va && vb; break;
+        case SPMD_SCAN_I32: break;
         case SPMD_JACOBI5_F32: d.aux = (uint32_t)cdiv(it.n, 64); break;
         }
         if (it.kernel_id == SPMD_HIST256_U32 && !is_direct(s))  // own grids clear their bins themselves

@@ -4,15 +4,14 @@
 //
 // A tile is B threads x I items, B*I consecutive elements; 32-lane warp w
 // owns the consecutive segment [w*32*I, (w+1)*32*I) of it.
-//   1. local offsets, by warp vote.  A full, 16-byte aligned tile with
-//      I >= 4 is read in rows of 32 lanes x 4 elements (16 bytes per lane)
-//      and held in registers.  A lane keeps c = 0..4 of its four; the three
-//      bit planes of c are balloted over the warp, and popc of each plane
-//      below the lane, scaled by 2^plane, is the number kept by the lanes
-//      before it.  Rows are chained by their totals.  Other tiles take one
-//      element per lane per step (one ballot, popc below the lane), in two
-//      passes over the tile (count, then place), so registers do not grow
-//      with I.
+//   1. local offsets, by warp vote.  With I >= 4 a tile is read in rows of 32
+//      lanes x 4 elements (16 bytes per lane, at any alignment) and held in
+//      registers.  A lane keeps c = 0..4 of its four; the three bit planes
+//      of c are balloted over the warp, and popc of each plane below the lane,
+//      scaled by 2^plane, is the number kept by the lanes before it.  Rows are
+//      chained by their totals.  Smaller I take one element per lane per step
+//      (one ballot, popc below the lane), in two passes over the tile (count,
+//      then place).
 //   2. warp totals through LDS; barrier; each warp's offset in the tile and
 //      the tile's count;
 //   3. the tile's offset in y by decoupled look-back over the tiles' counts
@@ -21,6 +20,9 @@
 //      at warp offset + its own (the tile's output, contiguous); after it,
 //      the block copies the stage to y at the tile's offset with coalesced
 //      stores.
+// The tile in which x ends is another matter (compact_end): guards on the rows
+// of every tile cost the kernel 23 registers and its full tiles 3%, one element
+// per lane and step through a last tile of 1024 x 32 10 us.
 // The last tile writes count.  The pieces below are sequenced by the
 // kernel (k_compact.hip), which overlaps one tile's look-back and copy-out
 // with the next tile's loads and count.
@@ -48,23 +50,28 @@ struct CompactFront {
     static constexpr int S = I >= 4 ? I / 4 : 1;
     u32x4 rv[S];
     uint32_t rpos[S];  // kept elements of this warp's segment before this lane's four
-    bool rows;         // full, 16-byte aligned tile with I >= 4: the rows form
 };
 
-// Issue the tile's loads (rows form); other tiles load in the two passes.
+// Issue a full tile's loads (rows form, 16 bytes per lane at any alignment;
+// smaller items load in the two passes).
 template <int B, int I>
-__device__ __forceinline__ void compact_issue(const int32_t* __restrict__ x, uint32_t n, uint32_t tile, bool vec,
-                                              CompactFront<B, I>& F) {
-    F.rows = false;
+__device__ __forceinline__ void compact_issue(const int32_t* __restrict__ x, uint32_t tile, CompactFront<B, I>& F) {
     if constexpr (I >= 4) {
-        const uint64_t tb = (uint64_t)tile * B * I;
-        if (vec && tb + (uint64_t)B * I <= (uint64_t)n) {
-            F.rows = true;
-            const u32x4* xv = reinterpret_cast<const u32x4*>(x + tb + (uint64_t)(threadIdx.x >> 5) * 32u * I);
+        const u32x4_a4* xv = reinterpret_cast<const u32x4_a4*>(x + (uint64_t)tile * B * I +
+                                                               (uint64_t)(threadIdx.x >> 5) * 32u * I);
 #pragma unroll
-            for (int q = 0; q < F.S; ++q) F.rv[q] = __builtin_nontemporal_load(xv + q * 32 + lane32());
-        }
+        for (int q = 0; q < F.S; ++q) F.rv[q] = __builtin_nontemporal_load(xv + q * 32 + lane32());
     }
+}
+
+// The lane's kept count before each of its four elements of a row, and the
+// row's total.
+__device__ __forceinline__ uint32_t compact_row(const u32x4& v, int32_t t, uint32_t& total) {
+    const uint32_t c = ((int32_t)v.x > t) + ((int32_t)v.y > t) + ((int32_t)v.z > t) + ((int32_t)v.w > t);
+    const uint32_t m0 = w32_ballot(c & 1u), m1 = w32_ballot(c & 2u), m2 = w32_ballot(c & 4u);
+    total = (uint32_t)__builtin_popcount(m0) + 2u * (uint32_t)__builtin_popcount(m1) +
+            4u * (uint32_t)__builtin_popcount(m2);
+    return below(m0) + 2u * below(m1) + 4u * below(m2);
 }
 
 // Step 1: local offsets by warp vote; lane 0 of each warp writes the
@@ -73,15 +80,12 @@ template <int B, int I>
 __device__ __forceinline__ void compact_count(const int32_t* __restrict__ x, uint32_t n, int32_t t, uint32_t tile,
                                               CompactFront<B, I>& F, CompactLds<B, I>& L) {
     uint32_t run = 0;  // warp-uniform
-    if (F.rows) {
+    if constexpr (I >= 4) {
 #pragma unroll
         for (int q = 0; q < F.S; ++q) {
-            const uint32_t c = ((int32_t)F.rv[q].x > t) + ((int32_t)F.rv[q].y > t) + ((int32_t)F.rv[q].z > t) +
-                               ((int32_t)F.rv[q].w > t);
-            const uint32_t m0 = w32_ballot(c & 1u), m1 = w32_ballot(c & 2u), m2 = w32_ballot(c & 4u);
-            F.rpos[q] = run + below(m0) + 2u * below(m1) + 4u * below(m2);
-            run += (uint32_t)__builtin_popcount(m0) + 2u * (uint32_t)__builtin_popcount(m1) +
-                   4u * (uint32_t)__builtin_popcount(m2);
+            uint32_t total;
+            F.rpos[q] = run + compact_row(F.rv[q], t, total);
+            run += total;
         }
     } else {
         const uint64_t seg = (uint64_t)tile * B * I + (uint64_t)(threadIdx.x >> 5) * 32u * I;
@@ -101,7 +105,7 @@ __device__ __forceinline__ void compact_sums(const CompactLds<B, I>& L, uint32_t
     const uint32_t w = threadIdx.x >> 5;
     agg = 0;
     wpre = 0;
-#pragma unroll
+#pragma unroll 8  // all 32 at once took the registers to 126, with spills, and 3% of the time
     for (int k = 0; k < NW; ++k) {
         const uint32_t s = L.warp[k];
         agg += s;
@@ -114,7 +118,7 @@ __device__ __forceinline__ void compact_sums(const CompactLds<B, I>& L, uint32_t
 template <int B, int I>
 __device__ __forceinline__ void compact_stage(const int32_t* __restrict__ x, uint32_t n, int32_t t, uint32_t tile,
                                               uint32_t wpre, const CompactFront<B, I>& F, CompactLds<B, I>& L) {
-    if (F.rows) {
+    if constexpr (I >= 4) {
 #pragma unroll
         for (int q = 0; q < F.S; ++q) {
             uint32_t p = wpre + F.rpos[q];
@@ -135,6 +139,63 @@ __device__ __forceinline__ void compact_stage(const int32_t* __restrict__ x, uin
         if (keep) L.stage[p + below(m)] = (uint32_t)v;
         p += (uint32_t)__builtin_popcount(m);
     }
+}
+
+// The tile in which x ends: no other tile waits for it, so it looks back first
+// and then takes pieces of 8 (or 4) elements per thread one after another, rows
+// of 32 lanes x 4 straight from registers to y.  Past n a row holds the least
+// value, which no t lets through.
+template <int B, int I>
+__device__ __forceinline__ void compact_end(const int32_t* __restrict__ x, int32_t* __restrict__ y, uint32_t* count,
+                                            uint32_t n, int32_t t, uint32_t tile, uint64_t* status, uint32_t tag,
+                                            uint32_t* err, CompactLds<B, I>& L) {
+    constexpr int S = I >= 8 ? 2 : 1;
+    const uint32_t tid = threadIdx.x;
+    if (tid < 64) {
+        const uint32_t excl = scan_lookback(status, tile, 0u, tag, err, true);
+        if (tid == 0) L.excl = excl;
+    }
+    __syncthreads();
+    uint32_t run = L.excl;
+#pragma unroll 1
+    for (uint64_t base = (uint64_t)tile * B * I; base < (uint64_t)n; base += 4ull * S * B) {
+        const uint64_t e0 = base + (uint64_t)(tid >> 5) * 128u * S + 4u * lane32();
+        u32x4 v[S];
+        uint32_t pos[S], mine = 0;
+#pragma unroll
+        for (int q = 0; q < S; ++q) {
+            const uint64_t e = e0 + 128u * q;
+            v[q] = u32x4{0x80000000u, 0x80000000u, 0x80000000u, 0x80000000u};
+            if (e + 4 <= (uint64_t)n) {
+                v[q] = *reinterpret_cast<const u32x4_a4*>(x + e);
+            } else {
+                if (e < (uint64_t)n) v[q].x = (uint32_t)x[e];
+                if (e + 1 < (uint64_t)n) v[q].y = (uint32_t)x[e + 1];
+                if (e + 2 < (uint64_t)n) v[q].z = (uint32_t)x[e + 2];
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < S; ++q) {
+            uint32_t total;
+            pos[q] = mine + compact_row(v[q], t, total);
+            mine += total;
+        }
+        if (lane32() == 0) L.warp[tid >> 5] = mine;
+        __syncthreads();
+        uint32_t agg, wpre;
+        compact_sums<B, I>(L, agg, wpre);
+        __syncthreads();  // the next piece writes L.warp
+#pragma unroll
+        for (int q = 0; q < S; ++q) {
+            int32_t* yo = y + run + wpre + pos[q];
+            const uint32_t w[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if ((int32_t)w[j] > t) *yo++ = (int32_t)w[j];
+        }
+        run += agg;
+    }
+    if (tid == 0) *count = run;
 }
 
 }  // namespace spmd

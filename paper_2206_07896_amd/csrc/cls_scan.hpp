@@ -2,15 +2,15 @@
 // modulo 2^32).
 //
 // A tile is B threads x I items: B*I consecutive elements.
-//   1. local scan.  A full, 16-byte aligned tile with I >= 4 is read in
-//      rows: wave w owns elements [w*64*I, (w+1)*64*I) of the tile and
+//   1. local scan.  A full tile with I >= 4 is read in rows: wave w owns elements [w*64*I, (w+1)*64*I) of the tile and
 //      reads them as I/4 coalesced 1 KiB rows, lane l holding elements
 //      4l .. 4l+3 of each row.  Each row is scanned where it lies: the
 //      lane's four values, then the 32-lane inclusive scan of the lane
 //      totals on each half-wavefront (warp32 DPP scan), the two halves
-//      joined by lane 31's total, rows chained by their totals.  Any other
-//      tile gives each thread I consecutive items: thread-serial scan, then
-//      the 32-lane scan of the thread totals.
+//      joined by lane 31's total, rows chained by their totals.  A tile of
+//      I < 4 gives each thread I consecutive items: thread-serial scan, then
+//      the 32-lane scan of the thread totals.  The tile in which x ends goes
+//      in pieces, after its look-back (scan_tile_end).
 //   2. the last lane of each wave (rows) or warp (items) writes its total
 //      to LDS; barrier; each thread adds the totals before its own;
 //   3. grid carry by decoupled look-back (Merrill and Garland, "Single-pass
@@ -152,12 +152,16 @@ struct NoHook {
     __device__ void operator()() const {}
 };
 
-// Rows form of a full, 16-byte aligned tile with I >= 4: wave w owns
-// elements [w*64*I, (w+1)*64*I) of the tile as I/4 rows of 64 lanes x 4
-// consecutive elements.  `wx` / `wy` point at the wave's first element.
+typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));  // 16 bytes at any element's address
+
+// Rows form of a full tile with I >= 4: wave w owns elements [w*64*I,
+// (w+1)*64*I) of the tile as I/4 rows of 64 lanes x 4 consecutive elements.
+// `wx` / `wy` point at the wave's first element, at any alignment (the same
+// 16-byte instructions serve; 2^26 elements one element off 16 bytes took 466 to
+// 1299 us one element at a time).
 template <int I>
 __device__ __forceinline__ void scan_rows_load(const int32_t* __restrict__ wx, uint32_t lane, u32x4 (&r)[I / 4]) {
-    const u32x4* xv = reinterpret_cast<const u32x4*>(wx);
+    const u32x4_a4* xv = reinterpret_cast<const u32x4_a4*>(wx);
 #pragma unroll
     for (int q = 0; q < I / 4; ++q) r[q] = __builtin_nontemporal_load(xv + q * 64 + lane);
 }
@@ -189,10 +193,10 @@ __device__ __forceinline__ uint32_t scan_rows_local(uint32_t lane, u32x4 (&r)[I 
 template <int I>
 __device__ __forceinline__ void scan_rows_store(int32_t* __restrict__ wy, uint32_t lane, const u32x4 (&r)[I / 4],
                                                 uint32_t pre) {
-    u32x4* yv = reinterpret_cast<u32x4*>(wy);
+    u32x4_a4* yv = reinterpret_cast<u32x4_a4*>(wy);
 #pragma unroll
     for (int q = 0; q < I / 4; ++q) {
-        u32x4 a = r[q];
+        u32x4_a4 a = r[q];
         a.x += pre;
         a.y += pre;
         a.z += pre;
@@ -215,8 +219,8 @@ __device__ __forceinline__ void scan_slot_sums(const uint32_t* slot, uint32_t mi
     }
 }
 
-// Items form (partial or unaligned tiles, and I < 4): each thread scans I
-// consecutive items, then the 32-lane scan of the thread totals.
+// Items form (I < 4): each thread scans I consecutive items, then the 32-lane
+// scan of the thread totals.
 template <int B, int I, typename Hook = NoHook>
 __device__ __forceinline__ void scan_tile_items(const int32_t* __restrict__ x, int32_t* __restrict__ y, uint32_t n,
                                                 uint32_t tile, uint64_t* status, uint32_t tag, uint32_t* err,
@@ -224,37 +228,6 @@ __device__ __forceinline__ void scan_tile_items(const int32_t* __restrict__ x, i
     constexpr int NW = B / 32;
     const uint32_t t = threadIdx.x;
     const uint64_t base = (uint64_t)tile * ((uint64_t)B * I) + (uint64_t)t * I;
-    if constexpr (I > 64) {
-        // Two rolled passes (the thread's total, then after the look-back
-        // the running prefix, re-reading x), so this path neither grows the
-        // registers nor unrolls into the code of the rows loop it shares a
-        // kernel with: fully unrolled at 128 items it made that kernel
-        // three times larger and its full tiles 3% slower.
-        uint32_t tot = 0;
-#pragma unroll 4
-        for (int k = 0; k < I; ++k) tot += (base + k < n) ? (uint32_t)x[base + k] : 0u;
-        const uint32_t wincl = w32_inclusive_add(tot);
-        if ((t & 31u) == 31u) L.warp[t >> 5] = wincl;
-        __syncthreads();
-        uint32_t agg, wpre;
-        scan_slot_sums<NW>(L.warp, t >> 5, agg, wpre);
-        if (t < 64) {
-            const uint32_t excl = scan_lookback(status, tile, agg, tag, err);
-            if (t == 0) {
-                L.excl = excl;
-                after_lookback();
-            }
-        }
-        __syncthreads();
-        uint32_t run = L.excl + wpre + (wincl - tot);
-#pragma unroll 4
-        for (int k = 0; k < I; ++k)
-            if (base + k < n) {
-                run += (uint32_t)x[base + k];
-                y[base + k] = (int32_t)run;
-            }
-        return;
-    }
     uint32_t v[I];
 #pragma unroll
     for (int k = 0; k < I; ++k) v[k] = (base + k < n) ? (uint32_t)x[base + k] : 0u;
@@ -280,6 +253,70 @@ __device__ __forceinline__ void scan_tile_items(const int32_t* __restrict__ x, i
         if (base + k < n) y[base + k] = (int32_t)(pre + v[k]);
 }
 
+// The tile in which x ends, I >= 4: pieces of up to 16 items per thread in rows
+// form, one after another, elements past n as zeros.  Nothing that is stored
+// depends on this tile (tiles past it are empty), so it looks back first and
+// publishes no aggregate.  One element at a time through the whole tile, each
+// thread its own run of I, a last tile of 512 x 128 held 2^18 elements up for 60 us
+// and 5 * 10^7 for 161 instead of 82.
+template <int B, int I, typename Hook>
+__device__ __forceinline__ void scan_tile_end(const int32_t* __restrict__ x, int32_t* __restrict__ y, uint32_t n,
+                                              uint32_t tile, uint64_t* status, uint32_t tag, uint32_t* err,
+                                              ScanLds<B, I>& L, Hook after_lookback) {
+    constexpr int P = I < 16 ? I : 16;
+    const uint32_t t = threadIdx.x, lane = lane64(), wave = t >> 6;
+    const uint64_t tbase = (uint64_t)tile * ((uint64_t)B * I);
+    const bool empty = tbase >= (uint64_t)n;
+    __syncthreads();  // every thread is done with the tile before, and with what the hook writes
+    if (t < 64) {
+        const uint32_t excl = empty ? 0u : scan_lookback(status, tile, 0u, tag, err, true);
+        if (t == 0) {
+            L.excl = excl;
+            after_lookback();
+        }
+    }
+    __syncthreads();
+    if (empty) return;
+    uint32_t run = L.excl;
+#pragma unroll 1
+    for (uint64_t base = tbase; base < (uint64_t)n && base < tbase + (uint64_t)B * I; base += (uint64_t)B * P) {
+        const uint64_t e0 = base + (uint64_t)wave * 64u * P + 4u * lane;
+        u32x4 r[P / 4];
+#pragma unroll
+        for (int q = 0; q < P / 4; ++q) {
+            const uint64_t e = e0 + 256u * q;
+            r[q] = u32x4{0u, 0u, 0u, 0u};
+            if (e + 4 <= (uint64_t)n) {
+                r[q] = *reinterpret_cast<const u32x4_a4*>(x + e);
+            } else {
+                if (e < (uint64_t)n) r[q].x = (uint32_t)x[e];
+                if (e + 1 < (uint64_t)n) r[q].y = (uint32_t)x[e + 1];
+                if (e + 2 < (uint64_t)n) r[q].z = (uint32_t)x[e + 2];
+            }
+        }
+        const uint32_t carry = scan_rows_local<P>(lane, r);
+        if (lane == 0) L.warp[wave] = carry;
+        __syncthreads();
+        uint32_t agg, wpre;
+        scan_slot_sums<B / 64>(L.warp, wave, agg, wpre);
+        __syncthreads();  // the next piece writes L.warp
+        const uint32_t pre = run + wpre;
+        run += agg;
+#pragma unroll
+        for (int q = 0; q < P / 4; ++q) {
+            const uint64_t e = e0 + 256u * q;
+            u32x4_a4 a = r[q] + pre;
+            if (e + 4 <= (uint64_t)n) {
+                *reinterpret_cast<u32x4_a4*>(y + e) = a;
+            } else {
+                if (e < (uint64_t)n) y[e] = (int32_t)a.x;
+                if (e + 1 < (uint64_t)n) y[e + 1] = (int32_t)a.y;
+                if (e + 2 < (uint64_t)n) y[e + 2] = (int32_t)a.z;
+            }
+        }
+    }
+}
+
 // Scan tile `tile` of x into y.  Thread 0 calls `after_lookback` once the
 // tile's inclusive prefix is published, i.e. once no other tile can wait on
 // this one any more.  Every thread's last access to L comes after the
@@ -289,13 +326,13 @@ __device__ __forceinline__ void scan_tile_items(const int32_t* __restrict__ x, i
 // that puts anything else in the area places one first.
 template <int B, int I, typename Hook = NoHook>
 __device__ __forceinline__ void scan_tile(const int32_t* __restrict__ x, int32_t* __restrict__ y, uint32_t n,
-                                          uint32_t tile, uint64_t* status, uint32_t tag, uint32_t* err, bool vec,
+                                          uint32_t tile, uint64_t* status, uint32_t tag, uint32_t* err,
                                           ScanLds<B, I>& L, Hook after_lookback = Hook()) {
     constexpr uint64_t T = (uint64_t)B * I;
     const uint32_t t = threadIdx.x;
     const uint64_t tbase = (uint64_t)tile * T;
     if constexpr (I >= 4) {
-        if (vec && tbase + T <= (uint64_t)n) {
+        if (tbase + T <= (uint64_t)n) {
             const uint32_t lane = lane64(), wave = t >> 6;
             const uint64_t wbase = tbase + (uint64_t)wave * 64u * I;
             u32x4 r[I / 4];
@@ -316,8 +353,10 @@ __device__ __forceinline__ void scan_tile(const int32_t* __restrict__ x, int32_t
             scan_rows_store<I>(y + wbase, lane, r, L.excl + wpre);
             return;
         }
+        scan_tile_end<B, I>(x, y, n, tile, status, tag, err, L, after_lookback);
+    } else {
+        scan_tile_items<B, I>(x, y, n, tile, status, tag, err, L, after_lookback);
     }
-    scan_tile_items<B, I>(x, y, n, tile, status, tag, err, L, after_lookback);
 }
 
 }  // namespace spmd

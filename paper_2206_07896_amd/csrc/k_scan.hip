@@ -36,8 +36,7 @@ __device__ __forceinline__ uint32_t scan_draw(uint64_t* ticket, uint32_t ntiles,
 
 template <int B, int I>
 __global__ __launch_bounds__(B) void scan_i32_kernel(const int32_t* __restrict__ x, int32_t* __restrict__ y,
-                                                      uint32_t n, uint32_t ntiles, uint32_t* ws, uint32_t* err,
-                                                      bool vec) {
+                                                      uint32_t n, uint32_t ntiles, uint32_t* ws, uint32_t* err) {
     __shared__ ScanLds<B, I> L;
     __shared__ uint32_t s_tile, s_next, s_tag;
     uint64_t* ticket = reinterpret_cast<uint64_t*>(ws);
@@ -51,7 +50,7 @@ __global__ __launch_bounds__(B) void scan_i32_kernel(const int32_t* __restrict__
             uint32_t unused;
             s_next = scan_draw(ticket, ntiles, &unused);
         };
-        scan_tile<B, I>(x, y, n, tile, status, tag, err, vec, L, draw_next);
+        scan_tile<B, I>(x, y, n, tile, status, tag, err, L, draw_next);
         // No barrier here: s_next is written before the tile's second
         // barrier, and thread 0 writes it, L.excl and L.warp again only after
         // the next tile's first barrier, which every thread reaches after
@@ -65,32 +64,45 @@ size_t ws_scan_i32(spmd_dim3 grid, spmd_dim3, uint64_t) { return SCAN_WS_HEADER 
 // Persistent grid for G tiles: at most the blocks that are resident at once.
 template <int B, int I>
 static void launch_bi(uint32_t G, size_t dyn, hipStream_t s, const int32_t* x, int32_t* y, uint32_t n,
-                      uint32_t* ws, uint32_t* err, bool vec, int num_cus) {
+                      uint32_t* ws, uint32_t* err, int num_cus) {
     int per_cu = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, scan_i32_kernel<B, I>, B, dyn) != hipSuccess ||
         per_cu < 1)
         per_cu = 1;
     const uint32_t P = (uint32_t)std::min<uint64_t>(G, (uint64_t)per_cu * (uint64_t)num_cus);
-    dispatch((scan_i32_kernel<B, I>), dim3(P), dim3(B), dyn, s, x, y, n, G, ws, err, vec);
+    dispatch((scan_i32_kernel<B, I>), dim3(P), dim3(B), dyn, s, x, y, n, G, ws, err);
 }
 
 template <int B>
 static void launch_b(uint32_t I, uint32_t G, size_t dyn, hipStream_t s, const int32_t* x, int32_t* y, uint32_t n,
-                     uint32_t* ws, uint32_t* err, bool vec, int num_cus) {
+                     uint32_t* ws, uint32_t* err, int num_cus) {
     switch (I) {
-    case 1: launch_bi<B, 1>(G, dyn, s, x, y, n, ws, err, vec, num_cus); break;
-    case 2: launch_bi<B, 2>(G, dyn, s, x, y, n, ws, err, vec, num_cus); break;
-    case 4: launch_bi<B, 4>(G, dyn, s, x, y, n, ws, err, vec, num_cus); break;
-    case 8: launch_bi<B, 8>(G, dyn, s, x, y, n, ws, err, vec, num_cus); break;
-    case 16: launch_bi<B, 16>(G, dyn, s, x, y, n, ws, err, vec, num_cus); break;
-    case 32: launch_bi<B, 32>(G, dyn, s, x, y, n, ws, err, vec, num_cus); break;
+    case 1: launch_bi<B, 1>(G, dyn, s, x, y, n, ws, err, num_cus); break;
+    case 2: launch_bi<B, 2>(G, dyn, s, x, y, n, ws, err, num_cus); break;
+    case 4: launch_bi<B, 4>(G, dyn, s, x, y, n, ws, err, num_cus); break;
+    case 8: launch_bi<B, 8>(G, dyn, s, x, y, n, ws, err, num_cus); break;
+    case 16: launch_bi<B, 16>(G, dyn, s, x, y, n, ws, err, num_cus); break;
+    case 32: launch_bi<B, 32>(G, dyn, s, x, y, n, ws, err, num_cus); break;
     case 64:
-        if constexpr (B <= 512) launch_bi<B, 64>(G, dyn, s, x, y, n, ws, err, vec, num_cus);
+        if constexpr (B <= 512) launch_bi<B, 64>(G, dyn, s, x, y, n, ws, err, num_cus);
         break;
     case 128:
-        if constexpr (B <= 512) launch_bi<B, 128>(G, dyn, s, x, y, n, ws, err, vec, num_cus);
+        if constexpr (B <= 512) launch_bi<B, 128>(G, dyn, s, x, y, n, ws, err, num_cus);
         break;
     }
+}
+
+// Tiles of 512 x this many elements are run in place of a launch's smaller ones
+// (0: none are).  Every tile costs about 15 ns of the one ticket, whatever its
+// size: 2^26 elements in 256 x 16 tiles take 234 us, in 512 x 16 143, 512 x 64 112
+// and 512 x 128 97; the launch's blocks are then fetched several at a time.
+// Larger tiles leave CUs idle on fewer elements.  The fastest at 2^18..2^19, to
+// 2^21, to 2^23 and on: 512 x 16 (2^19 6.4 us; 256 x 8 8.8), 512 x 32 (2^21 9.1;
+// 512 x 16 10.2, 256 x 16 15.9), 512 x 64 (2^23 16.4; 512 x 16 29.7), 512 x 128
+// (2^24 26.2; 512 x 64 30.9).  Below 2^18 no tile gains more than 5%.  A larger
+// tile needs fewer status words, so any launch's workspace holds them.
+static uint32_t scan_items(uint32_t n) {
+    return n < (1u << 18) ? 0u : n < (1u << 20) ? 16u : n < (1u << 22) ? 32u : n < (1u << 24) ? 64u : 128u;
 }
 
 int launch_scan_i32(const LaunchCtx& c) {
@@ -108,16 +120,21 @@ int launch_scan_i32(const LaunchCtx& c) {
     const uint32_t I = next_pow2(per ? (uint32_t)per : 1u);
     if (I > 128 || (I >= 64 && B > 512)) return SPMD_ERR_INVALID_DIM;  // 1024 x 64 would spill
     if (n == 0) return SPMD_OK;
-    const bool vec = aligned(x, 16) && aligned(y, 16);
-    const uint32_t G = c.grid.x;
     uint32_t* err = c.dev->err_word;
     const int cus = c.dev->num_cus;
+    const uint32_t big = scan_items(n);
+    if (c.dyn_shmem == 0 && (uint64_t)B * I < 512ull * big) {
+        launch_b<512>(big, (uint32_t)(((uint64_t)n + 512 * big - 1) / (512 * big)), 0, c.stream, x, y, n, ws, err, cus);
+        hipError_t e = hipGetLastError();
+        return e == hipSuccess ? SPMD_OK : hip_fail(e);
+    }
+    const uint32_t G = c.grid.x;
     switch (B) {
-    case 64: launch_b<64>(I, G, c.dyn_shmem, c.stream, x, y, n, ws, err, vec, cus); break;
-    case 128: launch_b<128>(I, G, c.dyn_shmem, c.stream, x, y, n, ws, err, vec, cus); break;
-    case 256: launch_b<256>(I, G, c.dyn_shmem, c.stream, x, y, n, ws, err, vec, cus); break;
-    case 512: launch_b<512>(I, G, c.dyn_shmem, c.stream, x, y, n, ws, err, vec, cus); break;
-    case 1024: launch_b<1024>(I, G, c.dyn_shmem, c.stream, x, y, n, ws, err, vec, cus); break;
+    case 64: launch_b<64>(I, G, c.dyn_shmem, c.stream, x, y, n, ws, err, cus); break;
+    case 128: launch_b<128>(I, G, c.dyn_shmem, c.stream, x, y, n, ws, err, cus); break;
+    case 256: launch_b<256>(I, G, c.dyn_shmem, c.stream, x, y, n, ws, err, cus); break;
+    case 512: launch_b<512>(I, G, c.dyn_shmem, c.stream, x, y, n, ws, err, cus); break;
+    case 1024: launch_b<1024>(I, G, c.dyn_shmem, c.stream, x, y, n, ws, err, cus); break;
     }
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? SPMD_OK : hip_fail(e);

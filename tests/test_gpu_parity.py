@@ -615,6 +615,60 @@ def test_scan_forms_share_a_workspace(spmd):
         assert np.array_equal(host(y), want), (block, items)
 
 
+@pytest.mark.parametrize("off", [0, 1, 3])
+@pytest.mark.parametrize("n,block,items", [
+    (1, 64, 4), (3, 64, 8), (255, 64, 4), (8191, 512, 64), (65537, 512, 128), (262143, 256, 8), (262145, 256, 8),
+    (1048575, 64, 16), (1048577, 512, 8), (4194303, 256, 16), (4194309, 512, 16), (16777215, 512, 32),
+    (16777217, 256, 16), (16842751, 512, 128)])
+def test_scan_and_compact_ends(spmd, n, block, items, off):
+    """Sizes around the pieces of a last tile and around the sizes from which
+    larger tiles run, at every alignment; the elements beside y stay."""
+    import torch
+
+    say("scan and compact ends", n, block, items, off)
+    x = synth.uniform_int32(0xE9D + n, n, -(2**31), 2**31 - 1)
+    xt = torch.empty(n + off, dtype=torch.int32, device="cuda")[off:]
+    xt.copy_(dev(x))
+    y = torch.full((n + off + 2,), 77, dtype=torch.int32, device="cuda")
+    spmd.ops.scan_i32(xt, block, items, y=y[1 + off:-1])
+    spmd.sync()
+    got = host(y)
+    assert np.array_equal(got[1 + off:-1], oracle.scan_i32(x, 64, 4))
+    assert (got[:1 + off] == 77).all() and got[-1] == 77
+    for t in (0, -(2**31), 2**31 - 1):
+        y.fill_(77)
+        spmd.ops.compact_i32(xt, t, block, min(items, 32), y=y[1 + off:-1], count=(c := torch.empty(1, dtype=torch.int32, device="cuda")))
+        spmd.sync()
+        want = x[x > t]
+        got = host(y)
+        assert int(host(c)[0]) == len(want), t
+        assert np.array_equal(got[1 + off:1 + off + len(want)], want), t
+        assert (got[1 + off + len(want):] == 77).all() and (got[:1 + off] == 77).all(), t
+
+
+def test_scan_and_compact_on_larger_grids(spmd):
+    """Tiles past the end: a grid of more tiles than the elements fill."""
+    import torch
+
+    say("scan and compact on larger grids")
+    for n, block, items, grid in ((1000, 64, 4, 40), (5000, 256, 4, 9), (70001, 128, 16, 77)):
+        x = synth.uniform_int32(n, n, -1000, 1000)
+        xt, y = dev(x), torch.zeros(n, dtype=torch.int32, device="cuda")
+        want = oracle.scan_i32(x, 64, 4)
+        ws = spmd.ops.workspace(spmd.SCAN_I32, grid, block, n)
+        for _ in range(3):
+            y.zero_()
+            spmd.launch(spmd.SCAN_I32, grid, block, 0, [xt, y, n, ws])
+            spmd.sync()
+            assert np.array_equal(host(y), want), (n, block, grid)
+        ws = spmd.ops.workspace(spmd.COMPACT_I32, grid, block, n)
+        c = torch.zeros(1, dtype=torch.int32, device="cuda")
+        spmd.launch(spmd.COMPACT_I32, grid, block, 0, [xt, y, c, n, 5, ws])
+        spmd.sync()
+        k = int(host(c)[0])
+        assert np.array_equal(host(y)[:k], x[x > 5]), (n, block, grid)
+
+
 def test_scan_graph_replays(spmd):
     """Three scans of different shapes on one workspace, captured in a graph:
     replays interleaved with eager scans on the same workspace and host
