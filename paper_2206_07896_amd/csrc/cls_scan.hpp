@@ -2,15 +2,16 @@
 // modulo 2^32).
 //
 // A tile is B threads x I items: B*I consecutive elements.
-//   1. local scan.  A full tile with I >= 4 is read in rows: wave w owns elements [w*64*I, (w+1)*64*I) of the tile and
-//      reads them as I/4 coalesced 1 KiB rows, lane l holding elements
-//      4l .. 4l+3 of each row.  Each row is scanned where it lies: the
-//      lane's four values, then the 32-lane inclusive scan of the lane
-//      totals on each half-wavefront (warp32 DPP scan), the two halves
-//      joined by lane 31's total, rows chained by their totals.  A tile of
-//      I < 4 gives each thread I consecutive items: thread-serial scan, then
-//      the 32-lane scan of the thread totals.  The tile in which x ends goes
-//      in pieces, after its look-back (scan_tile_end).
+//   1. local scan.  A full tile with I >= 4 is read in rows: wave w owns
+//      elements [w*64*I, (w+1)*64*I) of the tile and reads them as I/4
+//      coalesced 1 KiB rows, lane l holding elements 4l .. 4l+3 of each row.
+//      Each row is scanned where it lies: the lane's four values, then the
+//      32-lane inclusive scan of the lane totals on each half-wavefront
+//      (warp32 DPP scan), the two halves joined by lane 31's total, rows
+//      chained by their totals.  A tile of I < 4 gives each thread I
+//      consecutive items: thread-serial scan, then the 32-lane scan of the
+//      thread totals.  The tile in which x ends goes in pieces, after its
+//      look-back (scan_tile_end).
 //   2. the last lane of each wave (rows) or warp (items) writes its total
 //      to LDS; barrier; each thread adds the totals before its own;
 //   3. grid carry by decoupled look-back (Merrill and Garland, "Single-pass
@@ -257,8 +258,8 @@ __device__ __forceinline__ void scan_tile_items(const int32_t* __restrict__ x, i
 // form, one after another, elements past n as zeros.  Nothing that is stored
 // depends on this tile (tiles past it are empty), so it looks back first and
 // publishes no aggregate.  One element at a time through the whole tile, each
-// thread its own run of I, a last tile of 512 x 128 held 2^18 elements up for 60 us
-// and 5 * 10^7 for 161 instead of 82.
+// thread its own run of I, a last tile of 512 x 128 took 60 us
+// and 5 * 10^7 for 161 us instead of 79.
 template <int B, int I, typename Hook>
 __device__ __forceinline__ void scan_tile_end(const int32_t* __restrict__ x, int32_t* __restrict__ y, uint32_t n,
                                               uint32_t tile, uint64_t* status, uint32_t tag, uint32_t* err,
