@@ -147,8 +147,10 @@ __device__ __forceinline__ void run_logical_block(const BatchDesc& d, uint32_t b
 
 // JACOBI: the logical blocks (64 columns x B/64 * C rows) of one chunk, up to
 // four neighbours of a row at a time, as far as a multiple of 256 columns; wave
-// w runs rows w * C on of theirs as one strip.  Every cell is computed as in its
-// own block.  Against LDS tiles with a barrier per tile: 400 mixed launches of
+// w runs rows w * C on of theirs as one strip, or one by itself with a lane per
+// column (chunks of one block of 128 x 8 cells, 247 launches: 0.99 ms; as a
+// strip, a quarter of its lanes, 1.10; of 512 x 8 0.21 and 0.30).  Every cell is
+// computed as in its own block.  Against LDS tiles with a barrier per tile: 400 mixed launches of
 // up to 2^22 elements 340 us (375), 2000 of up to 2^20 419 us (454), 2000 of up
 // to 2^22 the same 1180; the stencil queue of those, 2.2 GB in 0.50 ms, is held
 // by HBM's rate for many rows of odd widths at once (4.6 TB/s), not by its
@@ -165,7 +167,9 @@ __device__ __forceinline__ void jacobi_chunk(const BatchDesc& d, uint32_t first,
         run = min(min(4u - (bx & 3u), w - bx), last - b);
         const int64_t y0 = ((int64_t)by * (B / 64) + wave) * C;
         const int64_t x0 = 64 * (int64_t)bx, xe = x0 + 64 * run;
-        if (y0 < (int64_t)d.ny) jacobi_strip<C>(u, v, d.n, d.ny, x0, xe < (int64_t)d.n ? xe : (int64_t)d.n, y0);
+        if (y0 >= (int64_t)d.ny) continue;
+        if (run == 1) jacobi_narrow<C>(u, v, d.n, d.ny, x0, xe < (int64_t)d.n ? xe : (int64_t)d.n, y0);
+        else jacobi_strip<C>(u, v, d.n, d.ny, x0, xe < (int64_t)d.n ? xe : (int64_t)d.n, y0);
     }
 }
 

@@ -159,4 +159,44 @@ __device__ __forceinline__ void jacobi_strip(const float* __restrict__ u, float*
     });
 }
 
+// As jacobi_strip for up to 64 columns, xe <= x0 + 64: a lane per column, since
+// 64 columns would leave 47 of a strip's lanes idle, and lane 2i (2i + 1) reads
+// the element before (after) row i for all.  Stores are plain: other waves
+// write the rest of a line.
+template <int R>
+__device__ __forceinline__ void jacobi_narrow(const float* __restrict__ u, float* __restrict__ v, int64_t NX, int64_t NY,
+                                              int64_t x0, int64_t xe, int64_t y0) {
+#pragma clang fp contract(off)
+    static_assert(2 * R <= 64, "a lane per element beside the strip");
+    const int lane = (int)lane64();
+    const int64_t gx = x0 + lane;
+    const bool in = gx < NX;
+    const int64_t origin = (y0 - 1) * NX + x0;
+    const int above = y0 > 0 ? 0 : 1;
+    const int rows = NY - y0 < R ? (int)(NY - y0) : R;
+    const int below = NY - y0 <= R ? (int)(NY - y0) : R + 1;
+    float c[R + 2], beside = 0.0f;
+    each_row<R + 2>([&](auto row) __attribute__((always_inline)) {
+        constexpr int i = row;
+        c[i] = 0.0f;
+        if (i >= above && i <= below && in) c[i] = u[origin + i * NX + lane];
+    });
+    if (lane < 2 * rows && ((lane & 1) ? x0 + 64 < NX : x0 > 0))
+        beside = u[origin + (1 + (lane >> 1)) * NX + ((lane & 1) ? 64 : -1)];
+    const bool own = gx < xe;
+    const bool keep = gx == 0 || gx >= NX - 1;
+    each_row<R>([&](auto row) __attribute__((always_inline)) {
+        constexpr int i = row;
+        if (i < rows) {
+            const float cur = c[i + 1];
+            const float west = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(beside), 2 * i));
+            const float east = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(beside), 2 * i + 1));
+            const float ns = c[i] + c[i + 2];
+            const float we = lane_left(cur, west) + lane_right(cur, east);
+            const float o = 0.25f * (ns + we);
+            if (own) v[origin + (i + 1) * NX + lane] = keep || y0 + i == 0 || y0 + i == NY - 1 ? cur : o;
+        }
+    });
+}
+
 }  // namespace spmd

@@ -437,6 +437,34 @@ def test_stencil_chunks_of_any_run(spmd, block, bpf):
     b.close()
 
 
+@pytest.mark.parametrize("nx", [1, 2, 3, 64, 65, 66, 128, 300])
+@pytest.mark.parametrize("bpf", [1, 4])
+def test_stencil_blocks_by_themselves(spmd, nx, bpf):
+    """A block that no neighbour of its row joins: the first, a middle, the
+    last one, of one column to 64, every cells count, short last rows."""
+    import torch
+
+    say("stencil blocks by themselves", nx, bpf)
+    items, sched, want, outs = [], [], [], []
+    for block in (64, 512):
+        for cells in (1, 2, 4, 8):
+            for ny in (1, 2, 8, 67):
+                u = synth.uniform_f32(0xB11 + nx + ny, ny * nx).reshape(ny, nx)
+                out = torch.full((ny * nx + 2,), -4.0, device="cuda")
+                items.append((spmd.JACOBI5_F32, nx, ny, block, torch.from_numpy(u.ravel()).cuda(), out[1:-1]))
+                sched.append((block, cells, bpf))
+                want.append(oracle.jacobi5_f32(u, 16, 16).ravel())
+                outs.append(out)
+    b = spmd.batch.Batch(items, sched)
+    b.launch()
+    spmd.sync()
+    for o, w, it, s in zip(outs, want, items, sched):
+        got = host(o)
+        assert np.array_equal(got[1:-1], w), (it[1:3], s)
+        assert got[0] == -4.0 and got[-1] == -4.0, (it[1:3], s)
+    b.close()
+
+
 @pytest.mark.parametrize("nx,ny", [(64, 65), (233, 300), (301, 299), (1024, 700), (2047, 601), (1, 40), (2, 2)])
 def test_stencil_chains_share_kernels(spmd, nx, ny):
     """Chains of every length that cuts into other groups of fused sweeps
