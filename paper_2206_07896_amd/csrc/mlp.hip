@@ -20,6 +20,8 @@
 //
 // Nothing depends on scheduling: every sum runs in a fixed order, so
 // gradients are reproducible.
+#include <algorithm>
+
 #include "common.hpp"
 #include "spmd_mlp.h"
 #include "warp32.hpp"
@@ -35,7 +37,7 @@ constexpr int OFF_W1 = 0, OFF_B1 = DIN * HID, OFF_W2 = OFF_B1 + HID, OFF_B2 = OF
               OFF_W3 = OFF_B2 + HID, OFF_B3 = OFF_W3 + HID;
 static_assert(OFF_B3 + 1 == NP, "parameter layout");
 static_assert(DIN == 12 && HID == 64, "the operand layouts below");
-constexpr int MLP_ROWS = 64;  // rows of one wave's tile (forward, choose) and of one backward chunk
+constexpr int MLP_ROWS = 64;  // rows per partial sum that a workspace holds; none has fewer
 
 __device__ __forceinline__ f32x16 mfma32(float a, float b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
@@ -193,7 +195,10 @@ __device__ __forceinline__ float upper_layers(const MlpWeights& S, float b3, f32
             const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(v0), __float_as_uint(v1), false, false);
             const float u0 = __uint_as_float(sw[0]), u1 = __uint_as_float(sw[1]);
             const int j = 32 * t + 2 * r;
-            if (STORE) {
+            if (STORE && RT == 1) {
+                const uint32_t i = row0 + (lane & 31);
+                if (i < n) h2t[(uint64_t)(j + half) * n + i] = v0;
+            } else if (STORE) {
                 const uint32_t i = row0 + lane;
                 if (i < n) {
                     h2t[(uint64_t)j * n + i] = u0;
@@ -228,79 +233,96 @@ __device__ __forceinline__ void first_weights(const MlpWeights& S, f32x2 (&a)[2]
         for (int q = Q0; q < DIN / 4; ++q) a[t][q - Q0] = *reinterpret_cast<const f32x2*>(S.a1[t][q][lane64()]);
 }
 
-// A wave per 64 rows, four to a block.  STORE: also the activations.  Bound by
+constexpr int FW_THREADS = 512, FW_ROWS = 32;
+
+// A wave per 32 rows, eight to a block.  STORE: also the activations.  Bound by
 // the matrix cores (152 of their 64-cycle steps per 64 rows, 4 us) behind the
-// start of the launch and the staging of the weights: 60 000 rows with stores
-// 20.1 us, against 49.8 us with a thread per row on the vector unit.
+// start of the launch, the staging of the weights and the stores: 60 000 rows with
+// stores 15 to 17 us, against 20.1 with 64 rows to a wave (one wave per SIMD, the
+// inputs' round trip after the weights') and 49.8 with a thread per row on the
+// vector unit.
 template <bool STORE>
-__global__ __launch_bounds__(256) void mlp_forward_kernel(const float* __restrict__ params,
-                                                          const float* __restrict__ norm,
-                                                          const float* __restrict__ x, uint32_t n,
-                                                          float* __restrict__ y, float* h1t, float* h2t) {
+__global__ __launch_bounds__(FW_THREADS) void mlp_forward_kernel(const float* __restrict__ params,
+                                                                 const float* __restrict__ norm,
+                                                                 const float* __restrict__ x, uint32_t n,
+                                                                 float* __restrict__ y, float* h1t, float* h2t) {
     __shared__ MlpWeights S;
-    stage_weights<256>(S, params);
     const int lane = (int)lane64(), half = lane >> 5;
-    const uint32_t row0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * MLP_ROWS;
-    float xn[2][DIN / 2];
+    const uint32_t row0 = (blockIdx.x * (FW_THREADS / 64) + (threadIdx.x >> 6)) * FW_ROWS;
+    const uint32_t row = row0 + (lane & 31);
+    const float* xr = x + (uint64_t)(row < n ? row : n - 1) * DIN;  // past the end: the last row, not stored
+    float xn[1][DIN / 2], mu[DIN / 2], sd[DIN / 2];
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt) {
-        const uint32_t i = row0 + 32u * rt + (lane & 31);
-        const float* xr = x + (uint64_t)(i < n ? i : n - 1) * DIN;  // past the end: the last row, not stored
-#pragma unroll
-        for (int s = 0; s < DIN / 2; ++s) xn[rt][s] = (xr[2 * s + half] - norm[2 * s + half]) * norm[DIN + 2 * s + half];
+    for (int s = 0; s < DIN / 2; ++s) {
+        xn[0][s] = xr[2 * s + half];
+        mu[s] = norm[2 * s + half];
+        sd[s] = norm[DIN + 2 * s + half];
     }
+    stage_weights<FW_THREADS>(S, params);
+#pragma unroll
+    for (int s = 0; s < DIN / 2; ++s) xn[0][s] = (xn[0][s] - mu[s]) * sd[s];
     __syncthreads();
     if (row0 >= n) return;
-    f32x16 h1[2][2];
+    f32x16 h1[2][1];
 #pragma unroll
-    for (int t = 0; t < 2; ++t) h1[t][0] = h1[t][1] = load_bias(S.b1[t][half]);
+    for (int t = 0; t < 2; ++t) h1[t][0] = load_bias(S.b1[t][half]);
     f32x2 a[2][DIN / 4];
     first_weights<0>(S, a);
-    Upper<2> U;
+    Upper<1> U;
     U.load(S);
     first_layer<0>(a, xn, h1);
     const float v = upper_layers<STORE>(S, params[OFF_B3], h1, U, row0, n, h1t, h2t, [] {});
-    if (row0 + lane < n) y[row0 + lane] = v;
+    if (half == 0 && row < n) y[row] = v;
 }
 
 // ---- backward ----
 //
-// A block of four waves takes chunks of 64 rows (block b: chunks b, b + G, ...)
+// A block of W waves takes chunks of 16 W rows (block b: chunks b, b + G, ...)
 // and keeps its partial gradients in accumulators over all of them.  Per chunk:
 //   stage   h1, h2 (unit-major), the normalised inputs and dy = 2 (y - t) / n
 //           go to LDS; the next chunk's loads are in flight meanwhile;
 //   back    d1 = (W2 d2) where h1 > 0, d2 = dy w3 where h2 > 0: a wave owns
 //           32 units x 32 rows;
-//   grads   dW2 = h1 d2^T: a wave owns one 32 x 32 tile of it, over the
-//           chunk's rows; dW1 = xn d1^T with a row of ones below xn (its
-//           product is db1): a wave takes 16 of the rows, and the four are
-//           added at the end; db2 and dw3 as a unit's sums per lane.
-// LDS rows are 68 floats, so 16-byte reads with one unit per lane hit all
-// banks evenly.  60 000 rows: 28.3 us and 5.7 us for the sum of the partials;
-// with a thread per row and each weight's sum over its rows serial in one
-// thread it took 387 us, and one thread per parameter adding the 938 partials of
-// 64 rows 220 us.  Block partials go to the workspace, part[b * (NP + 1) + p]
+//   grads   dW2 = h1 d2^T, step by step with back: a wave owns one 32 x 32 tile
+//           of it, over 64 of the chunk's rows; dW1 = xn d1^T with a row of ones
+//           below xn (its product is db1): a wave takes 16 of the rows; db2 and
+//           dw3 as a unit's sums per lane.  The waves' sums are added at the end.
+// LDS rows are 16 W + 4 floats, so 16-byte reads with one unit per lane hit all
+// banks evenly.  Bound by the matrix cores (80 of their 64-cycle steps per wave
+// and chunk, 8 us for 60 000 rows) behind the start of the launch and its first
+// loads, and the partials' way out.  A training step of 60 000 rows, all its
+// kernels: 48.1 us with blocks of four waves, two per CU and twice the partials,
+// each weight a round trip of its own and LDS operands read where they were
+// used; 40.1 us so.  (With a thread per row and each weight's sum over its rows
+// serial in one thread backward alone took 387 us, and one thread per parameter
+// adding the 938 partials of 64 rows 220 us.)
+// Block partials go to the workspace, part[b * (NP + 1) + p]
 // for parameter p and the sum of squared errors at p = NP.
-constexpr int BW_LD = MLP_ROWS + 4;
 constexpr int BW_XROWS = DIN + 2;         // inputs, ones, zeros
-// Two blocks per CU.  60 000 rows: 938 chunks.
-constexpr uint32_t BW_MAX_BLOCKS = 512;
+constexpr uint32_t BW_MAX_BLOCKS = 256;  // one per CU
 
-__host__ __device__ inline uint32_t bw_blocks(uint32_t n) {
-    const uint32_t chunks = (n + MLP_ROWS - 1) / MLP_ROWS;
-    return chunks < BW_MAX_BLOCKS ? chunks : BW_MAX_BLOCKS;
+// Waves of a block: eight where four, one to a SIMD, would leave more than one
+// chunk to a CU; up to there four spread the rows over more CUs (16 384 rows 26.0
+// us a training step, 16 500 30.6 in eight).
+inline int bw_waves(uint32_t n) { return n > 64 * BW_MAX_BLOCKS ? 8 : 4; }
+inline uint32_t bw_blocks(uint32_t n) {
+    const uint32_t rows = 16 * bw_waves(n);
+    return (uint32_t)std::min<uint64_t>(((uint64_t)n + rows - 1) / rows, BW_MAX_BLOCKS);
 }
 
+template <int W>
 struct BackwardLds {
+    static constexpr int ROWS = 16 * W, LD = ROWS + 4;
     alignas(16) float w2[2][HID / 8][64][4];  // A operand: W2[32 t + lane%32][2 (4q + e) + lane/32]
-    alignas(16) float h1[HID][BW_LD];
-    alignas(16) float h2[HID][BW_LD];
-    alignas(16) float d1[HID][BW_LD];
-    alignas(16) float xs[BW_XROWS][BW_LD];
-    alignas(16) float dy[MLP_ROWS];
-    float w3[HID];
+    alignas(16) float h1[HID][LD];
+    alignas(16) float h2[HID][LD];
+    alignas(16) float d1[HID][LD];
+    alignas(16) float xs[BW_XROWS][LD];
+    alignas(16) float dy[ROWS];
+    alignas(16) float w3[3][HID];  // in order; those of unit 2s, 2s + 1 at s
+    static_assert(W * (DIN + 1) * HID <= HID * LD, "dW1 partials fit the h1 area");
+    static_assert((W - 4) * (16 + 2) * 64 + 2 <= HID * LD, "the upper waves' partials fit the h2 area");
 };
-static_assert(sizeof(float) * 4 * (DIN + 1) * HID <= sizeof(float) * HID * BW_LD, "dW1 partials fit the h1 area");
 
 // Four consecutive rows of a unit's activations, zero past n.
 __device__ __forceinline__ f32x4 load_rows4(const float* __restrict__ p, uint32_t i, uint32_t n) {
@@ -312,41 +334,46 @@ __device__ __forceinline__ f32x4 load_rows4(const float* __restrict__ p, uint32_
     return v;
 }
 
-__global__ __launch_bounds__(256, 2) void mlp_backward_kernel(
+template <int W>
+__global__ __launch_bounds__(64 * W, 2) void mlp_backward_kernel(
     const float* __restrict__ params, const float* __restrict__ norm, const float* __restrict__ x,
     const float* __restrict__ t, uint32_t n, const float* __restrict__ y, const float* __restrict__ h1t,
     const float* __restrict__ h2t, float* __restrict__ part) {
-    __shared__ BackwardLds L;
+    constexpr int T = 64 * W, ROWS = 16 * W;
+    __shared__ BackwardLds<W> L;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5, l32 = lane & 31;
-    const uint32_t chunks = (n + MLP_ROWS - 1) / MLP_ROWS;
+    const uint32_t chunks = (uint32_t)(((uint64_t)n + ROWS - 1) / ROWS);
     float* w2 = &L.w2[0][0][0][0];
-    for (int i = tid; i < HID * HID; i += 256) {
+    float wv[HID * HID / T], w3v = 0.0f;
+#pragma unroll
+    for (int p = 0; p < HID * HID / T; ++p) {
+        const int i = tid + T * p;
         const int e = i & 3, ln = (i >> 2) & 63, q = (i >> 8) & 7, tt = i >> 11;
-        w2[i] = params[OFF_W2 + (32 * tt + (ln & 31)) * HID + 2 * (4 * q + e) + (ln >> 5)];
+        wv[p] = params[OFF_W2 + (32 * tt + (ln & 31)) * HID + 2 * (4 * q + e) + (ln >> 5)];
     }
-    if (tid < HID) L.w3[tid] = params[OFF_W3 + tid];
-    if (tid < BW_LD) {
+    if (tid < HID) w3v = params[OFF_W3 + tid];
+    if (tid < L.LD) {
         L.xs[DIN][tid] = 1.0f;
         L.xs[DIN + 1][tid] = 0.0f;
     }
 
-    // Thread's share of a chunk: rows 4 (tid % 16) .. + 3 of units tid / 16 + 16 q.
+    // Thread's share of a chunk: rows 4 (tid % (4 W)) .. + 3 of units tid / (4 W) + 16 q.
     f32x4 p1[4], p2[4], px;
     float py = 0.0f, pt = 0.0f;
     auto load = [&](uint32_t c) {
-        const uint32_t i = c * MLP_ROWS + 4 * (tid & 15);
+        const uint32_t i = c * ROWS + 4 * (tid % (4 * W));
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            p1[q] = load_rows4(h1t + (uint64_t)(16 * q + (tid >> 4)) * n, i, n);
-            p2[q] = load_rows4(h2t + (uint64_t)(16 * q + (tid >> 4)) * n, i, n);
+            p1[q] = load_rows4(h1t + (uint64_t)(16 * q + tid / (4 * W)) * n, i, n);
+            p2[q] = load_rows4(h2t + (uint64_t)(16 * q + tid / (4 * W)) * n, i, n);
         }
         px = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-        if (tid < MLP_ROWS * DIN / 4) {
-            const uint32_t r = c * MLP_ROWS + tid / (DIN / 4);
+        if (tid < ROWS * DIN / 4) {
+            const uint32_t r = c * ROWS + tid / (DIN / 4);
             if (r < n) px = *reinterpret_cast<const f32x4u*>(x + (uint64_t)r * DIN + 4 * (tid % (DIN / 4)));
         }
-        if (tid < MLP_ROWS) {
-            const uint32_t r = c * MLP_ROWS + tid;
+        if (tid < ROWS) {
+            const uint32_t r = c * ROWS + tid;
             py = r < n ? y[r] : 0.0f;
             pt = r < n ? t[r] : 0.0f;
         }
@@ -358,26 +385,34 @@ __global__ __launch_bounds__(256, 2) void mlp_backward_kernel(
         nsd[e] = norm[DIN + 4 * (tid % (DIN / 4)) + e];
     }
 
-    const int ta = wave >> 1, tj = wave & 1;  // this wave's tile of dW2, and of d1 (units, rows)
+    const int da = wave & 1, dr = wave >> 1;                       // this wave's tile of d1: units, rows
+    const int ta = (wave >> 1) & 1, tj = wave & 1, th = wave >> 2;  // of dW2, over rows 64 th .. + 63
     f32x16 g2, g1[2];
 #pragma unroll
     for (int r = 0; r < 16; ++r) g2[r] = g1[0][r] = g1[1][r] = 0.0f;
     float gb2 = 0.0f, gw3 = 0.0f, gb3 = 0.0f, e2 = 0.0f;
     uint32_t c = blockIdx.x;
     load(c);
+    __builtin_amdgcn_sched_barrier(0);  // every load is in flight before the first is waited for
+#pragma unroll
+    for (int p = 0; p < HID * HID / T; ++p) w2[tid + T * p] = wv[p];
+    if (tid < HID) {
+        L.w3[0][tid] = w3v;
+        L.w3[1 + (tid & 1)][tid >> 1] = w3v;
+    }
     for (; c < chunks; c += gridDim.x) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            *reinterpret_cast<f32x4*>(&L.h1[16 * q + (tid >> 4)][4 * (tid & 15)]) = p1[q];
-            *reinterpret_cast<f32x4*>(&L.h2[16 * q + (tid >> 4)][4 * (tid & 15)]) = p2[q];
+            *reinterpret_cast<f32x4*>(&L.h1[16 * q + tid / (4 * W)][4 * (tid % (4 * W))]) = p1[q];
+            *reinterpret_cast<f32x4*>(&L.h2[16 * q + tid / (4 * W)][4 * (tid % (4 * W))]) = p2[q];
         }
-        if (tid < MLP_ROWS * DIN / 4) {
+        if (tid < ROWS * DIN / 4) {
             const int r = tid / (DIN / 4), k = 4 * (tid % (DIN / 4));
-            const bool in = c * MLP_ROWS + r < n;
+            const bool in = c * ROWS + r < n;
 #pragma unroll
             for (int e = 0; e < 4; ++e) L.xs[k + e][r] = in ? (px[e] - nmu[e]) * nsd[e] : 0.0f;
         }
-        if (tid < MLP_ROWS) {
+        if (tid < ROWS) {
             const float err = py - pt;
             const float dy = 2.0f * err / (float)n;
             L.dy[tid] = dy;
@@ -387,82 +422,89 @@ __global__ __launch_bounds__(256, 2) void mlp_backward_kernel(
         __syncthreads();
         if (c + gridDim.x < chunks) load(c + gridDim.x);
 
-        {  // d1, units 32 ta .. + 31 of rows 32 tj .. + 31
-            f32x16 acc;
+        // d1, units 32 da .. + 31 of rows 32 dr .. + 31, and dW2, which needs no d1;
+        // a step's operands are read from LDS during the step before.
+        const int row = 32 * dr + l32;
+        const float dyr = L.dy[row], w3c = L.w3[0][32 * tj + l32];
+        f32x16 acc;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
-            const int row = 32 * tj + l32;
-            const float dy = L.dy[row];
+        for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+        struct Step {
+            f32x4 w, w3, hr, a, h, dy;
+        } st[2];
+        auto read = [&](int q, Step& o) {
+            o.w = *reinterpret_cast<const f32x4*>(L.w2[da][q][lane]);
+            o.w3 = *reinterpret_cast<const f32x4*>(&L.w3[1 + half][4 * q]);
 #pragma unroll
-            for (int q = 0; q < HID / 8; ++q) {
-                const f32x4 a = *reinterpret_cast<const f32x4*>(L.w2[ta][q][lane]);
+            for (int e = 0; e < 4; ++e) o.hr[e] = L.h2[2 * (4 * q + e) + half][row];
+            const int k = 64 * th + 8 * q + 4 * half;  // k steps take rows 8q + e and 8q + 4 + e
+            o.a = *reinterpret_cast<const f32x4*>(&L.h1[32 * ta + l32][k]);
+            o.h = *reinterpret_cast<const f32x4*>(&L.h2[32 * tj + l32][k]);
+            o.dy = *reinterpret_cast<const f32x4*>(&L.dy[k]);
+        };
+        read(0, st[0]);
+        float hm[16];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int j = 2 * (4 * q + e) + half;
-                    acc = mfma32(a[e], L.h2[j][row] > 0.0f ? dy * L.w3[j] : 0.0f, acc);
-                }
+        for (int q = 0; q < 8; ++q) {
+            if (q < 7) read(q + 1, st[(q + 1) & 1]);
+            else
+#pragma unroll
+                for (int r = 0; r < 16; ++r) hm[r] = L.h1[32 * da + acc_row(r, half)][row];
+            __builtin_amdgcn_sched_barrier(0);
+            const Step& o = st[q & 1];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                acc = mfma32(o.w[e], o.hr[e] > 0.0f ? dyr * o.w3[e] : 0.0f, acc);
+                const float d2 = o.h[e] > 0.0f ? o.dy[e] * w3c : 0.0f;
+                g2 = mfma32(o.a[e], d2, g2);
+                gb2 += d2;
+                gw3 += o.dy[e] * o.h[e];
             }
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int a = 32 * ta + acc_row(r, half);
-                L.d1[a][row] = L.h1[a][row] > 0.0f ? acc[r] : 0.0f;
-            }
+            __builtin_amdgcn_sched_barrier(0);
         }
-        // dW2 needs no d1: it runs before the barrier
-        {
-            const float w3 = L.w3[32 * tj + l32];
+        const int xr = l32 < DIN + 1 ? l32 : DIN + 1, k1 = 16 * wave + 4 * half;
+        f32x4 xa[2], dd[2][2];
 #pragma unroll
-            for (int q = 0; q < MLP_ROWS / 8; ++q) {
-                const int row = 8 * q + 4 * half;  // k steps take rows 8q + e and 8q + 4 + e
-                const f32x4 a = *reinterpret_cast<const f32x4*>(&L.h1[32 * ta + l32][row]);
-                const f32x4 h = *reinterpret_cast<const f32x4*>(&L.h2[32 * tj + l32][row]);
-                const f32x4 dy = *reinterpret_cast<const f32x4*>(&L.dy[row]);
+        for (int q = 0; q < 2; ++q) xa[q] = *reinterpret_cast<const f32x4*>(&L.xs[xr][k1 + 8 * q]);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float d2 = h[e] > 0.0f ? dy[e] * w3 : 0.0f;
-                    g2 = mfma32(a[e], d2, g2);
-                    gb2 += d2;
-                    gw3 += dy[e] * h[e];
-                }
-            }
-        }
+        for (int r = 0; r < 16; ++r) L.d1[32 * da + acc_row(r, half)][row] = hm[r] > 0.0f ? acc[r] : 0.0f;
         __syncthreads();
-        const int xr = l32 < DIN + 1 ? l32 : DIN + 1;
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int row = 16 * wave + 8 * q + 4 * half;
-            const f32x4 a = *reinterpret_cast<const f32x4*>(&L.xs[xr][row]);
+        for (int q = 0; q < 2; ++q)
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const f32x4 d = *reinterpret_cast<const f32x4*>(&L.d1[32 * u + l32][row]);
+            for (int u = 0; u < 2; ++u) dd[q][u] = *reinterpret_cast<const f32x4*>(&L.d1[32 * u + l32][k1 + 8 * q]);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) g1[u] = mfma32(a[e], d[e], g1[u]);
-            }
-        }
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int u = 0; u < 2; ++u) g1[u] = mfma32(xa[q][e], dd[q][u][e], g1[u]);
         __syncthreads();  // the next chunk reuses the LDS
     }
 
     float* out = part + (uint64_t)blockIdx.x * (NP + 1);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) out[OFF_W2 + (32 * ta + acc_row(r, half)) * HID + 32 * tj + l32] = g2[r];
     gb2 += __shfl_xor(gb2, 32);
     gw3 += __shfl_xor(gw3, 32);
-    if (ta == 0 && half == 0) {
-        out[OFF_B2 + 32 * tj + l32] = gb2;
-        out[OFF_W3 + 32 * tj + l32] = gw3;
-    }
-    if (wave == 0) {
 #pragma unroll
-        for (int m = 1; m < 64; m <<= 1) {
-            gb3 += __shfl_xor(gb3, m);
-            e2 += __shfl_xor(e2, m);
+    for (int m = 1; m < 64; m <<= 1) {
+        gb3 += __shfl_xor(gb3, m);
+        e2 += __shfl_xor(e2, m);
+    }
+    float* up = &L.h2[0][0];  // [wave - 4][register, db2, dw3][lane], then the second 64 rows' db3 and error
+    float* w1 = &L.h1[0][0];  // [wave][input or ones][unit]
+    if (W == 8) {
+        if (wave >= 4) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) up[((wave - 4) * 18 + r) * 64 + lane] = g2[r];
+            up[((wave - 4) * 18 + 16) * 64 + lane] = gb2;
+            up[((wave - 4) * 18 + 17) * 64 + lane] = gw3;
         }
-        if (lane == 0) {
-            out[OFF_B3] = gb3;
-            out[NP] = e2;
+        if (wave == 1 && lane == 0) {
+            up[4 * 18 * 64] = gb3;
+            up[4 * 18 * 64 + 1] = e2;
         }
     }
-    float* w1 = &L.h1[0][0];  // [wave][input or ones][unit]
 #pragma unroll
     for (int u = 0; u < 2; ++u)
 #pragma unroll
@@ -471,39 +513,54 @@ __global__ __launch_bounds__(256, 2) void mlp_backward_kernel(
             if (m <= DIN) w1[(wave * (DIN + 1) + m) * HID + 32 * u + l32] = g1[u][r];
         }
     __syncthreads();
-    for (int i = tid; i < (DIN + 1) * HID; i += 256)  // W1, then b1 right after it
-        out[i] = ((w1[i] + w1[(DIN + 1) * HID + i]) + w1[2 * (DIN + 1) * HID + i]) + w1[3 * (DIN + 1) * HID + i];
+    if (wave < 4) {
+        if (W == 8) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) g2[r] += up[(wave * 18 + r) * 64 + lane];
+            gb2 += up[(wave * 18 + 16) * 64 + lane];
+            gw3 += up[(wave * 18 + 17) * 64 + lane];
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) out[OFF_W2 + (32 * ta + acc_row(r, half)) * HID + 32 * tj + l32] = g2[r];
+        if (ta == 0 && half == 0) {
+            out[OFF_B2 + 32 * tj + l32] = gb2;
+            out[OFF_W3 + 32 * tj + l32] = gw3;
+        }
+        if (wave == 0 && lane == 0) {
+            out[OFF_B3] = W == 8 ? gb3 + up[4 * 18 * 64] : gb3;
+            out[NP] = W == 8 ? e2 + up[4 * 18 * 64 + 1] : e2;
+        }
+    }
+    for (int i = tid; i < (DIN + 1) * HID; i += T) {  // W1, then b1 right after it
+        float v = 0.0f;
+#pragma unroll
+        for (int w = 0; w < W; ++w) v += w1[w * (DIN + 1) * HID + i];
+        out[i] = v;
+    }
 }
 
-// Sum of the block partials: 64 parameters per block, 16 waves each adding
-// every 16th partial (their loads independent of each other), then the waves'
-// sums in wave order.
+// Sum of the block partials: 32 parameters per block, so that 158 CUs read; 32
+// half-waves each add every 32nd partial (up to eight, their loads all in
+// flight), then the half-waves' sums in order.
 __global__ __launch_bounds__(1024) void mlp_reduce_kernel(const float* __restrict__ part, uint32_t nblocks,
                                                           uint32_t n, float* __restrict__ grad,
                                                           float* __restrict__ loss) {
-    __shared__ float sums[16][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int p = blockIdx.x * 64 + lane;
-    float s = 0.0f;
-    if (p <= NP) {
-        uint32_t b = wave;
-        for (; b + 112 < nblocks; b += 128) {
-            float v[8];
+    __shared__ float sums[32][32];
+    static_assert(BW_MAX_BLOCKS <= 256, "eight partials per half-wave");
+    const uint32_t lane = threadIdx.x & 31, g = threadIdx.x >> 5;
+    const uint32_t p = blockIdx.x * 32 + lane;
+    float v[8];
 #pragma unroll
-            for (int q = 0; q < 8; ++q) v[q] = part[(uint64_t)(b + 16 * q) * (NP + 1) + p];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) s += v[q];
-        }
-        for (; b < nblocks; b += 16) s += part[(uint64_t)b * (NP + 1) + p];
-    }
-    sums[wave][lane] = s;
+    for (uint32_t q = 0; q < 8; ++q)
+        v[q] = p <= NP && g + 32 * q < nblocks ? part[(uint64_t)(g + 32 * q) * (NP + 1) + p] : 0.0f;
+    sums[g][lane] = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
     __syncthreads();
-    if (wave == 0 && p <= NP) {
-        float v = 0.0f;
+    if (g == 0 && p <= NP) {
+        float t = 0.0f;
 #pragma unroll
-        for (int w = 0; w < 16; ++w) v += sums[w][lane];
-        if (p < NP) grad[p] = v;
-        else *loss = v / (float)n;
+        for (int w = 0; w < 32; ++w) t += sums[w][lane];
+        if (p < NP) grad[p] = t;
+        else *loss = t / (float)n;
     }
 }
 
@@ -810,7 +867,8 @@ int spmd_mlp_forward(const float* params, const float* norm, const float* x, uin
     if (!params || !norm || (n && (!x || !y)) || (!h1t) != (!h2t)) return SPMD_ERR_ARGS;
     if (!n) return SPMD_OK;
     clear_stale_error();
-    const dim3 g((uint32_t)(((uint64_t)n + 4 * MLP_ROWS - 1) / (4 * MLP_ROWS))), b(256);
+    constexpr uint32_t per_block = FW_THREADS / 64 * FW_ROWS;
+    const dim3 g((uint32_t)(((uint64_t)n + per_block - 1) / per_block)), b(FW_THREADS);
     const hipStream_t s = static_cast<hipStream_t>(stream);
     if (h1t) hipLaunchKernelGGL(mlp_forward_kernel<true>, g, b, 0, s, params, norm, x, n, y, h1t, h2t);
     else hipLaunchKernelGGL(mlp_forward_kernel<false>, g, b, 0, s, params, norm, x, n, y, h1t, h2t);
@@ -832,8 +890,11 @@ int spmd_mlp_backward(const float* params, const float* norm, const float* x, co
     hipStream_t s = static_cast<hipStream_t>(stream);
     float* part = static_cast<float*>(workspace);
     clear_stale_error();
-    hipLaunchKernelGGL(mlp_backward_kernel, dim3(nb), dim3(256), 0, s, params, norm, x, t, n, y, h1t, h2t, part);
-    hipLaunchKernelGGL(mlp_reduce_kernel, dim3((NP + 1 + 63) / 64), dim3(1024), 0, s, part, nb, n, grad, loss);
+    if (bw_waves(n) == 8)
+        hipLaunchKernelGGL(mlp_backward_kernel<8>, dim3(nb), dim3(512), 0, s, params, norm, x, t, n, y, h1t, h2t, part);
+    else
+        hipLaunchKernelGGL(mlp_backward_kernel<4>, dim3(nb), dim3(256), 0, s, params, norm, x, t, n, y, h1t, h2t, part);
+    hipLaunchKernelGGL(mlp_reduce_kernel, dim3((NP + 1 + 31) / 32), dim3(1024), 0, s, part, nb, n, grad, loss);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? SPMD_OK : hip_fail(e);
 }

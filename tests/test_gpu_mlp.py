@@ -375,6 +375,13 @@ def test_training_kernels_at_tile_edges(L, n):
     assert abs(float(loss.item()) - omlp.loss(*args)) <= 1e-5 * omlp.loss(*args)
 
 
+@pytest.mark.parametrize("n", [31, 33, 127, 129, 16383, 16384, 16385, 16512, 128 * 256, 128 * 256 + 3, 70001])
+def test_training_kernels_at_block_edges(L, n):
+    """Rows around a wave's tile, around the change from blocks of four waves to
+    eight, and around one, two and three chunks to a block."""
+    test_training_kernels_at_tile_edges(L, n)
+
+
 @pytest.mark.parametrize("m,c,k", [(1, 256, 1), (255, 5, 3), (4100, 144, 3), (300, 65, 4)])
 def test_choose_is_the_least_forward_prediction(L, m, c, k):
     """Every (launch, candidate) through the forward kernel, the models' mean
