@@ -61,7 +61,7 @@ struct alignas(16) BatchDesc {
     uint32_t aux;      // REDUCE/HIST: elements per block; JACOBI: blocks per row
     uint64_t in, out;
     uint64_t ws;       // run-area scratch of this instance
-    uint32_t vec;      // REDUCE/HIST: in 16-byte aligned
+    uint32_t vec;      // HIST: in 16-byte aligned
     uint32_t pad;
 };
 static_assert(sizeof(BatchDesc) == 64, "descriptor is 64 bytes");
@@ -120,7 +120,7 @@ __device__ __forceinline__ void run_logical_block(const BatchDesc& d, uint32_t b
         uint32_t* ctl = reinterpret_cast<uint32_t*>(d.ws);
         uint64_t* status = reinterpret_cast<uint64_t*>(d.ws + REDUCE_CTL_BYTES);
         reduce_block<B>(reinterpret_cast<const int32_t*>(d.in), nullptr, reinterpret_cast<int32_t*>(d.out), d.n,
-                        d.aux, d.nblocks, b, ctl, status, err, d.vec != 0u, L.r);
+                        d.aux, d.nblocks, b, ctl, status, err, L.r);
     } else if constexpr (CLS == SPMD_SCAN_I32) {
         const int32_t* x = reinterpret_cast<const int32_t*>(d.in);
         int32_t* y = reinterpret_cast<int32_t*>(d.out);
@@ -193,7 +193,7 @@ __device__ __forceinline__ void run_fused_chunk(const BatchDesc& d, uint32_t q, 
         uint32_t* ctl = reinterpret_cast<uint32_t*>(d.ws);
         uint64_t* status = reinterpret_cast<uint64_t*>(d.ws + REDUCE_CTL_BYTES);
         reduce_block<B>(reinterpret_cast<const int32_t*>(d.in), nullptr, reinterpret_cast<int32_t*>(d.out), d.n,
-                        seg, nchunks, q, ctl, status, err, d.vec != 0u, L.r);
+                        seg, nchunks, q, ctl, status, err, L.r);
         (void)lo;
         (void)hi;
     } else {

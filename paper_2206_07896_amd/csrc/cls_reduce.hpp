@@ -1,8 +1,10 @@
 // cls_reduce.hpp -- block body of the REDUCE_I32 class.
 //
-// One logical block of B threads sums its segment x[lo, hi) into one
-// partial; the block that takes the last completion ticket then sums all G
-// partials into *out and re-arms the ticket counter.
+// One logical block sums its segment x[lo, hi) into one partial, by B threads
+// or, where segments are short, by one wave (reduce_waves); the workgroup that
+// takes the last completion ticket then sums all workgroups' totals into *out
+// and re-arms the ticket counter.  Loads are 16 bytes per lane at any alignment
+// (2^24 elements one element off 16 bytes, a word per lane: 68 us against 45).
 //
 // gfx950 mapping of the block tree: levels whose stride is >= 64 combine
 // values held by different waves and go through LDS with a barrier; levels
@@ -41,47 +43,42 @@ __device__ __forceinline__ uint32_t block_sum_t0(uint32_t v, ReduceLds<B>& L) {
 }
 
 // Thread t's share of x[lo, hi): the segment is walked in rows of B
-// 16-byte chunks (one per thread), four rows in flight per step, starting
+// 16-byte chunks (one per thread, at any alignment), four rows in flight per step, starting
 // at a row that depends on the block: blocks whose segments lie a large
 // power of two apart then do not stream the same memory channels in
 // lockstep.  Integer sums do not depend on the order.
 template <int B>
-__device__ __forceinline__ uint32_t segment_sum(const int32_t* __restrict__ x, uint64_t lo, uint64_t hi, bool vec,
-                                                uint32_t bid) {
+__device__ __forceinline__ uint32_t segment_sum(const int32_t* __restrict__ x, uint64_t lo, uint64_t hi, uint32_t bid) {
     const uint32_t t = threadIdx.x;
     uint32_t acc = 0;
     if (lo >= hi) return 0;
-    if (vec) {
-        const u32x4* xv = reinterpret_cast<const u32x4*>(x + lo);
-        const uint64_t nv = (hi - lo) >> 2;
-        const uint64_t rows = nv / B;  // full rows
-        const uint64_t r0 = rows ? (bid * 7u) % rows : 0;
-        uint64_t r = 0;
-        for (; r + 4 <= rows; r += 4) {
-            u32x4 a[4];
+    const u32x4_a4* xv = reinterpret_cast<const u32x4_a4*>(x + lo);
+    const uint64_t nv = (hi - lo) >> 2;
+    const uint64_t rows = nv / B;  // full rows
+    const uint64_t r0 = rows ? (bid * 7u) % rows : 0;
+    uint64_t r = 0;
+    for (; r + 4 <= rows; r += 4) {
+        u32x4 a[4];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                uint64_t row = r0 + r + q;
-                row = row >= rows ? row - rows : row;
-                a[q] = __builtin_nontemporal_load(xv + row * B + t);
-            }
-#pragma unroll
-            for (int q = 0; q < 4; ++q) acc += (a[q].x + a[q].y) + (a[q].z + a[q].w);
-        }
-        for (; r < rows; ++r) {
-            uint64_t row = r0 + r;
+        for (int q = 0; q < 4; ++q) {
+            uint64_t row = r0 + r + q;
             row = row >= rows ? row - rows : row;
-            const u32x4 a = __builtin_nontemporal_load(xv + row * B + t);
-            acc += (a.x + a.y) + (a.z + a.w);
+            a[q] = __builtin_nontemporal_load(xv + row * B + t);
         }
-        for (uint64_t k = rows * B + t; k < nv; k += B) {
-            const u32x4 a = __builtin_nontemporal_load(xv + k);
-            acc += (a.x + a.y) + (a.z + a.w);
-        }
-        for (uint64_t j = lo + (nv << 2) + t; j < hi; j += B) acc += (uint32_t)x[j];
-    } else {
-        for (uint64_t j = lo + t; j < hi; j += B) acc += (uint32_t)x[j];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc += (a[q].x + a[q].y) + (a[q].z + a[q].w);
     }
+    for (; r < rows; ++r) {
+        uint64_t row = r0 + r;
+        row = row >= rows ? row - rows : row;
+        const u32x4 a = __builtin_nontemporal_load(xv + row * B + t);
+        acc += (a.x + a.y) + (a.z + a.w);
+    }
+    for (uint64_t k = rows * B + t; k < nv; k += B) {
+        const u32x4 a = __builtin_nontemporal_load(xv + k);
+        acc += (a.x + a.y) + (a.z + a.w);
+    }
+    for (uint64_t j = lo + (nv << 2) + t; j < hi; j += B) acc += (uint32_t)x[j];
     return acc;
 }
 
@@ -159,12 +156,12 @@ __device__ __forceinline__ void reduce_final(uint64_t* status, uint32_t count, u
 template <int B>
 __device__ __forceinline__ bool reduce_block(const int32_t* __restrict__ x, int32_t* partials, int32_t* out,
                                              uint32_t n, uint32_t seg, uint32_t G, uint32_t bid, uint32_t* ctl,
-                                             uint64_t* status, uint32_t* err, bool vec, ReduceLds<B>& L) {
+                                             uint64_t* status, uint32_t* err, ReduceLds<B>& L) {
     const uint64_t lo = (uint64_t)bid * seg;
     const uint64_t hi = lo + seg < (uint64_t)n ? lo + seg : (uint64_t)n;
     // the epoch's round trip overlaps the segment's loads
     const uint32_t epoch = threadIdx.x == 0 ? load_dev(ctl + REDUCE_EPOCH_WORD) : 0u;
-    const uint32_t tot = block_sum_t0<B>(segment_sum<B>(x, lo, hi, vec, bid), L);
+    const uint32_t tot = block_sum_t0<B>(segment_sum<B>(x, lo, hi, bid), L);
     if (threadIdx.x == 0) {
         if (partials) partials[bid] = (int32_t)tot;
         status_put(status + bid, status_pack(tot, 1u, epoch));
@@ -181,6 +178,44 @@ __device__ __forceinline__ bool reduce_block(const int32_t* __restrict__ x, int3
 }
 
 
+// acc[j] = thread t's share of logical block b0 + j, j < K, T threads at it:
+// 16-byte groups in rows of T, four rows of each of the K blocks in flight.
+template <int T, int K>
+__device__ __forceinline__ void segment_sums(const int32_t* __restrict__ x, uint32_t n, uint32_t seg, uint32_t G,
+                                             uint32_t b0, uint32_t t, uint32_t (&acc)[K]) {
+    uint64_t lo[K], hi[K], nv[K];
+    uint64_t nvmax = 0;
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+        acc[j] = 0;
+        lo[j] = (uint64_t)(b0 + j) * seg;
+        hi[j] = b0 + j < G ? (lo[j] + seg < (uint64_t)n ? lo[j] + seg : (uint64_t)n) : lo[j];
+        if (hi[j] < lo[j]) hi[j] = lo[j];
+        nv[j] = (hi[j] - lo[j]) >> 2;  // whole 16-byte groups (seg is a multiple of 4)
+        nvmax = nv[j] > nvmax ? nv[j] : nvmax;
+    }
+    // the K segments' 16-byte groups, four rows of T per segment in flight
+    const u32x4_a4* xv = reinterpret_cast<const u32x4_a4*>(x);
+    for (uint64_t v0 = t; v0 < nvmax; v0 += 4u * T) {
+        u32x4 a[K][4];
+#pragma unroll
+        for (int j = 0; j < K; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const uint64_t v = v0 + (uint64_t)q * T;
+                a[j][q] = v < nv[j] ? __builtin_nontemporal_load(xv + (lo[j] >> 2) + v) : u32x4{0u, 0u, 0u, 0u};
+            }
+#pragma unroll
+        for (int j = 0; j < K; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) acc[j] += (a[j][q].x + a[j][q].y) + (a[j][q].z + a[j][q].w);
+    }
+    // what is left: the last segment's tail
+#pragma unroll
+    for (int j = 0; j < K; ++j)
+        for (uint64_t e = lo[j] + (nv[j] << 2) + t; e < hi[j]; e += T) acc[j] += (uint32_t)x[e];
+}
+
 // K consecutive logical blocks [K w, K w + K) of a G-block reduction run by
 // workgroup w of P (the launcher's persistent form: P covers the device's
 // resident workgroups, so fewer workgroups than logical blocks each keep
@@ -191,43 +226,13 @@ __device__ __forceinline__ bool reduce_block(const int32_t* __restrict__ x, int3
 template <int B, int K>
 __device__ __forceinline__ void reduce_blocks(const int32_t* __restrict__ x, int32_t* partials, int32_t* out,
                                               uint32_t n, uint32_t seg, uint32_t G, uint32_t P, uint32_t w,
-                                              uint32_t* ctl, uint64_t* status, uint32_t* err, bool vec,
-                                              ReduceLds<B>& L, uint32_t (&wsum)[K][B / 64]) {
+                                              uint32_t* ctl, uint64_t* status, uint32_t* err, ReduceLds<B>& L,
+                                              uint32_t (&wsum)[K][B / 64]) {
     const uint32_t t = threadIdx.x;
     const uint32_t b0 = w * K;
     const uint32_t epoch = t == 0 ? load_dev(ctl + REDUCE_EPOCH_WORD) : 0u;
     uint32_t acc[K];
-    uint64_t lo[K], hi[K], nv[K];
-    uint64_t nvmax = 0;
-#pragma unroll
-    for (int j = 0; j < K; ++j) {
-        acc[j] = 0;
-        lo[j] = (uint64_t)(b0 + j) * seg;
-        hi[j] = b0 + j < G ? (lo[j] + seg < (uint64_t)n ? lo[j] + seg : (uint64_t)n) : lo[j];
-        if (hi[j] < lo[j]) hi[j] = lo[j];
-        nv[j] = vec ? (hi[j] - lo[j]) >> 2 : 0;  // whole 16-byte groups (seg is a multiple of 4)
-        nvmax = nv[j] > nvmax ? nv[j] : nvmax;
-    }
-    // the K segments' 16-byte groups, four rows of B per segment in flight
-    const u32x4* xv = reinterpret_cast<const u32x4*>(x);
-    for (uint64_t v0 = t; v0 < nvmax; v0 += 4u * B) {
-        u32x4 a[K][4];
-#pragma unroll
-        for (int j = 0; j < K; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const uint64_t v = v0 + (uint64_t)q * B;
-                a[j][q] = v < nv[j] ? __builtin_nontemporal_load(xv + (lo[j] >> 2) + v) : u32x4{0u, 0u, 0u, 0u};
-            }
-#pragma unroll
-        for (int j = 0; j < K; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) acc[j] += (a[j][q].x + a[j][q].y) + (a[j][q].z + a[j][q].w);
-    }
-    // what is left: the last segment's tail, or everything when unaligned
-#pragma unroll
-    for (int j = 0; j < K; ++j)
-        for (uint64_t e = lo[j] + (nv[j] << 2) + t; e < hi[j]; e += B) acc[j] += (uint32_t)x[e];
+    segment_sums<B, K>(x, n, seg, G, b0, t, acc);
 #pragma unroll
     for (int j = 0; j < K; ++j) {
         const uint32_t s = wave_sum(acc[j]);
@@ -255,6 +260,38 @@ __device__ __forceinline__ void reduce_blocks(const int32_t* __restrict__ x, int
     const uint32_t tag = L.epoch;
     __syncthreads();
     if (last) reduce_final<B>(status, P, tag, ctl, out, err, L);
+}
+
+// The same with a wave per logical block, J of them at once: the four
+// waves of workgroup w run blocks [4 J w, 4 J w + 4 J).
+template <int J>
+__device__ __forceinline__ void reduce_waves(const int32_t* __restrict__ x, int32_t* partials, int32_t* out,
+                                             uint32_t n, uint32_t seg, uint32_t G, uint32_t P, uint32_t w,
+                                             uint32_t* ctl, uint64_t* status, uint32_t* err, ReduceLds<256>& L) {
+    const uint32_t t = threadIdx.x, lane = lane64(), wave = t >> 6;
+    const uint32_t b0 = (4 * w + wave) * J;
+    const uint32_t epoch = t == 0 ? load_dev(ctl + REDUCE_EPOCH_WORD) : 0u;
+    uint32_t acc[J], total = 0, mine = 0;
+    segment_sums<64, J>(x, n, seg, G, b0, lane, acc);
+#pragma unroll
+    for (int j = 0; j < J; ++j) {  // blocks past G sum nothing
+        const uint32_t s = wave_sum(acc[j]);
+        total += s;
+        mine = lane == (uint32_t)j ? s : mine;
+    }
+    if (partials && lane < J && b0 + lane < G) partials[b0 + lane] = (int32_t)mine;
+    if (lane == 0) L.wave[wave] = total;
+    __syncthreads();
+    if (t == 0) {
+        status_put(status + w, status_pack((L.wave[0] + L.wave[1]) + (L.wave[2] + L.wave[3]), 1u, epoch));
+        L.last = reduce_ticket_last(ctl, P, w) ? 1u : 0u;
+        L.epoch = epoch;
+    }
+    __syncthreads();
+    const bool last = L.last != 0u;
+    const uint32_t tag = L.epoch;
+    __syncthreads();
+    if (last) reduce_final<256>(status, P, tag, ctl, out, err, L);
 }
 
 }  // namespace spmd

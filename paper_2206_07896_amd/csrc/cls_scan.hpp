@@ -153,8 +153,6 @@ struct NoHook {
     __device__ void operator()() const {}
 };
 
-typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));  // 16 bytes at any element's address
-
 // Rows form of a full tile with I >= 4: wave w owns elements [w*64*I,
 // (w+1)*64*I) of the tile as I/4 rows of 64 lanes x 4 consecutive elements.
 // `wx` / `wy` point at the wave's first element, at any alignment (the same

@@ -112,6 +112,39 @@ def test_reduce_wrapping_and_unaligned(spmd):
         assert np.array_equal(host(p), want_p), grid
 
 
+@pytest.mark.parametrize("off", [0, 1, 2])
+@pytest.mark.parametrize("n,grid,block", [
+    # a wave per logical block, one or two at a time: segments of nothing to a
+    # few rows, the last ones empty, grids that no workgroup divides
+    (1, 5, 64), (257, 3, 1024), (1021, 257, 64), (4099, 4097, 256), (1000003, 1023, 512), (1000003, 4095, 256),
+    (1000003, 16385, 128), (1024 * 255 + 1, 256, 256), (2048 * 1024, 1024, 64), (2048 * 4096 - 1, 4096, 1024),
+    # past it: a workgroup per one, two, four and eight, of the launch's threads or fewer
+    (1024 * 255 + 8, 255, 256), (2048 * 1024 + 1, 1024, 512), (2048 * 4096 + 7, 4096, 1024), (2052 * 8192, 8192, 512),
+    (2052 * 16384 + 3, 16384, 256)])
+def test_reduce_forms(spmd, n, grid, block, off):
+    """The sizes at which a reduction changes form, at every alignment; the
+    elements beside the partials stay."""
+    import torch
+
+    say("reduce forms", n, grid, block, off)
+    x = synth.uniform_int32(0x4ED + n, n, -(2**31), 2**31 - 1)
+    seg = 4 * ((n + 4 * grid - 1) // (4 * grid))
+    at = np.minimum(np.arange(grid, dtype=np.int64) * seg, n)
+    run = np.concatenate([[0], np.cumsum(x, dtype=np.int64)])
+    want = (run[np.minimum(at + seg, n)] - run[at]).astype(np.uint32).view(np.int32)
+    xt = torch.empty(n + off, dtype=torch.int32, device="cuda")[off:]
+    xt.copy_(dev(x))
+    p = torch.full((grid + 2,), 77, dtype=torch.int32, device="cuda")
+    out = torch.full((3,), 77, dtype=torch.int32, device="cuda")
+    ws = spmd.ops.workspace(spmd.REDUCE_I32, grid, block, n)
+    for rep in range(2):
+        spmd.launch(spmd.REDUCE_I32, grid, block, 0, [xt, p[1:], out[1:], n, ws])
+        spmd.sync()
+        got = host(p)
+        assert np.array_equal(got[1:-1], want) and got[0] == got[-1] == 77, rep
+        assert host(out).tolist() == [77, int(run[-1:].astype(np.uint32).view(np.int32)[0]), 77], rep
+
+
 # --------------------------------------------------------------------------
 # SCAN
 # --------------------------------------------------------------------------
