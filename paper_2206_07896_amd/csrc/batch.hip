@@ -61,8 +61,7 @@ struct alignas(16) BatchDesc {
     uint32_t aux;      // REDUCE/HIST: elements per block; JACOBI: blocks per row
     uint64_t in, out;
     uint64_t ws;       // run-area scratch of this instance
-    uint32_t vec;      // HIST: in 16-byte aligned
-    uint32_t pad;
+    uint32_t pad[2];
 };
 static_assert(sizeof(BatchDesc) == 64, "descriptor is 64 bytes");
 
@@ -141,7 +140,7 @@ __device__ __forceinline__ void run_logical_block(const BatchDesc& d, uint32_t b
         const uint64_t lo = (uint64_t)b * d.aux;
         const uint64_t hi = lo + d.aux < (uint64_t)d.n ? lo + d.aux : (uint64_t)d.n;
         hist_block<B, HIST_COPIES>(reinterpret_cast<const uint32_t*>(d.in), reinterpret_cast<uint32_t*>(d.out), lo,
-                                   hi, d.vec != 0u, L.h);
+                                   hi, L.h);
     }
 }
 
@@ -198,7 +197,7 @@ __device__ __forceinline__ void run_fused_chunk(const BatchDesc& d, uint32_t q, 
         (void)hi;
     } else {
         hist_block<B, HIST_COPIES>(reinterpret_cast<const uint32_t*>(d.in), reinterpret_cast<uint32_t*>(d.out), lo,
-                                   hi, d.vec != 0u, L.h);
+                                   hi, L.h);
         (void)q;
         (void)err;
     }
@@ -1099,10 +1098,9 @@ int spmd_batch_create_dep(const spmd_batch_item* items, const spmd_schedule* sch
         d.in = (uint64_t)(uintptr_t)it.in;
         d.out = (uint64_t)(uintptr_t)it.out;
         d.ws = (uint64_t)(uintptr_t)(b->ws + run);
-        const bool va = ((uintptr_t)it.in % 16) == 0;
         switch (it.kernel_id) {
         case SPMD_REDUCE_I32:
-        case SPMD_HIST256_U32: d.aux = s.block * s.items; d.vec = va; break;
+        case SPMD_HIST256_U32: d.aux = s.block * s.items; break;
         case SPMD_SCAN_I32: break;
         case SPMD_JACOBI5_F32: d.aux = (uint32_t)cdiv(it.n, 64); break;
         }
@@ -1119,7 +1117,7 @@ int spmd_batch_create_dep(const spmd_batch_item* items, const spmd_schedule* sch
         }
         each += each_scratch(it, blocks[i]);
         b->total_blocks += blocks[i];
-        b->each_launches += it.kernel_id == SPMD_HIST256_U32 ? 2u : 1u;
+        b->each_launches += it.kernel_id == SPMD_HIST256_U32 ? hist_launches(it.n) : 1u;
     }
     std::vector<uint32_t> held(nseg, 0);  // instances per segment
     for (int i = 0; i < n; ++i) {

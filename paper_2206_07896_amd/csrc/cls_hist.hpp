@@ -22,7 +22,8 @@
 //     keys; under heavy skew the longest chain of same-address atomics
 //     collapses to one.
 // The loads of the next eight keys are issued before the current ones are
-// counted, so twice the bytes are in flight.  Counts are exact, so none of
+// counted, so twice the bytes are in flight, 16 bytes per lane at any
+// alignment.  Counts are exact, so none of
 // this changes the result.
 #pragma once
 #include "common.hpp"
@@ -39,9 +40,10 @@ struct HistLds {
     uint32_t s[COPIES * HIST_STRIDE];
 };
 
-template <int B, int COPIES>
+// ALONE: no other block counts, and the bins are written, not added to.
+template <int B, int COPIES, bool ALONE = false>
 __device__ __forceinline__ void hist_block(const uint32_t* __restrict__ keys, uint32_t* hist, uint64_t lo,
-                                           uint64_t hi, bool vec, HistLds<COPIES>& L) {
+                                           uint64_t hi, HistLds<COPIES>& L) {
     const uint32_t t = threadIdx.x;
     for (uint32_t i = t; i < COPIES * HIST_STRIDE; i += B) L.s[i] = 0u;
     __syncthreads();
@@ -74,38 +76,35 @@ __device__ __forceinline__ void hist_block(const uint32_t* __restrict__ keys, ui
         }
     };
     if (lo < hi) {
-        if (vec) {
-            const u32x4* kv = reinterpret_cast<const u32x4*>(keys + lo);
-            const uint64_t nv = (hi - lo) >> 2;
-            uint64_t k = t;
-            if (k + B < nv) {
-                u32x4 a = __builtin_nontemporal_load(kv + k);
-                u32x4 b = __builtin_nontemporal_load(kv + k + B);
-                for (; k + 3 * B < nv; k += 2 * B) {
-                    const u32x4 c = __builtin_nontemporal_load(kv + k + 2 * B);
-                    const u32x4 d = __builtin_nontemporal_load(kv + k + 3 * B);
-                    count8(a, b);
-                    a = c;
-                    b = d;
-                }
+        const u32x4_a4* kv = reinterpret_cast<const u32x4_a4*>(keys + lo);
+        const uint64_t nv = (hi - lo) >> 2;
+        uint64_t k = t;
+        if (k + B < nv) {
+            u32x4 a = __builtin_nontemporal_load(kv + k);
+            u32x4 b = __builtin_nontemporal_load(kv + k + B);
+            for (; k + 3 * B < nv; k += 2 * B) {
+                const u32x4 c = __builtin_nontemporal_load(kv + k + 2 * B);
+                const u32x4 d = __builtin_nontemporal_load(kv + k + 3 * B);
                 count8(a, b);
-                k += 2 * B;
+                a = c;
+                b = d;
             }
-            for (; k < nv; k += B) {
-                const u32x4 a = __builtin_nontemporal_load(kv + k);
-                plain(a.x); plain(a.y); plain(a.z); plain(a.w);
-            }
-            for (uint64_t j = lo + (nv << 2) + t; j < hi; j += B) plain(keys[j]);
-        } else {
-            for (uint64_t j = lo + t; j < hi; j += B) plain(keys[j]);
+            count8(a, b);
+            k += 2 * B;
         }
+        for (; k < nv; k += B) {
+            const u32x4 a = __builtin_nontemporal_load(kv + k);
+            plain(a.x); plain(a.y); plain(a.z); plain(a.w);
+        }
+        for (uint64_t j = lo + (nv << 2) + t; j < hi; j += B) plain(keys[j]);
     }
     __syncthreads();
     for (uint32_t bin = t; bin < 256u; bin += B) {
         uint32_t c = 0;
 #pragma unroll
         for (int r = 0; r < COPIES; ++r) c += L.s[r * HIST_STRIDE + bin];
-        if (c) __hip_atomic_fetch_add(hist + bin, c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (ALONE) hist[bin] = c;
+        else if (c) __hip_atomic_fetch_add(hist + bin, c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 

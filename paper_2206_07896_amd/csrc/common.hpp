@@ -132,6 +132,9 @@ int launch_jacobi5t_f32(const LaunchCtx& c);
 int jacobi_tb_enqueue(const float* u, float* v, uint32_t nx, uint32_t ny, uint32_t sweeps, size_t dyn_shmem,
                       const DevInfo* dev, hipStream_t stream);
 
+// Kernels of a histogram launch of n keys (k_hist.hip).
+uint32_t hist_launches(uint32_t n);
+
 size_t ws_reduce_i32(spmd_dim3 grid, spmd_dim3 block, uint64_t n);
 
 }  // namespace spmd

@@ -112,6 +112,28 @@ def test_reduce_wrapping_and_unaligned(spmd):
         assert np.array_equal(host(p), want_p), grid
 
 
+@pytest.mark.parametrize("off", [0, 1, 3])
+@pytest.mark.parametrize("n", [1, 3, 8191, 8192, 8193, (1 << 17) - 1, 1 << 17, (1 << 18) + 2, (1 << 21) - 3, (1 << 21) + 1,
+                               (1 << 23) + 5, (1 << 24) + 7])
+def test_hist_forms(spmd, n, off):
+    """The sizes at which a histogram takes another number of blocks, at every
+    alignment, launched in any shape and with dynamic shared memory (as
+    launched); the elements beside the bins stay."""
+    import torch
+
+    say("hist forms", n, off)
+    x = synth.uniform_int32(0x415 + n, n, -(2**31), 2**31 - 1) >> (n % 5)
+    want = np.bincount(x & 255, minlength=256).astype(np.int32)
+    xt = torch.empty(n + off, dtype=torch.int32, device="cuda")[off:]
+    xt.copy_(dev(x))
+    h = torch.full((258,), 77, dtype=torch.int32, device="cuda")
+    for grid, block, dyn in ((1, 64, 0), (700, 256, 0), (64, 512, 1024)):
+        spmd.launch(spmd.HIST256_U32, grid, block, dyn, [xt, h[1:], n])
+        spmd.sync()
+        got = host(h)
+        assert np.array_equal(got[1:-1], want) and got[0] == got[-1] == 77, (grid, block, dyn)
+
+
 @pytest.mark.parametrize("off", [0, 1, 2])
 @pytest.mark.parametrize("n,grid,block", [
     # a wave per logical block, one or two at a time: segments of nothing to a
