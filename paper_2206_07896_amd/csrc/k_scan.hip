@@ -45,16 +45,26 @@ __global__ __launch_bounds__(B) void scan_i32_kernel(const int32_t* __restrict__
     __syncthreads();
     uint32_t tile = s_tile;
     const uint32_t tag = s_tag;  // every draw of a launch carries its epoch
+    auto draw_next = [&]() {
+        uint32_t unused;
+        s_next = scan_draw(ticket, ntiles, &unused);
+    };
+    // No barrier between tiles: s_next is written before the tile's second
+    // barrier, and thread 0 writes it, L.excl and L.warp again only after
+    // the next tile's first barrier, which every thread reaches after
+    // its last read of them.
+    // The full tiles have a loop of their own: with the last tile's form in it
+    // 2^26 elements took 0.3 us more.
+    if constexpr (I >= 4) {
+        const uint32_t nfull = n / (uint32_t)(B * I);
+        while (tile < nfull) {
+            scan_tile_rows<B, I>(x, y, (uint64_t)tile * (B * I), tile, status, tag, err, L, draw_next);
+            tile = s_next;
+        }
+    }
     while (tile < ntiles) {
-        auto draw_next = [&]() {
-            uint32_t unused;
-            s_next = scan_draw(ticket, ntiles, &unused);
-        };
-        scan_tile<B, I>(x, y, n, tile, status, tag, err, L, draw_next);
-        // No barrier here: s_next is written before the tile's second
-        // barrier, and thread 0 writes it, L.excl and L.warp again only after
-        // the next tile's first barrier, which every thread reaches after
-        // its last read of them.
+        if constexpr (I >= 4) scan_tile_end<B, I>(x, y, n, tile, status, tag, err, L, draw_next);
+        else scan_tile_items<B, I>(x, y, n, tile, status, tag, err, L, draw_next);
         tile = s_next;
     }
 }
