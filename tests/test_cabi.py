@@ -467,3 +467,29 @@ def test_native_marshalling_equals_ctypes(spmd, grid, block, args):
         g, b = spmd._dim3(grid), spmd._dim3(block)
         record(spmd.REDUCE_I32, g, b, 1024, arr, 77)
         assert seen[0] == seen[1]
+
+
+@pytest.mark.parametrize("make", [iter, tuple, lambda a: (v for v in a), lambda a: map(int, a), dict.fromkeys])
+def test_launch_takes_any_iterable_of_arguments(spmd, make):
+    """launch() marshals what list() makes of `args`, an iterator's items
+    among them, and refuses a wrong number of them with the library's error."""
+    from paper_2206_07896_amd import _launch
+
+    seen = []
+    proto = ctypes.CFUNCTYPE(ctypes.c_int, ctypes.c_int, spmd.Dim3, spmd.Dim3, ctypes.c_size_t,
+                             ctypes.POINTER(ctypes.c_void_p), ctypes.c_void_p)
+
+    def record(kid, g, b, shm, argv, stream):
+        seen.append([ctypes.c_uint32.from_address(argv[i]).value for i in range(5)])
+        return 0
+
+    fake = proto(record)
+    real = [ctypes.cast(f, ctypes.c_void_p).value for f in (spmd._lib.spmd_launch, spmd._lib.spmd_kernel_signature)]
+    _launch.bind(ctypes.cast(fake, ctypes.c_void_p).value, real[1])
+    try:
+        spmd.launch(spmd.REDUCE_I32, 4, 64, 0, make([11, 22, 33, 44, 55]), 77)
+    finally:
+        _launch.bind(*real)
+    assert seen == [[11, 22, 33, 44, 55]]
+    with pytest.raises(spmd.SpmdError):
+        spmd.launch(spmd.REDUCE_I32, 4, 64, 0, make([11, 22, 33]), 77)
