@@ -44,11 +44,17 @@ enum class GemmForm { SPLIT32, SPLIT64, DMA64, DMA128, DMA256 };
 struct GemmCost {
     GemmForm form;
     uint32_t tile, cost;
+    size_t lds;  // of a block
 };
-constexpr GemmCost GEMM_ALIGNED[] = {
-    {GemmForm::DMA256, 256, 2620}, {GemmForm::DMA128, 128, 690}, {GemmForm::DMA64, 64, 194}, {GemmForm::SPLIT32, 32, 75}};
-constexpr GemmCost GEMM_ANY[] = {
-    {GemmForm::DMA256, 256, 2890}, {GemmForm::DMA128, 128, 770}, {GemmForm::SPLIT64, 64, 224}, {GemmForm::SPLIT32, 32, 80}};
+constexpr size_t dma_lds(size_t tile, size_t stages) { return 8 * tile * GEMM_DMA_KT * stages + 16 * (4 - stages); }
+constexpr GemmCost GEMM_ALIGNED[] = {{GemmForm::DMA256, 256, 2620, dma_lds(256, 3)},
+                                     {GemmForm::DMA128, 128, 690, dma_lds(128, 4)},
+                                     {GemmForm::DMA64, 64, 194, dma_lds(64, 4)},
+                                     {GemmForm::SPLIT32, 32, 75, 0}};
+constexpr GemmCost GEMM_ANY[] = {{GemmForm::DMA256, 256, 2890, dma_lds(256, 3)},
+                                 {GemmForm::DMA128, 128, 770, dma_lds(128, 4)},
+                                 {GemmForm::SPLIT64, 64, 224, sizeof(GemmKsplitLds<2, 4>)},
+                                 {GemmForm::SPLIT32, 32, 80, 0}};
 
 uint64_t tiles_of(uint32_t M, uint32_t N, uint32_t t) {
     return (((uint64_t)M + t - 1) / t) * (((uint64_t)N + t - 1) / t);
@@ -59,16 +65,18 @@ uint64_t tiles_of(uint32_t M, uint32_t N, uint32_t t) {
 // over the CUs) x (time of a tile).  1000 x 901 x 1111 at the 128 x 128 tiles of
 // its launch kept 64 CUs busy for 174 us (64 x 64 split: 25.4 us); 4096^3 at 64 x 64
 // tiles took 1059 us (256 x 256: 958 us).  Ties go to the larger tile.  Forms
-// whose offsets (32 bits) or grid (32 bits of threads) a shape exceeds are left
-// out; the 32 x 32 split form has a 64-bit build and strides over its tiles.
-GemmForm gemm_form(uint32_t M, uint32_t N, uint32_t K, bool vec, int num_cus) {
+// whose offsets (32 bits) or grid (32 bits of threads) a shape exceeds, or whose
+// LDS is more than the launch's dynamic shared memory leaves (`room`), are left
+// out; the 32 x 32 split form has a 64-bit build, strides over its tiles and
+// takes four waves where eight don't fit.
+GemmForm gemm_form(uint32_t M, uint32_t N, uint32_t K, bool vec, int num_cus, size_t room) {
     GemmForm best = GemmForm::SPLIT32;
     uint64_t least = ~0ull;
     for (const GemmCost& f : vec ? GEMM_ALIGNED : GEMM_ANY) {
         const uint64_t tiles = tiles_of(M, N, f.tile);
         if (f.form != GemmForm::SPLIT32) {
             if (4ull * f.tile * K >= (1ull << 31) || 4ull * GEMM_DMA_KT * N >= (1ull << 31)) continue;
-            if (tiles >= (1ull << 24)) continue;
+            if (tiles >= (1ull << 24) || f.lds > room) continue;
         }
         const uint64_t c = (tiles + num_cus - 1) / num_cus * f.cost;
         if (c < least) {
@@ -90,21 +98,28 @@ int launch_gemm_f32(const LaunchCtx& c) {
     auto N = arg<uint32_t>(c.args, 4);
     auto K = arg<uint32_t>(c.args, 5);
     if (!A || !B || !C || M == 0 || N == 0 || K == 0) return SPMD_ERR_ARGS;
-    bool covered = false;  // by tiles of 64, 128 or 256
-    for (int t : {64, 128, 256}) covered = covered || ((uint64_t)c.grid.x * t >= N && (uint64_t)c.grid.y * t >= M);
-    if (!covered) return SPMD_ERR_INVALID_DIM;
+    uint32_t T = 0;  // the launch's tile
+    for (uint32_t t : {256u, 128u, 64u})
+        if ((uint64_t)c.grid.x * t >= N && (uint64_t)c.grid.y * t >= M) T = t;
+    if (!T) return SPMD_ERR_INVALID_DIM;
     const bool vec = aligned(A, 16) && K % 4 == 0 && aligned(B, 16) && N % 4 == 0;
+    // What the launch reserves has to fit beside its own tile's stages: four of
+    // 16 deep (three at 256), rows off 16 bytes two, each row padded by 4 floats.
+    const bool dma_rows = vec && (uint64_t)T * K < (1ull << 31) && (uint64_t)GEMM_DMA_KT * N < (1ull << 31);
+    const size_t own = dma_rows ? dma_lds(T, T == 256 ? 3 : 4) : 16 * GEMM_DMA_KT * ((size_t)T + 4);
+    if (own + c.dyn_shmem > c.dev->max_shmem_per_block) return SPMD_ERR_SHMEM;
+    const size_t dyn = c.dyn_shmem, room = c.dev->max_shmem_per_block - dyn;
     const hipStream_t s = c.stream;
-    // The class declares no dynamic shared memory and its kernels use none.
     auto dma = [&](auto kernel, uint32_t t) {
-        dispatch(kernel, dim3((uint32_t)tiles_of(M, N, t)), dim3(256), 0, s, A, B, C, M, N, K, (N + t - 1) / t);
+        dispatch(kernel, dim3((uint32_t)tiles_of(M, N, t)), dim3(256), (uint32_t)dyn, s, A, B, C, M, N, K,
+                 (N + t - 1) / t);
     };
     auto split = [&](auto kernel, uint32_t t, uint32_t threads) {
         const uint64_t tiles = tiles_of(M, N, t);
-        dispatch(kernel, dim3((uint32_t)(tiles < (1u << 22) ? tiles : (1u << 22))), dim3(threads), 0, s, A, B, C, M, N,
-                 K, (uint32_t)(((uint64_t)N + t - 1) / t), (uint32_t)tiles);
+        dispatch(kernel, dim3((uint32_t)(tiles < (1u << 22) ? tiles : (1u << 22))), dim3(threads), (uint32_t)dyn, s, A,
+                 B, C, M, N, K, (uint32_t)(((uint64_t)N + t - 1) / t), (uint32_t)tiles);
     };
-    switch (gemm_form(M, N, K, vec, c.dev->num_cus)) {
+    switch (gemm_form(M, N, K, vec, c.dev->num_cus, room)) {
     case GemmForm::DMA256:
         if (vec) dma(gemm_f32_dma_kernel<256, 3, 4>, 256);
         else dma(gemm_f32_dma_kernel<256, 3, 1>, 256);
@@ -116,7 +131,10 @@ int launch_gemm_f32(const LaunchCtx& c) {
     case GemmForm::DMA64: dma(gemm_f32_dma_kernel<64, 4, 4>, 64); break;
     case GemmForm::SPLIT64: split(gemm_f32_ksplit_kernel<2, 4, 4, uint32_t>, 64, 256); break;
     case GemmForm::SPLIT32:
-        if (4ull * 32 * K < (1ull << 31) && 4ull * 8 * N < (1ull << 31))
+        static_assert(sizeof(GemmKsplitLds<1, 4>) <= 16 * GEMM_DMA_KT * (64 + 4), "fits wherever the least tile does");
+        if (sizeof(GemmKsplitLds<1, 8>) > room)
+            split(gemm_f32_ksplit_kernel<1, 4, 2, uint64_t>, 32, 256);
+        else if (4ull * 32 * K < (1ull << 31) && 4ull * 8 * N < (1ull << 31))
             split(gemm_f32_ksplit_kernel<1, 8, 2, uint32_t>, 32, 512);
         else
             split(gemm_f32_ksplit_kernel<1, 8, 2, uint64_t>, 32, 512);

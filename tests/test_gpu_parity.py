@@ -600,6 +600,34 @@ def test_gemm_forms(spmd, M, N, K, shift):
     assert np.all(np.abs(C - c64) <= bound + 1e-30)
 
 
+@pytest.mark.parametrize("M,N,K,tile,own", [
+    (300, 260, 36, 64, 32768), (300, 260, 36, 128, 65536), (300, 260, 36, 256, 98304 + 16),  # 16-byte rows
+    (301, 259, 37, 64, 17408), (301, 259, 37, 128, 33792), (301, 259, 37, 256, 66560),       # other rows
+    (2040, 2044, 20, 64, 32768), (2045, 2047, 21, 64, 17408), (4090, 4095, 19, 256, 66560)])
+def test_gemm_dynamic_shared_memory(spmd, M, N, K, tile, own):
+    """A launch's dynamic shared memory is reserved: the most that fits beside
+    its tile's stages runs, and 16 bytes more is refused."""
+    import torch
+
+    say("gemm dynamic shared memory", M, N, K, tile)
+    A, B = synth.normal_f32(M + K, M * K).reshape(M, K), synth.normal_f32(N + K, K * N).reshape(K, N)
+    a, b = dev(A), dev(B)
+    c64 = A.astype(np.float64) @ B.astype(np.float64)
+    grid = (-(-N // tile), -(-M // tile))
+    most = 163840 - own
+    for dyn in (0, 1024, 65536, most):
+        if dyn > most:
+            continue
+        C = torch.zeros((M, N), dtype=torch.float32, device="cuda")
+        spmd.launch(spmd.GEMM_F32, grid, 256, dyn, [a, b, C, M, N, K])
+        spmd.sync()
+        assert _gemm_gate(host(C), c64, K), dyn
+    for dyn in (most + 16, 163840):
+        with pytest.raises(spmd.SpmdError) as e:
+            spmd.launch(spmd.GEMM_F32, grid, 256, dyn, [a, b, C, M, N, K])
+        assert e.value.code == -3, dyn  # SPMD_ERR_SHMEM
+
+
 @pytest.mark.parametrize("tile", [64, 128, 256])
 def test_gemm_exact_cases(spmd, tile):
     say("gemm exact", tile)
