@@ -110,7 +110,9 @@ int launch_reduce_i32(const LaunchCtx& c) {
     const uint32_t seg = (uint32_t)seg64;
     uint32_t* err = c.dev->err_word;
     const int cus = c.dev->num_cus;
-    if (const uint32_t J = wave_blocks(seg, G, cus)) {
+    // (four waves' LDS is a few bytes more than a small block's own)
+    const bool room = c.dyn_shmem + sizeof(ReduceLds<256>) <= c.dev->max_shmem_per_block;
+    if (const uint32_t J = room ? wave_blocks(seg, G, cus) : 0) {
         const dim3 g((G + 4 * J - 1) / (4 * J)), b(256);
         if (J == 2) dispatch((reduce_i32_wkernel<2>), g, b, c.dyn_shmem, c.stream, x, partials, out, n, seg, G, ws, err);
         else dispatch((reduce_i32_wkernel<1>), g, b, c.dyn_shmem, c.stream, x, partials, out, n, seg, G, ws, err);

@@ -167,6 +167,25 @@ def test_reduce_forms(spmd, n, grid, block, off):
         assert host(out).tolist() == [77, int(run[-1:].astype(np.uint32).view(np.int32)[0]), 77], rep
 
 
+@pytest.mark.parametrize("block,own", [(64, 12), (128, 16), (256, 24)])
+def test_reduce_with_all_shared_memory(spmd, block, own):
+    """Short segments with as much dynamic shared memory as a block of the
+    launch's own size leaves."""
+    import torch
+
+    say("reduce with all shared memory", block)
+    n, grid = 70001, 300
+    x = synth.uniform_int32(0x5E3 + block, n, -1000, 1000)
+    p = torch.empty(grid, dtype=torch.int32, device="cuda")
+    out = torch.empty(1, dtype=torch.int32, device="cuda")
+    ws = spmd.ops.workspace(spmd.REDUCE_I32, grid, block, n)
+    for dyn in (0, 163840 - own, 4 * block):
+        spmd.launch(spmd.REDUCE_I32, grid, block, dyn, [dev(x), p, out, n, ws])
+        spmd.sync()
+        want_p, want_t = oracle.reduce_i32(x, grid, block)
+        assert int(host(out)[0]) == want_t and np.array_equal(host(p), want_p), dyn
+
+
 # --------------------------------------------------------------------------
 # SCAN
 # --------------------------------------------------------------------------
