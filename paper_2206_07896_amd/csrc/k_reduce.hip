@@ -49,7 +49,11 @@ size_t ws_reduce_i32(spmd_dim3 grid, spmd_dim3, uint64_t) { return REDUCE_WS_HEA
 // Logical blocks per workgroup: the largest K in {1, 2, 4, 8} that still
 // leaves at least one workgroup per resident slot (2 for 4096 blocks of 256:
 // 2048 workgroups of 256 threads fill the device).  At K = 1 the
-// one-block-per-workgroup kernel runs.
+// one-block-per-workgroup kernel runs.  More than 256 threads run fewer than 16
+// blocks to a CU (launch_reduce_i32), so K stays below 16 / (2048 / B) there.
+template <int B>
+constexpr uint32_t REDUCE_K_MAX = B > 256 ? B / 256 : 8;
+
 template <int B>
 static uint32_t reduce_blocks_per_wg(uint32_t G, int num_cus) {
     static const int per_cu = [] {  // one query per block size (one GPU architecture)
@@ -60,7 +64,7 @@ static uint32_t reduce_blocks_per_wg(uint32_t G, int num_cus) {
     if (per_cu < 1) return 1;
     const uint64_t slots = (uint64_t)per_cu * (uint64_t)num_cus;
     uint32_t K = 1;
-    while (K < 8 && (uint64_t)G >= 2ull * K * slots) K *= 2;
+    while (K < REDUCE_K_MAX<B> && (uint64_t)G >= 2ull * K * slots) K *= 2;
     return K;
 }
 
@@ -73,8 +77,14 @@ static void launch_reduce_b(uint32_t G, size_t dyn, hipStream_t s, const int32_t
     switch (K) {
     case 1: dispatch(reduce_i32_kernel<B>, dim3(G), b, dyn, s, x, partials, out, n, seg, ws, err); break;
     case 2: dispatch((reduce_i32_pkernel<B, 2>), dim3((G + 1) / 2), b, dyn, s, x, partials, out, n, seg, G, ws, err); break;
-    case 4: dispatch((reduce_i32_pkernel<B, 4>), dim3((G + 3) / 4), b, dyn, s, x, partials, out, n, seg, G, ws, err); break;
-    default: dispatch((reduce_i32_pkernel<B, 8>), dim3((G + 7) / 8), b, dyn, s, x, partials, out, n, seg, G, ws, err); break;
+    case 4:
+        if constexpr (REDUCE_K_MAX<B> >= 4)
+            dispatch((reduce_i32_pkernel<B, 4>), dim3((G + 3) / 4), b, dyn, s, x, partials, out, n, seg, G, ws, err);
+        break;
+    case 8:
+        if constexpr (REDUCE_K_MAX<B> >= 8)
+            dispatch((reduce_i32_pkernel<B, 8>), dim3((G + 7) / 8), b, dyn, s, x, partials, out, n, seg, G, ws, err);
+        break;
     }
 }
 

@@ -167,6 +167,32 @@ def test_reduce_forms(spmd, n, grid, block, off):
         assert host(out).tolist() == [77, int(run[-1:].astype(np.uint32).view(np.int32)[0]), 77], rep
 
 
+@pytest.mark.parametrize("grid,block", [
+    (1023, 1024), (1024, 1024), (2049, 1024),                # one, two and four blocks to a workgroup
+    (2047, 512), (3001, 512),                                # one and two
+    (8192, 128), (16385, 128), (32768, 128),                 # two, four and eight
+    (16384, 64), (32769, 64), (65536, 64),
+    (4099, 256), (8195, 256), (16389, 256)])
+def test_reduce_long_segments(spmd, grid, block):
+    """Segments too long for a wave each, at every number of logical blocks to
+    a workgroup that a block size can get; the last segments ragged or empty."""
+    import torch
+
+    say("reduce long segments", grid, block)
+    seg = 2052
+    n = grid * seg - 2047
+    x = torch.empty(n, dtype=torch.int32, device="cuda")
+    spmd.batch.synth_uniform_i32(x, grid + block, -1000, 1000)
+    want = torch.zeros(grid * seg, dtype=torch.int64, device="cuda")
+    want[:n] = x
+    want = want.view(grid, seg).sum(1)
+    for rep in range(2):
+        p, out = spmd.ops.reduce_i32(x, grid, block)
+        spmd.sync()
+        assert torch.equal(p.long(), want), rep
+        assert int(host(out)[0]) == int(host(want).sum().astype(np.int32)), rep
+
+
 @pytest.mark.parametrize("block,own", [(64, 12), (128, 16), (256, 24)])
 def test_reduce_with_all_shared_memory(spmd, block, own):
     """Short segments with as much dynamic shared memory as a block of the
