@@ -36,6 +36,14 @@ __device__ __forceinline__ uint32_t xcd_tile(uint32_t id, uint32_t nt) {
     return x < r ? x * (q + 1) + local : r * (q + 1) + (x - r) * q + local;
 }
 
+// Launch grid of gx x gy tiles, which blocks find by their linear id (t % gx,
+// t / gx).  A grid's y ends at 65536, so taller ones are folded into x; the last
+// tiles may then lie below the grid.
+inline dim3 tile_grid(uint64_t gx, uint64_t gy) {
+    const uint64_t fold = (gy + 65535) / 65536;
+    return dim3((uint32_t)(gx * fold), (uint32_t)((gy + fold - 1) / fold));
+}
+
 constexpr int JS_W = 256;  // columns of a strip
 
 typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));  // 16 bytes at any float's address

@@ -8,18 +8,18 @@ constexpr int JS_WAVES = 4;
 // A workgroup of four waves owns 256 columns and 4 R rows.
 template <int R>
 __global__ __launch_bounds__(64 * JS_WAVES) void jacobi5_kernel(const float* __restrict__ u, float* __restrict__ v,
-                                                                uint32_t nx, uint32_t ny) {
+                                                                uint32_t nx, uint32_t ny, uint32_t gx) {
     const uint32_t t = xcd_tile(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int64_t x0 = (int64_t)(t % gridDim.x) * JS_W, y0 = ((int64_t)(t / gridDim.x) * JS_WAVES + w) * R;
+    const int64_t x0 = (int64_t)(t % gx) * JS_W, y0 = ((int64_t)(t / gx) * JS_WAVES + w) * R;
     if (y0 < ny) jacobi_strip<R>(u, v, nx, ny, x0, x0 + JS_W < nx ? x0 + JS_W : nx, y0);
 }
 
 template <int R>
 static void launch(const LaunchCtx& c, const float* u, float* v, uint32_t nx, uint32_t ny) {
-    const dim3 g((uint32_t)(((uint64_t)nx + JS_W - 1) / JS_W),
-                 (uint32_t)(((uint64_t)ny + JS_WAVES * R - 1) / (JS_WAVES * R)));
-    dispatch((jacobi5_kernel<R>), g, dim3(64 * JS_WAVES), c.dyn_shmem, c.stream, u, v, nx, ny);
+    const uint32_t gx = (uint32_t)(((uint64_t)nx + JS_W - 1) / JS_W);
+    const dim3 g = tile_grid(gx, ((uint64_t)ny + JS_WAVES * R - 1) / (JS_WAVES * R));
+    dispatch((jacobi5_kernel<R>), g, dim3(64 * JS_WAVES), c.dyn_shmem, c.stream, u, v, nx, ny, gx);
 }
 
 int launch_jacobi5_f32(const LaunchCtx& c) {

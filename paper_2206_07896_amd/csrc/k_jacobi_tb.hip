@@ -6,11 +6,11 @@ namespace spmd {
 template <int RS, int WV, bool VEC, bool NT>
 __global__ __launch_bounds__(64 * WV, 4) void jacobi5_tb_kernel(const float* __restrict__ u, float* __restrict__ v,
                                                                 uint32_t nx, uint32_t ny, uint32_t sweeps,
-                                                                uint32_t hc) {
+                                                                uint32_t hc, uint32_t gx) {
     __shared__ JacobiTbLds<WV> L;
     const uint32_t nt = gridDim.x * gridDim.y;
     const uint32_t tile = xcd_tile(blockIdx.y * gridDim.x + blockIdx.x, nt);
-    jacobi_tb_block<RS, WV, VEC, NT>(u, v, nx, ny, sweeps, hc, tile % gridDim.x, tile / gridDim.x, L);
+    jacobi_tb_block<RS, WV, VEC, NT>(u, v, nx, ny, sweeps, hc, tile % gx, tile / gx, L);
 }
 
 namespace {
@@ -61,8 +61,9 @@ template <int F, bool VEC>
 void launch_form(const float* u, float* v, uint32_t nx, uint32_t ny, uint32_t sweeps, size_t dyn, hipStream_t st) {
     constexpr int RS = (int)kForms[F].rs, WV = (int)kForms[F].wv;
     const uint32_t hc = halo_cols(sweeps, F == LARGE), w = JT_W - 2 * hc, h = RS * WV - 2 * sweeps;
-    const dim3 g((uint32_t)(((uint64_t)nx + w - 1) / w), (uint32_t)(((uint64_t)ny + h - 1) / h));
-    dispatch((jacobi5_tb_kernel<RS, WV, VEC, F == LARGE>), g, dim3(64 * WV), dyn, st, u, v, nx, ny, sweeps, hc);
+    const uint32_t gx = (uint32_t)(((uint64_t)nx + w - 1) / w);
+    const dim3 g = tile_grid(gx, ((uint64_t)ny + h - 1) / h);
+    dispatch((jacobi5_tb_kernel<RS, WV, VEC, F == LARGE>), g, dim3(64 * WV), dyn, st, u, v, nx, ny, sweeps, hc, gx);
 }
 
 template <bool VEC>

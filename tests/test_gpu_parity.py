@@ -463,6 +463,50 @@ def test_jacobi_strips(spmd, ny, nx):
     assert (got[:4] == -3.0).all() and (got[-4:] == -3.0).all()
 
 
+@pytest.mark.parametrize("ny,nx", [(65536 * 8, 3), (65536 * 8 + 1, 5), ((1 << 20) + 3, 4), (65536 * 16 + 9, 2),
+                                   (65536 * 4 + 1, 129), (65536 * 4 + 64, 300)])  # the last two: one row per wave
+def test_jacobi_grids_of_any_height(spmd, ny, nx):
+    """Grids of more tile rows than a launch grid has blocks along y, launched
+    in blocks of 64 rows."""
+    import torch
+
+    say("jacobi grids of any height", ny, nx)
+    u = synth.uniform_f32(0x7A11 + nx, ny * nx).reshape(ny, nx)
+    out = torch.full((ny * nx + 8,), -3.0, device="cuda")
+    spmd.ops.jacobi5_f32(dev(u), out=out[4:-4].view(ny, nx), block=(64, 4), cells=16)
+    spmd.sync()
+    got = host(out)
+    assert np.array_equal(got[4:-4].reshape(ny, nx), oracle.jacobi5_f32(u, 16, 16))
+    assert (got[:4] == -3.0).all() and (got[-4:] == -3.0).all()
+
+
+def test_fused_sweeps_of_any_height(spmd):
+    """The same for fused sweeps: 24-row regions (whose blocks take less shared
+    memory) of eight sweeps, and a chain's eleven."""
+    import torch
+
+    say("fused sweeps of any height")
+    ny, nx = 65536 * 8 + 13, 8
+    u = synth.uniform_f32(0x7A12, ny * nx).reshape(ny, nx)
+    out = torch.full((ny + 2, nx), -3.0, device="cuda")
+    spmd.launch(spmd.JACOBI5T_F32, spmd.ops.jacobi5t_grid(nx, ny, 8), 256, 140000, [dev(u), out[1:-1], nx, ny, 8])
+    spmd.sync()
+    got = host(out)
+    assert np.array_equal(got[1:-1], oracle.jacobi5_f32_sweeps(u, 8))
+    assert (got[0] == -3.0).all() and (got[-1] == -3.0).all()
+
+    ny, nx, sweeps = 65536 * 74 + 75, 4, 12
+    u = synth.uniform_f32(0x7A13, ny * nx).reshape(ny, nx)
+    bufs = [dev(u), torch.empty((ny, nx), device="cuda")]
+    items = [(spmd.JACOBI5_F32, nx, ny, 256, bufs[t % 2], bufs[(t + 1) % 2]) for t in range(sweeps)]
+    b = spmd.batch.Batch(items, [(256, 8, 8)] * sweeps, deps=[None] + list(range(sweeps - 1)))
+    b.launch()
+    spmd.sync()
+    b.close()
+    for back in (0, 1):
+        assert np.array_equal(host(bufs[(sweeps - back) % 2]), oracle.jacobi5_f32_sweeps(u, sweeps - back)), back
+
+
 def test_jacobi_misaligned_rows(spmd):
     """nx a multiple of 4 but the grid one float into its buffer: rows are
     not 16-byte aligned, so the general-width form runs."""
