@@ -87,7 +87,8 @@ size_t spmd_batch_workspace_size(const spmd_batch_item* items, const spmd_schedu
  * spmd_batch_workspace_size bytes, 256-byte aligned, owned by the caller,
  * alive until spmd_batch_destroy), upload descriptors and chunk tables
  * (synchronously) and return a plan.  `workers_per_cu` persistent
- * workgroups per compute unit and group (0 = as many as fit). */
+ * workgroups per compute unit and group (0 = as many as fit); it bounds the
+ * queues, not the instances with bpf 0. */
 int spmd_batch_create(const spmd_batch_item* items, const spmd_schedule* sched, int n, void* workspace,
                       size_t ws_bytes, uint32_t workers_per_cu, spmd_batch** out);
 
@@ -101,8 +102,9 @@ int spmd_batch_create(const spmd_batch_item* items, const spmd_schedule* sched, 
  * kernel per (class, block size) queue present in it, so a chain such as
  * 100 Jacobi sweeps is one batch, one graph, and no host round trip.  Sweeps
  * that take turns between two buffers, each alone in its level, run several to
- * a kernel (a buffer then holds no sweep in between, only what the last one of
- * the batch to write it leaves there).  An
+ * a kernel of its own, outside the queue (a buffer then holds no sweep in
+ * between, only what the last one of the batch to write it leaves there); not
+ * the queued ones (bpf >= 1) of a plan with a non-zero workers_per_cu.  An
  * instance may read from several earlier instances as long as they all sit
  * below its level (levels are ordered as a whole).  A HIST instance's bins
  * are cleared in stream order just before its own level, so an instance of
@@ -131,8 +133,9 @@ int spmd_batch_graph_launch(spmd_batch* b, void* stream);
  * dispatch of the blocks), issued from a host loop. */
 int spmd_batch_launch_each(spmd_batch* b, void* stream);
 
-/* Total logical blocks and chunks of the plan, and its kernel launches per
- * run of spmd_batch_launch and of spmd_batch_launch_each. */
+/* Total logical blocks of the plan, the chunks its queues hand out in a run
+ * (sweeps that share a kernel have none), and its kernel launches per run of
+ * spmd_batch_launch and of spmd_batch_launch_each. */
 int spmd_batch_stats(const spmd_batch* b, uint64_t* blocks, uint64_t* chunks, uint32_t* persistent_launches,
                      uint32_t* each_launches);
 

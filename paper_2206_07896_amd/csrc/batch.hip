@@ -792,10 +792,11 @@ int plan_layout(const spmd_batch_item* items, const spmd_schedule* sched, const 
 // sweeps of 1024^2: 93 us, 356 with a kernel each; of 8192^2, 1490 and 10540.
 constexpr uint32_t JACOBI_FUSE_MAX = 11;
 
-void fuse_chains(const spmd_batch_item* items, std::vector<BatchSegment>& seg) {
+// A queue's workers may be capped (workers_per_cu): its sweeps then stay in it.
+void fuse_chains(const spmd_batch_item* items, std::vector<BatchSegment>& seg, bool capped) {
     const size_t nseg = seg.size();
     auto alone = [&](size_t k) {  // its level's only segment, one stencil instance in it
-        return seg[k].only >= 0 && items[seg[k].only].kernel_id == SPMD_JACOBI5_F32 && items[seg[k].only].n >= 4 &&
+        return seg[k].only >= 0 && (seg[k].direct >= 0 || !capped) && items[seg[k].only].kernel_id == SPMD_JACOBI5_F32 && items[seg[k].only].n >= 4 &&
                (k == 0 || seg[k - 1].level != seg[k].level) && (k + 1 == nseg || seg[k + 1].level != seg[k].level);
     };
     for (size_t lo = 0; lo < nseg;) {
@@ -1124,10 +1125,12 @@ int spmd_batch_create_dep(const spmd_batch_item* items, const spmd_schedule* sch
         BatchSegment& g = b->seg[L.seg_of[i]];
         g.only = held[L.seg_of[i]]++ ? -1 : i;
     }
-    fuse_chains(items, b->seg);
+    fuse_chains(items, b->seg, workers_per_cu != 0);
     for (size_t k = 0; k < nseg; k += b->seg[k].fused ? b->seg[k].fused : 1) {
         ++b->run_launches;
-        if (!b->seg[k].fused && b->seg[k].direct < 0) b->queued = true;
+        if (b->seg[k].fused) continue;  // nobody fetches these levels' chunks
+        b->total_chunks += b->seg[k].chunks;
+        if (b->seg[k].direct < 0) b->queued = true;
     }
     b->run_launches += b->queued ? 1 : 0;
     std::stable_sort(hist_lv.begin(), hist_lv.end(),
@@ -1155,7 +1158,6 @@ int spmd_batch_create_dep(const spmd_batch_item* items, const spmd_schedule* sch
     for (int i = 0; i < n; ++i) seg_elems[L.seg_of[i]] += items[i].n;
     for (size_t k = 0; k < nseg; ++k) {
         BatchSegment& g = b->seg[k];
-        b->total_chunks += g.chunks;
         if (g.direct >= 0) continue;
         uint32_t pool = 0;
         const int cls = CLS_ID[g.group / NSIZES];

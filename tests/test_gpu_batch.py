@@ -493,6 +493,32 @@ def test_stencil_chains_share_kernels(spmd, nx, ny):
             assert got[0] == -2.0 and got[-1] == -2.0
 
 
+@pytest.mark.parametrize("wpc", [0, 1, 3])
+@pytest.mark.parametrize("bpf", [0, 1, 8])
+def test_stencil_chains_under_a_worker_cap(spmd, wpc, bpf):
+    """A cap on the workers holds for queued chains: their sweeps stay in the
+    queue, whose chunks the statistics count.  Without one, and for sweeps that
+    run as their own grids, they share kernels and have no chunks."""
+    import torch
+
+    nx, ny, sweeps = 260, 515, 13
+    say("stencil chain under a worker cap", wpc, bpf)
+    u = synth.uniform_f32(0xC4A3, ny * nx).reshape(ny, nx)
+    bufs = [dev(u), torch.empty((ny, nx), device="cuda")]
+    items = [(spmd.JACOBI5_F32, nx, ny, 256, bufs[t % 2], bufs[(t + 1) % 2]) for t in range(sweeps)]
+    b = spmd.batch.Batch(items, [(256, 4, bpf)] * sweeps, workers_per_cu=wpc, deps=[None] + list(range(sweeps - 1)))
+    st = b.stats()
+    per = -(-(-(-nx // 64) * -(-ny // 16)) // bpf) if bpf else 0  # chunks of a sweep
+    shared = wpc == 0 or bpf == 0  # 12 sweeps as 7 + 5, and the last
+    assert st["chunks"] == per * (1 if shared else sweeps)
+    assert st["persistent_launches"] == (3 if shared else sweeps) + (1 if bpf else 0)
+    b.launch()
+    spmd.sync()
+    b.close()
+    for back in (0, 1):
+        assert np.array_equal(host(bufs[(sweeps - back) % 2]), oracle.jacobi5_f32_sweeps(u, sweeps - back)), back
+
+
 @pytest.mark.parametrize("count,log2n", [(1, 10), (3, 10), (5, 12), (30, 10), (30, 21)])
 def test_grids_side_by_side(spmd, count, log2n):
     """Independent instances that run as their own grids: in a row, on a few
