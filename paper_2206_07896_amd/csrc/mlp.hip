@@ -938,7 +938,7 @@ int choose_impl(const float* params, uint32_t k_models, const float* norm, const
     if (!m) return SPMD_OK;
     const uint32_t grid = m < CH_MAX_BLOCKS ? m : CH_MAX_BLOCKS;
     // groups of one size, as few as fit the 160 KB LDS (4 models of 256
-    // candidates still take 22 launches at a time)
+    // candidates still take 21 launches at a time)
     const uint32_t share = (m + grid - 1) / grid;
     uint32_t fit = CH_GROUP_MAX;
     while (choose_layout(k_models, c, fit).total > 163840) --fit;

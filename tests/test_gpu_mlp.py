@@ -410,3 +410,69 @@ def test_choose_is_the_least_forward_prediction(L, m, c, k):
     assert np.array_equal(best[some], np.argmin(mean, axis=1)[some].astype(np.uint32))
     assert np.array_equal(pred[some], mean.min(axis=1)[some])
     assert np.all(best[~some] == 0xFFFFFFFF)
+
+
+def _choose_batch(L, params, norm, feats, cands, valid, chunks, slack):
+    import torch
+
+    m, c = valid.shape
+    dp, dn, df, dc = cuda(np.concatenate(params)), cuda(norm), cuda(feats), cuda(cands)
+    dv, dk = cuda(valid, np.uint8), cuda(chunks, np.int32)
+    best = torch.empty(m, dtype=torch.int32, device="cuda")
+    pred, sd = (torch.empty(m, dtype=torch.float32, device="cuda") for _ in range(2))
+    ok(L._lib.spmd_mlp_choose_batch(dp.data_ptr(), len(params), dn.data_ptr(), df.data_ptr(), m, dc.data_ptr(), c,
+                                    dv.data_ptr(), dk.data_ptr(), slack, best.data_ptr(), pred.data_ptr(),
+                                    sd.data_ptr(), None), "spmd_mlp_choose_batch")
+    torch.cuda.synchronize()
+    return best.cpu().numpy().view(np.uint32), pred.cpu().numpy()
+
+
+# a block's launches, and the most that one group of them holds: 24 and 21, 40
+# and 31, 47 and 44, 91 and 64, 160 and 64, 26 and 24; other blocks have one less
+@pytest.mark.parametrize("m,c,k", [(6000, 256, 4), (10000, 144, 4), (11900, 144, 3), (23111, 5, 1), (40900, 7, 4),
+                                   (6401, 215, 4)])
+def test_choose_in_several_groups(L, m, c, k):
+    """Blocks that take their launches in more than one group, the last one
+    shorter: the least forward prediction's bits, and the batch-aware choice's
+    from the same predictions."""
+    import torch
+
+    say("mlp choose in several groups", m, c, k)
+    rng = np.random.default_rng(11 * m + c)
+    feats = (rng.standard_normal((m, 9)) * 2.0).astype(np.float32)
+    cands = (rng.standard_normal((c, 3)) * 2.0).astype(np.float32)
+    valid = rng.random((m, c)) < 0.6
+    valid[::97] = False
+    params = [omlp.init_params(90 + q).astype(np.float32) for q in range(k)]
+    norm = np.concatenate([rng.standard_normal(12) * 0.1, 0.5 + rng.random(12)]).astype(np.float32)
+    dn = cuda(norm)
+    dx = torch.cat([cuda(feats).repeat_interleave(c, 0), cuda(cands).repeat(m, 1)], 1).contiguous()
+    s = np.zeros(m * c, np.float32)
+    for q in params:
+        y, _, _ = _fwd(L, cuda(q), dn, dx, store=False)
+        s = s + y.cpu().numpy()
+    mean = np.where(valid, (s / np.float32(k)).reshape(m, c), np.float32(np.inf))
+    some = valid.any(axis=1)
+    at = np.arange(m)
+
+    best, pred, _ = _choose(L, params, norm, feats, cands, valid)
+    least = np.argmin(mean, axis=1)
+    assert np.array_equal(best[some], least[some].astype(np.uint32))
+    assert np.array_equal(pred[some], mean[at, least][some])
+    assert np.all(best[~some] == 0xFFFFFFFF)
+
+    chunks = rng.integers(1, 9, (m, c))
+    slack = np.float32(0.3)
+    best, pred = _choose_batch(L, params, norm, feats, cands, valid, chunks, float(slack))
+    # nearness decided in doubles; a mean within a rounding of the line may go either way
+    line = mean.min(axis=1).astype(np.float64) + np.log1p(np.float64(slack))
+    off = np.where(valid, mean, np.float32(1e9)).astype(np.float64) - np.where(some, line, 0.0)[:, None]
+    edge = np.abs(off).min(axis=1) < 1e-5
+    key = np.where(valid & (mean <= line[:, None]), chunks, 99).astype(np.float64)
+    tied = np.where(key == key.min(axis=1)[:, None], mean, np.float32(np.inf))
+    pick = np.argmin(tied, axis=1)
+    sure = some & ~edge
+    assert sure.sum() > 0.9 * some.sum()
+    assert np.array_equal(best[sure], pick[sure].astype(np.uint32))
+    assert np.array_equal(pred[sure], mean[at, pick][sure])
+    assert np.all(best[~some] == 0xFFFFFFFF)
