@@ -493,6 +493,35 @@ def test_stencil_chains_share_kernels(spmd, nx, ny):
             assert got[0] == -2.0 and got[-1] == -2.0
 
 
+@pytest.mark.parametrize("nx,ny,sweeps,kernels,off", [
+    # 16-byte rows: 9 sweeps and one; 11 and one; 7, 5 and one; nine times 11 and one
+    *[(nx, ny, sweeps, kernels, 0) for nx, ny in ((4, 9), (64, 64), (232, 3), (236, 149), (512, 1300), (1024, 1024), (2044, 2048))
+      for sweeps, kernels in ((10, 2), (12, 2), (13, 3), (100, 10))],
+    # 96-row regions of 11 sweeps: enough tiles for three to a CU, rows on and off 16 bytes
+    (8192, 1640, 23, 3, 0), (8192, 1640, 23, 3, 1), (8189, 1700, 23, 3, 0), (8188, 1628, 34, 4, 2)])
+def test_stencil_chains_on_whole_rows(spmd, nx, ny, sweeps, kernels, off):
+    """As above on 16-byte-aligned buffers and on large grids, in as many
+    kernels as the chain is cut into."""
+    import torch
+
+    say("stencil chains on whole rows", nx, ny, sweeps, off)
+    n = nx * ny
+    u = synth.uniform_f32(0xC4A4 + nx, n).reshape(ny, nx)
+    store = [torch.full((n + 8,), -2.0, device="cuda") for _ in range(2)]
+    bufs = [s[4 + off:4 + off + n] for s in store]
+    bufs[0].copy_(torch.from_numpy(u.ravel()))
+    items = [(spmd.JACOBI5_F32, nx, ny, 256, bufs[t % 2], bufs[(t + 1) % 2]) for t in range(sweeps)]
+    b = spmd.batch.Batch(items, [(256, 4, 0)] * sweeps, deps=[None] + list(range(sweeps - 1)))
+    assert b.stats()["persistent_launches"] == kernels
+    b.launch()
+    spmd.sync()
+    b.close()
+    for back in (0, 1):
+        got = host(store[(sweeps - back) % 2])
+        assert np.array_equal(got[4 + off:4 + off + n].reshape(ny, nx), oracle.jacobi5_f32_sweeps(u, sweeps - back)), back
+        assert (got[:4 + off] == -2.0).all() and (got[4 + off + n:] == -2.0).all(), back
+
+
 @pytest.mark.parametrize("wpc", [0, 1, 3])
 @pytest.mark.parametrize("bpf", [0, 1, 8])
 def test_stencil_chains_under_a_worker_cap(spmd, wpc, bpf):
