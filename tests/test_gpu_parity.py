@@ -134,6 +134,39 @@ def test_hist_forms(spmd, n, off):
         assert np.array_equal(got[1:-1], want) and got[0] == got[-1] == 77, (grid, block, dyn)
 
 
+@pytest.mark.parametrize("block", [64, 128, 256, 512, 1024])
+@pytest.mark.parametrize("n,grid", [(1, 3), (8191, 2), (100003, 17), ((1 << 18) + 5, 40), ((1 << 20) + 1, 257)])
+def test_shapes_with_dynamic_shared_memory(spmd, n, grid, block):
+    """A launch that reserves shared memory runs in its own blocks: histogram,
+    scan and compaction at every block size, off 16 bytes."""
+    import torch
+
+    say("shapes with dynamic shared memory", n, grid, block)
+    x = synth.uniform_int32(0xD15 + n, n, -1000, 1000)
+    xt = torch.empty(n + 1, dtype=torch.int32, device="cuda")[1:]
+    xt.copy_(dev(x))
+    h = torch.full((258,), 77, dtype=torch.int32, device="cuda")
+    spmd.launch(spmd.HIST256_U32, grid, block, 64, [xt, h[1:], n])
+    spmd.sync()
+    assert np.array_equal(host(h)[1:-1], np.bincount(x & 255, minlength=256)) and host(h)[0] == host(h)[-1] == 77
+    items = 16 if block <= 512 else 8
+    g = spmd.ops.scan_grid(n, block, items)
+    y = torch.full((n + 2,), 77, dtype=torch.int32, device="cuda")
+    ws = spmd.ops.workspace(spmd.SCAN_I32, g, block, n)
+    spmd.launch(spmd.SCAN_I32, g, block, 64, [xt, y[1:-1], n, ws])
+    spmd.sync()
+    assert np.array_equal(host(y)[1:-1], oracle.scan_i32(x, 64, 4)) and host(y)[0] == host(y)[-1] == 77
+    y.fill_(77)
+    c = torch.empty(1, dtype=torch.int32, device="cuda")
+    ws = spmd.ops.workspace(spmd.COMPACT_I32, g, block, n)
+    spmd.launch(spmd.COMPACT_I32, g, block, 64, [xt, y[1:-1], c, n, 5, ws])
+    spmd.sync()
+    want = x[x > 5]
+    assert int(host(c)[0]) == want.size
+    assert np.array_equal(host(y)[1:1 + want.size], want)
+    assert (host(y)[1 + want.size:] == 77).all() and host(y)[0] == 77
+
+
 @pytest.mark.parametrize("off", [0, 1, 2])
 @pytest.mark.parametrize("n,grid,block", [
     # a wave per logical block, one or two at a time: segments of nothing to a
