@@ -74,7 +74,6 @@ __device__ __forceinline__ void gemm_block_dma(const float* __restrict__ A, cons
     constexpr int RPS = 64 / KT;         // A rows per 64-bank span
     constexpr int NI = T * KT / (256 * V);  // loads per wave per operand per slice
     constexpr int LPW = 2 * NI;          // loads per wave per slice
-    constexpr int BCH = T / 4;           // 16-byte chunks per B row
     constexpr int SA = T * KT;           // floats per operand per stage
     static_assert(V == 1 || V == 4, "floats per load");
     static_assert(NS >= 2 && NS <= 4 && LPW * (NS - 2) < 64, "stage count");
@@ -185,6 +184,30 @@ __device__ __forceinline__ void gemm_block_dma(const float* __restrict__ A, cons
     using I1 = std::integral_constant<int, 1>;
     using I2 = std::integral_constant<int, 2>;
     using I3 = std::integral_constant<int, 3>;
+    // The K tail, shorter than a slice, goes through registers, zero outside the
+    // matrices, into stage 0 in the same layouts.  Of 64 x 64 tiles its loads are
+    // issued first: they are few, and K is short (4096 x 4096 x 33: 28.7 us, 30.1
+    // with them last).
+    const int64_t k0 = (int64_t)nk * KT;
+    const bool tail = Ki % KT != 0;
+    using vec = std::conditional_t<V == 4, f32x4, float>;
+    auto tail_a = [&](int p) {
+        const int r = p / KT, k = p % KT;
+        return m0 + r < Mi && k0 + k < Ki ? *reinterpret_cast<const vec*>(A + (m0 + r) * Ki + k0 + k) : vec{};
+    };
+    auto tail_b = [&](int p) {
+        const int k = p / T, col = p % T;
+        return k0 + k < Ki && n0 + col < Ni ? *reinterpret_cast<const vec*>(B + (k0 + k) * Ni + n0 + col) : vec{};
+    };
+    constexpr bool EARLY = T == 64;
+    vec ta[EARLY ? NI : 1], tb[EARLY ? NI : 1];
+    if (EARLY && tail) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            ta[i] = tail_a(V * (tid + 256 * i));
+            tb[i] = tail_b(V * (tid + 256 * i));
+        }
+    }
     if (nk > 0) {
         // Slices 0 .. NS - 2, unconditionally (clamped to slice 0), so every
         // path into the loop has the same loads in flight.
@@ -213,22 +236,12 @@ __device__ __forceinline__ void gemm_block_dma(const float* __restrict__ A, cons
         GEMM_WAIT_VM(0);  // the clamped prologue loads too: nothing lands later
         __syncthreads();  // every wave is done reading the stages
     }
-    if (Ki % KT) {
-        // The K tail through registers, zero outside the matrices, into
-        // stage 0 in the same layouts.
-        const int64_t k0 = (int64_t)nk * KT;
-        using vec = std::conditional_t<V == 4, f32x4, float>;
-        for (int p = V * tid; p < T * KT; p += 256 * V) {
-            const int r = p / KT, k = p % KT;
-            vec v = {};
-            if (m0 + r < Mi && k0 + k < Ki) v = *reinterpret_cast<const vec*>(A + (m0 + r) * Ki + k0 + k);
-            *reinterpret_cast<vec*>(S0 + r * KT + 4 * ((k / 4) ^ ((r / RPS) % CPR)) + k % 4) = v;
-        }
-        for (int p = V * tid; p < KT * T; p += 256 * V) {
-            const int k = p / T, col = p % T;
-            vec v = {};
-            if (k0 + k < Ki && n0 + col < Ni) v = *reinterpret_cast<const vec*>(B + (k0 + k) * Ni + n0 + col);
-            *reinterpret_cast<vec*>(S0 + SA + k * T + (col + ((k & 4) ? 32 : 0)) % T) = v;
+    if (tail) {
+#pragma unroll(EARLY ? NI : 1)
+        for (int i = 0; i < NI; ++i) {
+            const int p = V * (tid + 256 * i), r = p / KT, c = p % KT, k = p / T, col = p % T;
+            *reinterpret_cast<vec*>(S0 + r * KT + 4 * ((c / 4) ^ ((r / RPS) % CPR)) + c % 4) = EARLY ? ta[EARLY ? i : 0] : tail_a(p);
+            *reinterpret_cast<vec*>(S0 + SA + k * T + (col + ((k & 4) ? 32 : 0)) % T) = EARLY ? tb[EARLY ? i : 0] : tail_b(p);
         }
         __syncthreads();
         compute(S0);

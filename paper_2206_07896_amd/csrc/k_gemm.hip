@@ -1,4 +1,6 @@
 // k_gemm.hip -- GEMM_F32 kernels and launcher.
+#include <iterator>
+
 #include "cls_gemm.hpp"
 #include "cls_jacobi.hpp"  // xcd_tile
 
@@ -33,28 +35,37 @@ __global__ __launch_bounds__(64 * W) void gemm_f32_ksplit_kernel(const float* __
 
 namespace {
 
-// The forms, and what one tile takes on a CU per unit of K, in 0.1 ns,
-// measured at shapes that fill the 256 CUs with one or more of them: 4096^3,
-// 2048^3, 3000^3 and 1536^3 with 16-byte rows; 4095^3, 2047 x 2049 x 2047 and
-// 3001 x 2999 x 3001 without; 512 x 512 x 4096 and 1023 x 1025 x 1027 for the
-// 32 x 32 tiles.  The larger the tile, the nearer it runs to the matrix
-// cores' rate, and the more a shape that does not fill a round of tiles
-// leaves idle.
+// The forms, and what one tile takes on a CU, in 0.1 ns: per unit of K, and
+// beside it for its start and the way out of C.  Per K measured at shapes that
+// fill the 256 CUs with one or more tiles: 4096^3, 2048^3, 3000^3 and 1536^3 with
+// 16-byte rows; 4095^3, 2047 x 2049 x 2047 and 3001 x 2999 x 3001 without; 512 x
+// 512 x 4096 and 1023 x 1025 x 1027 for the 32 x 32 tiles.  Beside it fitted to
+// 242 shapes of K from 1 to 512: the larger the tile, the nearer it runs to the
+// matrix cores' rate, the more a shape that does not fill a round of tiles
+// leaves idle, and the longer its C takes with no other block's products beside
+// it (8192 x 8192 x 16: 52 us on 64 x 64 tiles, 57 on 128 x 128, 64 on 256 x 256;
+// 4096 x 4096 x 256 75 on all three).  Without 16-byte rows 64 x 64 tiles by 4-byte
+// loads take short K (2047 x 2049 x 64: 12.2 us, 18.3 split over waves).
 enum class GemmForm { SPLIT32, SPLIT64, DMA64, DMA128, DMA256 };
 struct GemmCost {
     GemmForm form;
-    uint32_t tile, cost;
+    uint32_t tile, per_k, beside;
     size_t lds;  // of a block
 };
 constexpr size_t dma_lds(size_t tile, size_t stages) { return 8 * tile * GEMM_DMA_KT * stages + 16 * (4 - stages); }
-constexpr GemmCost GEMM_ALIGNED[] = {{GemmForm::DMA256, 256, 2620, dma_lds(256, 3)},
-                                     {GemmForm::DMA128, 128, 690, dma_lds(128, 4)},
-                                     {GemmForm::DMA64, 64, 194, dma_lds(64, 4)},
-                                     {GemmForm::SPLIT32, 32, 75, 0}};
-constexpr GemmCost GEMM_ANY[] = {{GemmForm::DMA256, 256, 2890, dma_lds(256, 3)},
-                                 {GemmForm::DMA128, 128, 770, dma_lds(128, 4)},
-                                 {GemmForm::SPLIT64, 64, 224, sizeof(GemmKsplitLds<2, 4>)},
-                                 {GemmForm::SPLIT32, 32, 80, 0}};
+constexpr GemmCost GEMM_ALIGNED[] = {{GemmForm::DMA256, 256, 2620, 160000, dma_lds(256, 3)},
+                                     {GemmForm::DMA128, 128, 690, 30000, dma_lds(128, 4)},
+                                     {GemmForm::DMA64, 64, 194, 4000, dma_lds(64, 4)},
+                                     {GemmForm::SPLIT32, 32, 75, 4000, 0}};
+constexpr GemmCost GEMM_ANY[] = {{GemmForm::DMA256, 256, 2890, 160000, dma_lds(256, 3)},
+                                 {GemmForm::DMA128, 128, 770, 40000, dma_lds(128, 4)},
+                                 {GemmForm::SPLIT64, 64, 224, 6000, sizeof(GemmKsplitLds<2, 4>)},
+                                 {GemmForm::DMA64, 64, 240, 1000, dma_lds(64, 4)},
+                                 {GemmForm::SPLIT32, 32, 80, 1000, 0}};
+// Of 16-byte rows that don't begin on 128-byte lines (N % 32), a 64-column piece
+// ends in two lines that others write too: 10000 x 10000 x 16 94 us on 128 x 128
+// tiles, 112 on 64 x 64.
+constexpr uint32_t GEMM_CUT_LINES = 4000;
 
 uint64_t tiles_of(uint32_t M, uint32_t N, uint32_t t) {
     return (((uint64_t)M + t - 1) / t) * (((uint64_t)N + t - 1) / t);
@@ -72,13 +83,17 @@ uint64_t tiles_of(uint32_t M, uint32_t N, uint32_t t) {
 GemmForm gemm_form(uint32_t M, uint32_t N, uint32_t K, bool vec, int num_cus, size_t room) {
     GemmForm best = GemmForm::SPLIT32;
     uint64_t least = ~0ull;
-    for (const GemmCost& f : vec ? GEMM_ALIGNED : GEMM_ANY) {
+    const GemmCost* const first = vec ? GEMM_ALIGNED : GEMM_ANY;
+    const GemmCost* const last = vec ? std::end(GEMM_ALIGNED) : std::end(GEMM_ANY);
+    for (const GemmCost* p = first; p != last; ++p) {
+        const GemmCost& f = *p;
         const uint64_t tiles = tiles_of(M, N, f.tile);
         if (f.form != GemmForm::SPLIT32) {
             if (4ull * f.tile * K >= (1ull << 31) || 4ull * GEMM_DMA_KT * N >= (1ull << 31)) continue;
             if (tiles >= (1ull << 24) || f.lds > room) continue;
         }
-        const uint64_t c = (tiles + num_cus - 1) / num_cus * f.cost;
+        const uint64_t cut = vec && f.form == GemmForm::DMA64 && N % 32 ? GEMM_CUT_LINES : 0;
+        const uint64_t c = (tiles + num_cus - 1) / num_cus * ((uint64_t)f.per_k * K + f.beside + cut);
         if (c < least) {
             least = c;
             best = f.form;
@@ -128,7 +143,10 @@ int launch_gemm_f32(const LaunchCtx& c) {
         if (vec) dma(gemm_f32_dma_kernel<128, 4, 4>, 128);
         else dma(gemm_f32_dma_kernel<128, 4, 1>, 128);
         break;
-    case GemmForm::DMA64: dma(gemm_f32_dma_kernel<64, 4, 4>, 64); break;
+    case GemmForm::DMA64:
+        if (vec) dma(gemm_f32_dma_kernel<64, 4, 4>, 64);
+        else dma(gemm_f32_dma_kernel<64, 4, 1>, 64);
+        break;
     case GemmForm::SPLIT64: split(gemm_f32_ksplit_kernel<2, 4, 4, uint32_t>, 64, 256); break;
     case GemmForm::SPLIT32:
         static_assert(sizeof(GemmKsplitLds<1, 4>) <= 16 * GEMM_DMA_KT * (64 + 4), "fits wherever the least tile does");

@@ -722,6 +722,19 @@ def test_gemm_forms(spmd, M, N, K, shift):
     assert np.all(np.abs(C - c64) <= bound + 1e-30)
 
 
+@pytest.mark.parametrize("M,N,K,shift", [
+    # staged in LDS, 16-byte rows: 64 x 64 tiles of short and long K, 128 and 256
+    (1020, 1000, 516, 0), (4089, 4096, 116, 0), (1023, 1004, 260, 0), (2041, 2036, 520, 0), (4089, 4096, 520, 0),
+    # other rows: 64 x 64 tiles below one slice, with tails of 1 to 15 and past the main loop
+    (1000, 901, 6, 0), (999, 903, 15, 1), (997, 905, 16, 0), (2046, 2045, 131, 0), (4090, 4095, 33, 3), (1000, 904, 113, 2),
+    # 128, 256, and 64 x 64 split over waves
+    (2045, 2047, 520, 0), (2046, 2045, 527, 1), (4090, 4093, 523, 0), (4093, 4090, 512, 0), (1000, 901, 517, 0), (1001, 1000, 401, 0)])
+def test_gemm_forms_by_length(spmd, M, N, K, shift):
+    """The forms that a shape takes by the length of K, each at edges of its
+    tiles and slices."""
+    test_gemm_forms(spmd, M, N, K, shift)
+
+
 @pytest.mark.parametrize("M,N,K,tile,own", [
     (300, 260, 36, 64, 32768), (300, 260, 36, 128, 65536), (300, 260, 36, 256, 98304 + 16),  # 16-byte rows
     (301, 259, 37, 64, 17408), (301, 259, 37, 128, 33792), (301, 259, 37, 256, 66560),       # other rows
