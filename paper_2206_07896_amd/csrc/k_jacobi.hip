@@ -3,23 +3,37 @@
 
 namespace spmd {
 
-constexpr int JS_WAVES = 4;
-
-// A workgroup of four waves owns 256 columns and 4 R rows.
-template <int R>
-__global__ __launch_bounds__(64 * JS_WAVES) void jacobi5_kernel(const float* __restrict__ u, float* __restrict__ v,
-                                                                uint32_t nx, uint32_t ny, uint32_t gx) {
+// A workgroup of W waves owns 256 columns and R W rows.
+template <int R, int W>
+__global__ __launch_bounds__(64 * W) void jacobi5_kernel(const float* __restrict__ u, float* __restrict__ v,
+                                                         uint32_t nx, uint32_t ny, uint32_t gx) {
     const uint32_t t = xcd_tile(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int64_t x0 = (int64_t)(t % gx) * JS_W, y0 = ((int64_t)(t / gx) * JS_WAVES + w) * R;
+    const int64_t x0 = (int64_t)(t % gx) * JS_W, y0 = ((int64_t)(t / gx) * W + w) * R;
     if (y0 < ny) jacobi_strip<R>(u, v, nx, ny, x0, x0 + JS_W < nx ? x0 + JS_W : nx, y0);
 }
 
-template <int R>
+// The same for grids of up to 64 columns: a lane per column.
+template <int R, int W>
+__global__ __launch_bounds__(64 * W) void jacobi5_narrow_kernel(const float* __restrict__ u, float* __restrict__ v,
+                                                                uint32_t nx, uint32_t ny) {
+    const uint32_t t = xcd_tile(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int64_t y0 = ((int64_t)t * W + w) * R;
+    if (y0 < ny) jacobi_narrow<R>(u, v, nx, ny, 0, nx, y0);
+}
+
+template <int R, int W>
 static void launch(const LaunchCtx& c, const float* u, float* v, uint32_t nx, uint32_t ny) {
     const uint32_t gx = (uint32_t)(((uint64_t)nx + JS_W - 1) / JS_W);
-    const dim3 g = tile_grid(gx, ((uint64_t)ny + JS_WAVES * R - 1) / (JS_WAVES * R));
-    dispatch((jacobi5_kernel<R>), g, dim3(64 * JS_WAVES), c.dyn_shmem, c.stream, u, v, nx, ny, gx);
+    const dim3 g = tile_grid(gx, ((uint64_t)ny + W * R - 1) / (W * R));
+    dispatch((jacobi5_kernel<R, W>), g, dim3(64 * W), c.dyn_shmem, c.stream, u, v, nx, ny, gx);
+}
+
+template <int R, int W>
+static void launch_narrow(const LaunchCtx& c, const float* u, float* v, uint32_t nx, uint32_t ny) {
+    const dim3 g = tile_grid(1, ((uint64_t)ny + W * R - 1) / (W * R));
+    dispatch((jacobi5_narrow_kernel<R, W>), g, dim3(64 * W), c.dyn_shmem, c.stream, u, v, nx, ny);
 }
 
 int launch_jacobi5_f32(const LaunchCtx& c) {
@@ -43,10 +57,21 @@ int launch_jacobi5_f32(const LaunchCtx& c) {
     // The launch's blocks are fetched 256 columns at a time (coarse-grained
     // fetching along x, Section IV-A) and their rows dealt to waves; every cell
     // is computed as in its own block.  One row per wave where input and output
-    // outgrow the 256 MB cache (8190 x 8191: 94 us against 101 with two), two
-    // below (333 x 5000: 4.6 against 5.2; 2001 x 1999 6.6 with either).
-    if ((uint64_t)nx * ny > (1ull << 25)) launch<1>(c, u, v, nx, ny);
-    else launch<2>(c, u, v, nx, ny);
+    // outgrow the 256 MB cache (8190 x 8191: 94 us against 101 with two), eight
+    // waves to a workgroup, which share the rows between them (16384^2 352 us, 378
+    // with four and 388 with sixteen; 8192^2 84.0, 85.0 and 91.7), four where rows
+    // are longer (1500 x 300 000 670 against 712, 20000 x 20004 561 against 571); two
+    // rows and four waves below (333 x 5000: 4.6 against 5.2; 2001 x 1999 6.6 with either).
+    // Tall grids that leave many of a strip's lanes without a column take more
+    // rows: up to 64 columns eight with a lane each (200 000 x 16 15.6 us, 31.1 as
+    // strips of two), up to 160 four (2^18 rows of 65 40.5 against 50.2, of 100
+    // 49.5 against 53.3, of 128 53.5 against 57.2; of 250 99.8 against 92.0 with
+    // one).  Below 2^15 rows they take as long either way.
+    const bool tall = ny >= 1u << 15;
+    if (tall && nx <= 64) launch_narrow<8, 4>(c, u, v, nx, ny);
+    else if (tall && nx <= 160) launch<4, 4>(c, u, v, nx, ny);
+    else if ((uint64_t)nx * ny > (1ull << 25)) nx <= 1u << 14 ? launch<1, 8>(c, u, v, nx, ny) : launch<1, 4>(c, u, v, nx, ny);
+    else launch<2, 4>(c, u, v, nx, ny);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? SPMD_OK : hip_fail(e);
 }

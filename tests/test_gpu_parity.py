@@ -496,6 +496,32 @@ def test_jacobi_strips(spmd, ny, nx):
     assert (got[:4] == -3.0).all() and (got[-4:] == -3.0).all()
 
 
+@pytest.mark.parametrize("ny,nx", [(2051, 16384), (2050, 16385), (1027, 40001), (131075, 257)])
+def test_jacobi_one_row_a_wave(spmd, ny, nx):
+    """Large grids on both sides of the row length at which a workgroup's waves
+    change number."""
+    test_jacobi_strips(spmd, ny, nx)
+
+
+@pytest.mark.parametrize("ny", [32767, 32768, 32771, 65536 * 32 + 33])
+@pytest.mark.parametrize("nx", [1, 2, 3, 4, 31, 63, 64, 65, 128, 159, 160, 161])
+def test_jacobi_tall_grids(spmd, ny, nx):
+    """The rows and columns at which tall grids change form; of up to 31 columns
+    also more rows than a launch grid has blocks along y."""
+    import torch
+
+    if ny > 1 << 20 and nx > 31:
+        ny = 40000 + nx
+    say("jacobi tall grids", ny, nx)
+    u = synth.uniform_f32(0x7A14 + nx, ny * nx).reshape(ny, nx)
+    out = torch.full((ny * nx + 8,), -3.0, device="cuda")
+    spmd.ops.jacobi5_f32(dev(u), out=out[3:-5].view(ny, nx), block=(64, 4), cells=16)
+    spmd.sync()
+    got = host(out)
+    assert np.array_equal(got[3:-5].reshape(ny, nx), oracle.jacobi5_f32(u, 16, 16))
+    assert (got[:3] == -3.0).all() and (got[-5:] == -3.0).all()
+
+
 @pytest.mark.parametrize("ny,nx", [(65536 * 8, 3), (65536 * 8 + 1, 5), ((1 << 20) + 3, 4), (65536 * 16 + 9, 2),
                                    (65536 * 4 + 1, 129), (65536 * 4 + 64, 300)])  # the last two: one row per wave
 def test_jacobi_grids_of_any_height(spmd, ny, nx):
