@@ -649,6 +649,13 @@ def test_jacobi_fused_regions(spmd, ny, nx, sweeps):
     assert (got[0] == -3.0).all() and (got[-1] == -3.0).all()
 
 
+@pytest.mark.parametrize("ny,nx,sweeps", [(1, 200000, 8), (3, 180000, 4), (25, 180000, 7), (383, 40004, 5),
+                                          (384, 40000, 5), (384, 40000, 1), (385, 39996, 8)])
+def test_jacobi_fused_flat_grids(spmd, ny, nx, sweeps):
+    """Grids of fewer rows than four of the highest regions, and just past it."""
+    test_jacobi_fused_regions(spmd, ny, nx, sweeps)
+
+
 def test_jacobi_fused_chain_and_closed_form(spmd):
     """27 sweeps as 8 + 8 + 8 + 3 fused launches against the oracle, and the
     linear field u = i + 2j, a fixed point of the stencil, through 8."""
