@@ -133,7 +133,8 @@ static void launch_b(uint32_t I, uint32_t G, size_t dyn, hipStream_t s, const in
 // 2^26 elements in 256 x 16 tiles take 239 us, 512 x 16 126, 512 x 32 90, 1024 x 32
 // 88.  The fastest at 2^18..2^20, to 2^22 and on: 512 x 16 (2^20 7.9 us; 256 x 16
 // 10.2), 1024 x 16 (2^22 12.8; 256 x 16 31.0) and 1024 x 32 (2^23 17.3; 1024 x 16
-// 19.6, 256 x 16 57.1).
+// 19.6, 256 x 16 57.1).  512 x 64, as many elements, gives way to 1024 x 32 too
+// (2^23 18.6 and 16.5 us, 2^26 100.6 and 87.8, 2^28 370 and 342).
 static uint32_t compact_tile(uint32_t n) {
     return n < (1u << 18) ? 0u : n < (1u << 21) ? 512u * 16 : n < (1u << 23) ? 1024u * 16 : 1024u * 32;
 }
@@ -156,7 +157,7 @@ int launch_compact_i32(const LaunchCtx& c) {
     if (I > 64 || (I == 64 && B > 512)) return SPMD_ERR_INVALID_DIM;
     uint32_t* err = c.dev->err_word;
     const int cus = c.dev->num_cus;
-    if (const uint32_t tile = compact_tile(n); c.dyn_shmem == 0 && (uint64_t)B * I < tile) {
+    if (const uint32_t tile = compact_tile(n); c.dyn_shmem == 0 && ((uint64_t)B * I < tile || (I == 64 && (uint64_t)B * I == tile))) {
         const uint32_t tiles = (uint32_t)(((uint64_t)n + tile - 1) / tile);
         if (tile == 512 * 16) launch_bi<512, 16>(tiles, 0, c.stream, x, y, cnt, n, t, ws, err, cus);
         else if (tile == 1024 * 16) launch_bi<1024, 16>(tiles, 0, c.stream, x, y, cnt, n, t, ws, err, cus);

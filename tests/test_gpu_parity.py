@@ -897,6 +897,28 @@ def test_scan_and_compact_ends(spmd, n, block, items, off):
         assert (got[1 + off + len(want):] == 77).all() and (got[:1 + off] == 77).all(), t
 
 
+@pytest.mark.parametrize("n", [32768 * 255 - 5, (1 << 23) - 1, (1 << 23) + 1, (1 << 24) + 32768])
+@pytest.mark.parametrize("dyn", [0, 64])
+def test_compact_in_512_by_64(spmd, n, dyn):
+    """The largest tile around the size from which another shape of it runs."""
+    import torch
+
+    say("compact in 512 x 64", n, dyn)
+    x = synth.uniform_int32(0xC064 + n, n, -1000, 1000)
+    xt = dev(x)
+    grid = spmd.ops.compact_grid(n, 512, 64)
+    ws = spmd.ops.workspace(spmd.COMPACT_I32, grid, 512, n)
+    c = torch.empty(1, dtype=torch.int32, device="cuda")
+    for t in (-1001, -300, 1000):
+        y = torch.full((n + 1,), 7777, dtype=torch.int32, device="cuda")
+        spmd.launch(spmd.COMPACT_I32, grid, 512, dyn, [xt, y, c, n, t & 0xFFFFFFFF, ws])
+        spmd.sync()
+        want = x[x > t]
+        got = host(y)
+        assert int(host(c)[0]) == want.size and np.array_equal(got[:want.size], want), t
+        assert (got[want.size:] == 7777).all(), t
+
+
 def test_scan_and_compact_on_larger_grids(spmd):
     """Tiles past the end: a grid of more tiles than the elements fill."""
     import torch
