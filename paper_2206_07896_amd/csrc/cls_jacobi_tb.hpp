@@ -162,13 +162,13 @@ __device__ __forceinline__ void jacobi_tb_region(const float* __restrict__ u, fl
 // Tile (bx, by) of the grid cut into tiles of 256 - 2 hc columns and
 // RS * WV - 2 sweeps rows.  nx >= 4, hc is a multiple of 4, sweeps <= hc.  VEC: nx is a
 // multiple of 4 and the rows are 16-byte aligned.  NT: whole-line stores that
-// pass the L2 by (for grids far larger than it).
+// pass the L2 by (for grids far larger than it).  A tile below the grid reads and
+// stores nothing.
 template <int RS, int WV, bool VEC, bool NT>
 __device__ __forceinline__ void jacobi_tb_block(const float* __restrict__ u, float* __restrict__ v, uint32_t nx,
                                                 uint32_t ny, uint32_t sweeps, uint32_t hc, uint32_t bx, uint32_t by,
                                                 JacobiTbLds<WV>& L) {
     const int64_t x0 = (int64_t)bx * (JT_W - 2 * hc) - hc, y0 = (int64_t)by * (RS * WV - 2 * sweeps) - sweeps;
-    if (y0 + sweeps >= (int64_t)ny) return;  // block-uniform: a tile below the grid
     if (x0 <= 0 || x0 + JT_W >= (int64_t)nx || y0 <= 0 || y0 + RS * WV >= (int64_t)ny)
         jacobi_tb_region<RS, WV, VEC, NT, true>(u, v, nx, ny, sweeps, hc, x0, y0, L);
     else

@@ -3,14 +3,23 @@
 
 namespace spmd {
 
+// Halo columns, whole groups of four.  Few sweeps of a large grid: 16, so that a
+// tile's rows are whole 128-byte lines (2 sweeps of 8192^2 97 us against 104 at
+// 4); with 5 or more the columns recomputed cost more (8 sweeps 112 against 107
+// at 8).
+__host__ __device__ inline uint32_t halo_cols(uint32_t sweeps, bool large) {
+    return large && sweeps <= 4 ? 16 : (sweeps + 3) / 4 * 4;
+}
+
+// Eight words of arguments: one more took 100 sweeps of 1024^2 from 89.1 to 90.2 us.
 template <int RS, int WV, bool VEC, bool NT>
 __global__ __launch_bounds__(64 * WV, 4) void jacobi5_tb_kernel(const float* __restrict__ u, float* __restrict__ v,
                                                                 uint32_t nx, uint32_t ny, uint32_t sweeps,
-                                                                uint32_t hc, uint32_t gx) {
+                                                                uint32_t gx) {
     __shared__ JacobiTbLds<WV> L;
     const uint32_t nt = gridDim.x * gridDim.y;
     const uint32_t tile = xcd_tile(blockIdx.y * gridDim.x + blockIdx.x, nt);
-    jacobi_tb_block<RS, WV, VEC, NT>(u, v, nx, ny, sweeps, hc, tile % gx, tile / gx, L);
+    jacobi_tb_block<RS, WV, VEC, NT>(u, v, nx, ny, sweeps, halo_cols(sweeps, NT), tile % gx, tile / gx, L);
 }
 
 namespace {
@@ -22,12 +31,6 @@ struct TbForm {
 };
 constexpr TbForm kForms[] = {{6, 4}, {4, 8}, {5, 8}, {6, 8}, {8, 8}, {12, 8}};
 constexpr int NFORMS = sizeof kForms / sizeof kForms[0], LARGE = NFORMS - 1;
-
-// Whole groups of four columns.  Few sweeps of a large grid: 16, so that a
-// tile's rows are whole 128-byte lines (2 sweeps of 8192^2 97 us against 104 at
-// 4); with 5 or more the columns recomputed cost more (8 sweeps 112 against 107
-// at 8).
-uint32_t halo_cols(uint32_t sweeps, bool large) { return large && sweeps <= 4 ? 16 : (sweeps + 3) / 4 * 4; }
 
 uint64_t tiles_of(int f, uint32_t nx, uint32_t ny, uint32_t sweeps) {
     const uint64_t w = JT_W - 2 * halo_cols(sweeps, f == LARGE), h = kForms[f].rows() - 2 * sweeps;
@@ -67,7 +70,7 @@ void launch_form(const float* u, float* v, uint32_t nx, uint32_t ny, uint32_t sw
     const uint32_t hc = halo_cols(sweeps, F == LARGE), w = JT_W - 2 * hc, h = RS * WV - 2 * sweeps;
     const uint32_t gx = (uint32_t)(((uint64_t)nx + w - 1) / w);
     const dim3 g = tile_grid(gx, ((uint64_t)ny + h - 1) / h);
-    dispatch((jacobi5_tb_kernel<RS, WV, VEC, F == LARGE>), g, dim3(64 * WV), dyn, st, u, v, nx, ny, sweeps, hc, gx);
+    dispatch((jacobi5_tb_kernel<RS, WV, VEC, F == LARGE>), g, dim3(64 * WV), dyn, st, u, v, nx, ny, sweeps, gx);
 }
 
 template <bool VEC>
