@@ -32,6 +32,13 @@
  *    zero-filled once before its first use, and is left reusable by every
  *    launch that completes.  Two launches in flight at the same time must
  *    not share a workspace.
+ *  - Grid and block say how the work is cut: what a block owns, and with it
+ *    the partials, the workspace and which shapes are accepted.  Which
+ *    workgroups run it is the library's choice by the sizes (several logical
+ *    blocks to a workgroup, as in coarse-grained fetching, Section IV-A, a
+ *    wave each, or other tiles); results do not depend on it.  SCAN, COMPACT
+ *    and HIST launches with dyn_shmem > 0 run in blocks as launched: what they
+ *    reserve bounds how many of those blocks a compute unit takes.
  *  - The library owns only immutable state (dispatch tables, device
  *    attributes) and one device error word per device, which kernels set on
  *    an internal failure and spmd_sync reports and clears.
@@ -82,26 +89,30 @@ enum {
      * Block b owns x[b*S, min((b+1)*S, n)), S = 4*ceil(n / (4G))
      * (SPMD_ERR_INVALID_DIM when S does not fit 32 bits: G = 1 and
      * n > 2^32 - 4); partials[b] = sum of its elements, *out = sum of all n
-     * elements. */
+     * elements.  Short segments run with a wave each. */
     SPMD_REDUCE_I32 = 1,
 
     /* Inclusive prefix sum: y[i] = x[0] + ... + x[i] (mod 2^32), single
      * pass with decoupled look-back across tiles.
      * args: const int32_t* x, int32_t* y, uint32_t n, void* workspace
-     * grid (G,1,1), block (B,1,1), B in {64,128,256,512,1024}.  Block g
-     * (in the order blocks start) scans a tile of B*I consecutive elements,
-     * I = the smallest power of two >= ceil(n / (G*B)); I <= 32 (I <= 128 for B <= 512).
+     * grid (G,1,1), block (B,1,1), B in {64,128,256,512,1024}.  A block's
+     * tile is B*I consecutive elements, I = the smallest power of two >=
+     * ceil(n / (G*B)); I <= 32 (I <= 128 for B <= 512).  Tiles are taken in
+     * order; with dyn_shmem 0, small ones of 2^18 elements or more are taken
+     * several at a time (tiles of 512 x 16 to 512 x 128).
      * x and y may not overlap (SPMD_ERR_ARGS). */
     SPMD_SCAN_I32 = 2,
 
     /* 256-bin histogram of keys & 255 with per-block LDS sub-histograms
      * (LDS atomics) flushed to hist with global atomics.  hist is
-     * overwritten: the library clears it in stream order before counting.
+     * overwritten: cleared in stream order before counting, or written by
+     * the one block that few keys take.
      * args: const uint32_t* keys, uint32_t* hist, uint32_t n
      * grid (G,1,1), block (B,1,1), B a power of two in [64, 1024].  Block b
-     * counts keys[b*S, min((b+1)*S, n)), S = 4*ceil(n / (4G))
+     * owns keys[b*S, min((b+1)*S, n)), S = 4*ceil(n / (4G))
      * (SPMD_ERR_INVALID_DIM when S does not fit 32 bits: G = 1 and
-     * n > 2^32 - 4). */
+     * n > 2^32 - 4); with dyn_shmem 0 the keys are counted by as many blocks
+     * of 1024 threads as their number pays for, whatever G and B. */
     SPMD_HIST256_U32 = 3,
 
     /* One sweep of the 5-point Laplace-Jacobi stencil on an ny x nx
@@ -111,18 +122,22 @@ enum {
      * the neighbours' rows in registers.
      * args: const float* u, float* u_next, uint32_t nx, uint32_t ny
      * block (BX,BY,1) with (BX,BY) in {(16,16), (32,8), (64,1), (64,2),
-     * (64,4), (64,8), (128,2), (128,4), (256,1)}; grid (GX,GY,1) with GX*BX >= nx; each
-     * thread computes C cells down its column, C = the smallest power of
+     * (64,4), (64,8), (128,2), (128,4), (256,1)}; grid (GX,GY,1) with GX*BX >= nx; a
+     * thread owns C cells down its column, C = the smallest power of
      * two >= ceil(ny / (GY*BY)), C <= 16.  u and u_next may not overlap. */
     SPMD_JACOBI5_F32 = 4,
 
     /* C = A * B, fp32 row-major, fp32 accumulation on the matrix cores
-     * (v_mfma_f32_32x32x2f32), LDS-staged T x T output tiles.
+     * (v_mfma_f32_32x32x2f32).
      * args: const float* A, const float* B, float* C, uint32_t M,
      *       uint32_t N, uint32_t K
-     * block (256,1,1); grid (GX,GY,1); the tile edge T is the smallest of
-     * {64, 128, 256} with GX*T >= N and GY*T >= M (at 256 each wave holds
-     * a 128 x 128 block of C in accumulator registers, one wave per SIMD). */
+     * block (256,1,1); grid (GX,GY,1); the launch's tile edge T is the
+     * smallest of {64, 128, 256} with GX*T >= N and GY*T >= M.  It says what
+     * a block owns; tiles of 32 to 256 are run, staged in LDS or with K split
+     * over a block's waves, as M, N and K suit.  dyn_shmem has to fit beside
+     * the stages of the launch's tile (SPMD_ERR_SHMEM): 512 T bytes, 98320 at
+     * T = 256, for A and B 16-byte aligned and K and N multiples of 4, else
+     * 256 (T + 4). */
     SPMD_GEMM_F32 = 5,
 
     /* Conformance of the 32-lane warp operations on half-wavefronts.
@@ -161,7 +176,9 @@ enum {
      *       uint32_t t, void* workspace
      * grid (G,1,1), block (B,1,1), B a power of two in [64, 1024]; each
      * thread handles I items, I = the smallest power of two >=
-     * ceil(n / (G*B)), I <= 32 (I <= 64 for B <= 512).  workspace:
+     * ceil(n / (G*B)), I <= 32 (I <= 64 for B <= 512); as for SCAN, with
+     * dyn_shmem 0 the tiles of 2^18 elements or more may be larger (512 x 16
+     * to 1024 x 32).  workspace:
      * spmd_workspace_size() bytes,
      * 16-byte aligned, zero-filled before first use, then reusable as for
      * SCAN.  y must hold n elements; x may overlap neither y nor count

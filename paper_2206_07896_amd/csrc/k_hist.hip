@@ -29,7 +29,9 @@ __global__ __launch_bounds__(HIST_THREADS) void hist256_alone_kernel(const uint3
 }
 
 // Blocks (of 1024 threads) for n keys on the device's CUs; 0: one block alone,
-// without the clear.  The counts do not depend on the launch's grid, but every
+// without the clear.  (Not for a launch with dynamic shared memory, here as for
+// scans and compactions: what it reserves bounds how many of its own blocks a CU
+// takes, and would mean something else in others.)  The counts do not depend on the launch's grid, but every
 // block adds up to 256 bins to the same 1 KiB, 18 billion a second in all:
 // launched in 1024 blocks 2^16 keys took 22 us, 2^20 23, 2^24 27 to 31; in 64
 // blocks of 256 2^24 65, 2^26 252.  Fewer blocks read more slowly.  The fastest,

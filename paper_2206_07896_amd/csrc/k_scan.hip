@@ -110,7 +110,8 @@ static void launch_b(uint32_t I, uint32_t G, size_t dyn, hipStream_t s, const in
 // 2^21, to 2^23 and on: 512 x 16 (2^19 6.4 us; 256 x 8 8.8), 512 x 32 (2^21 9.1;
 // 512 x 16 10.2, 256 x 16 15.9), 512 x 64 (2^23 16.4; 512 x 16 29.7), 512 x 128
 // (2^24 26.2; 512 x 64 30.9).  Below 2^18 no tile gains more than 5%.  A larger
-// tile needs fewer status words, so any launch's workspace holds them.
+// tile needs fewer status words, so any launch's workspace holds them.  A launch
+// with dynamic shared memory keeps its blocks, which it bounds the number of.
 static uint32_t scan_items(uint32_t n) {
     return n < (1u << 18) ? 0u : n < (1u << 20) ? 16u : n < (1u << 22) ? 32u : n < (1u << 24) ? 64u : 128u;
 }

@@ -620,7 +620,6 @@ __host__ __device__ inline ChooseLayout choose_layout(uint32_t k_models, uint32_
 }
 
 struct ChooseArgs {
-    const float* params;
     uint32_t k_models, c;
     const MlpWeights* W;
     const float *shared, *cand, *feat;
@@ -699,7 +698,7 @@ __global__ __launch_bounds__(CH_THREADS) void mlp_choose_kernel(
     uint64_t* masks = reinterpret_cast<uint64_t*>(smem + at.mask);
     uint16_t* list = reinterpret_cast<uint16_t*>(smem + at.list);
     uint32_t* length = reinterpret_cast<uint32_t*>(smem + at.list - 4);
-    const ChooseArgs A{params, k_models, c, W, shared, cand, feat, list, group};
+    const ChooseArgs A{k_models, c, W, shared, cand, feat, list, group};
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     for (uint32_t k = 0; k < k_models; ++k) stage_weights<CH_THREADS>(W[k], params + k * NP);
