@@ -151,9 +151,11 @@ __device__ __forceinline__ void run_logical_block(const BatchDesc& d, uint32_t b
 // strip, a quarter of its lanes, 1.10; of 512 x 8 0.21 and 0.30).  Every cell is
 // computed as in its own block.  Against LDS tiles with a barrier per tile: 400 mixed launches of
 // up to 2^22 elements 340 us (375), 2000 of up to 2^20 419 us (454), 2000 of up
-// to 2^22 the same 1180; the stencil queue of those, 2.2 GB in 0.50 ms, is held
+// to 2^22 1164 (1178); the stencil queue of those, 2.2 GB in 0.50 ms, is held
 // by HBM's rate for many rows of odd widths at once (4.6 TB/s), not by its
-// traffic (1.1 of the least).
+// traffic (1.1 of the least).  One large grid by itself takes 0.75 of the tiles'
+// time over all schedules, but up to 1.2 of it in some (4096^2 in (256, 4, 16) 31.5
+// us a sweep against 26.5, in (256, 8, 32) 35.7 against 68.2).
 template <int B, int C>
 __device__ __forceinline__ void jacobi_chunk(const BatchDesc& d, uint32_t first, uint32_t last) {
     const float* u = reinterpret_cast<const float*>(d.in);

@@ -11,10 +11,10 @@
 //
 // All loads of a strip are in flight at once and nothing is shared between
 // waves, so there is no LDS tile, no barrier, and one body for every block
-// shape, width and alignment.  Bound by memory.  A sweep of 2001 x 1999: 6.6 us,
-// 9.9 with an LDS tile that four 4-byte loads per thread and row filled; 4099 x
-// 4001 21.7 us against 31.7; 8190 x 8191 94 us against 101; 8192^2 (5.9 to 6.1
-// TB/s) as with a tile that 16-byte loads filled, 88 us.
+// shape, width and alignment.  Bound by memory.  A sweep on buffers that no cache
+// holds: 2001 x 1999 6.1 us, 8.2 with an LDS tile that four 4-byte loads per thread
+// and row filled; 4099 x 4001 27.7 us against 30.2; 8190 x 8191 89.5 against 101;
+// 8192^2 84.4 us (6.4 TB/s) against 86.5 with a tile that 16-byte loads filled.
 #pragma once
 #include <type_traits>
 #include <utility>

@@ -4,7 +4,8 @@
 // or, where segments are short, by one wave (reduce_waves); the workgroup that
 // takes the last completion ticket then sums all workgroups' totals into *out
 // and re-arms the ticket counter.  Loads are 16 bytes per lane at any alignment
-// (2^24 elements one element off 16 bytes, a word per lane: 68 us against 45).
+// (2^24 elements one element off 16 bytes in 4096 blocks of 256: 11.6 us, as on 16
+// bytes; a word per lane 16.0).
 //
 // gfx950 mapping of the block tree: levels whose stride is >= 64 combine
 // values held by different waves and go through LDS with a barrier; levels

@@ -39,14 +39,14 @@ uint64_t tiles_of(int f, uint32_t nx, uint32_t ny, uint32_t sweeps) {
 
 // The form for a grid.  Taller regions recompute fewer halo rows but make
 // fewer tiles.  96 rows where their tiles fill the chip's three resident
-// blocks per CU and the grid is at least four tiles high; there it is at least
-// 50 MB and stores that pass the L2
-// by are the faster ones (8192^2 on buffers that no cache holds, 8 sweeps: 107
-// us against 115 with plain stores and 129 with the loads passing the L2 by).
-// Flat grids leave most of a region's rows outside: one row of 2^20 takes 69 us
-// in 96-row regions for 4 sweeps, 16.5 in 24; 4 x 300 000 24.5 and 8.0; 300 x
-// 65 536 30.3 and 28.4 in 48 (1000 x 16 384 within 7% either way).
-// Below that the rows that the busiest CU works on decide: 11 sweeps of
+// blocks per CU and the grid is at least four of them high; there it is at
+// least 50 MB and stores that pass the L2 by are the faster ones (8192^2 on
+// buffers that no cache holds, 8 sweeps: 107 us against 115 with plain stores
+// and 129 with the loads passing the L2 by).  Flat grids leave most of a
+// region's rows outside: 4 sweeps of one row of 2^20 take 69 us in 96-row
+// regions, 16.5 in 24; of 4 x 300 000 24.5 and 8.0; of 300 x 65 536 30.3, and 28.4
+// in 48 (1000 x 16 384 within 7% either way).
+// Otherwise the rows that the busiest CU works on decide: 11 sweeps of
 // 1024^2 take 9.9 us at 48 rows (200 tiles), 11.7 at 40 (285), 12.2 at 32
 // (515) and 11.5 at 64 (125); of 128^2, 6.5 us at 24 rows and 10.5 at 64; of
 // 2048^2, 18.2 us at 64 rows, 18.5 at 48, 19.7 at 40.

@@ -91,8 +91,8 @@ static void launch_reduce_b(uint32_t G, size_t dyn, hipStream_t s, const int32_t
 // Logical blocks in flight per wave where a wave takes them (0: a workgroup
 // does).  A block's own threads have nothing to do where its segment is short:
 // 2^20 elements in 4096 blocks of 256 threads are 64 loads of 16 bytes a block,
-// 7.0 us, 5.6 with a wave each; 2^22 in 4096 blocks of 1024 25 and 7.6, 2^24 in
-// 16 384 of 512 44.7 and 14.7, 2^26 in 65 536 of 256 70.5 and 46.1.  From 4096
+// 6.4 us, 4.8 with a wave each; 2^22 in 4096 blocks of 1024 32.6 and 5.6, 2^24 in
+// 16 384 of 512 42.8 and 11.0, 2^26 in 65 536 of 256 70.4 and 48.4.  From 4096
 // elements on a block is as fast (2^24 in 4096 of 256: 14.5 us both ways), then
 // faster (2^26: 46.2 against 52.8), with few blocks sooner (2^20 in 256 of 1024:
 // 6.0 against 6.75, 2^18 in 256 of 128: 5.5 against 5.1).  Two blocks to a wave
@@ -130,7 +130,8 @@ int launch_reduce_i32(const LaunchCtx& c) {
         return e == hipSuccess ? SPMD_OK : hip_fail(e);
     }
     // Sixteen blocks to a CU are enough waves at 256 threads each; more threads
-    // only share the same loads (2^26 in 4096 blocks of 1024: 73 us, of 256 46).
+    // only share the same loads (2^26 in 4096 blocks of 1024: 44.6 us on 256 threads
+    // each, 114 on their own).
     switch (G >= 16u * (uint32_t)cus ? std::min(B, 256u) : B) {
     case 64: launch_reduce_b<64>(G, c.dyn_shmem, c.stream, x, partials, out, n, seg, ws, err, cus); break;
     case 128: launch_reduce_b<128>(G, c.dyn_shmem, c.stream, x, partials, out, n, seg, ws, err, cus); break;

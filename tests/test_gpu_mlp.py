@@ -350,8 +350,8 @@ def test_choose_batch_matches_oracle(L, slack):
 
 @pytest.mark.parametrize("n", [65, 255, 257, 64 * 512 + 1])
 def test_training_kernels_at_tile_edges(L, n):
-    """Row counts around the forward block (256 rows), the backward chunk (64)
-    and the chunk after the last block's first (512 blocks)."""
+    """Row counts around the forward block (256 rows), the backward chunk (64
+    rows up to 16 384, then 128) and one past a chunk to each of its 256 blocks."""
     import torch
 
     say("mlp tile edges", n)
@@ -386,8 +386,8 @@ def test_training_kernels_at_block_edges(L, n):
 def test_choose_is_the_least_forward_prediction(L, m, c, k):
     """Every (launch, candidate) through the forward kernel, the models' mean
     and the first least one on the host: choose gives the same bits, around
-    one launch per block, a block's second group of launches (more than 16)
-    and candidate counts off the wave's 64."""
+    one launch per block, 17 launches to a block in one group, and candidate
+    counts off the wave's 64."""
     import torch
 
     say("mlp choose against forward", m, c, k)

@@ -82,8 +82,8 @@ def test_warp_conformance(spmd, grid, block):
 
 @pytest.mark.parametrize("n,grid,block", [(1, 1, 64), (1000, 3, 64), (12345, 37, 256), (1 << 16, 64, 1024),
                                           (100003, 4096, 128), (1 << 20, 4096, 256),
-                                          # grids past the resident workgroups: 2, 4 and 8 logical blocks per
-                                          # workgroup, with ragged and empty trailing segments
+                                          # short segments on large grids, a wave each, two at once, with ragged
+                                          # and empty trailing segments
                                           (3 * (1 << 20) + 1, 8192, 256), ((1 << 20) + 3, 16384, 256),
                                           (500001, 8192, 64), (1 << 22, 65536, 512)])
 def test_reduce(spmd, n, grid, block):
@@ -104,9 +104,9 @@ def test_reduce_wrapping_and_unaligned(spmd):
     n = 50001
     x = synth.uniform_int32(99, n, -(2**31), 2**31 - 1)
     xt = dev(x)
-    for grid in (13, 4096):  # one logical block per workgroup, then two
+    for grid in (13, 4096):  # a workgroup per logical block, then a wave
         want_p, want_t = oracle.reduce_i32(x[1:], grid, 256)
-        p, out = spmd.ops.reduce_i32(xt[1:], grid, 256)  # 4-byte offset: scalar load path
+        p, out = spmd.ops.reduce_i32(xt[1:], grid, 256)  # 4-byte offset: 16-byte loads off 16 bytes
         spmd.sync()
         assert int(host(out)[0]) == want_t, grid
         assert np.array_equal(host(p), want_p), grid
@@ -465,9 +465,8 @@ SHAPES = [(16, 16), (32, 8), (64, 4), (64, 8), (128, 2), (128, 4), (256, 1)]
 @pytest.mark.parametrize("block", SHAPES)
 @pytest.mark.parametrize("cells", [1, 4])
 def test_jacobi_one_sweep(spmd, block, cells):
-    # Block rows of 4 to 64 rows run 256 columns per workgroup: nx % 4 == 0 with aligned rows
-    # takes the 16-byte form, any other nx the general-width form (four columns 64 apart);
-    # block rows of 1 or 2 rows take the scalar body.
+    # Every launched block shape runs as strips of 256 columns and two rows to a wave, a lane per
+    # cell where there are fewer than four columns.
     # degenerate grids last: one row or column, or two (every cell a border cell, copied)
     for (ny, nx) in [(33, 70), (130, 257), (3, 3), (33, 68), (130, 520), (5, 4), (64, 260),
                      (1, 1), (1, 300), (300, 1), (2, 2), (2, 513), (1, 4), (2, 260)]:
@@ -480,10 +479,10 @@ def test_jacobi_one_sweep(spmd, block, cells):
 
 
 @pytest.mark.parametrize("ny,nx", [(5, 255), (5, 256), (6, 258), (7, 259), (9, 511), (8, 513), (70001, 3), (300000, 4),
-                                   (4097, 8190), (4096, 8192), (4100, 8191)])  # the last: one row per wave
+                                   (4097, 8190), (4096, 8192), (4100, 8191)])  # the last: one row per wave, the tall ones a lane per column
 def test_jacobi_strips(spmd, ny, nx):
     """Strip ends at every remainder of a lane's four columns, tall grids and
-    both row counts; cells past the grid stay as they were."""
+    one and two rows to a wave; cells past the grid stay as they were."""
     import torch
 
     say("jacobi strips", ny, nx)
@@ -568,7 +567,7 @@ def test_fused_sweeps_of_any_height(spmd):
 
 def test_jacobi_misaligned_rows(spmd):
     """nx a multiple of 4 but the grid one float into its buffer: rows are
-    not 16-byte aligned, so the general-width form runs."""
+    not 16-byte aligned."""
     import torch
 
     ny, nx = 70, 260
@@ -698,9 +697,9 @@ def _gemm_gate(C, c64, K):
 @pytest.mark.parametrize("tile", [64, 128, 256])
 @pytest.mark.parametrize("M,N,K", [(1, 1, 1), (64, 64, 16), (65, 63, 17), (128, 96, 130), (3, 200, 5), (257, 130, 64),
                                    (512, 512, 512),
-                                   # 16-byte rows (N, K multiples of 4): the direct-to-LDS form, with
-                                   # K below one slice, K tails of 4 / 8 / 12, slice counts on both
-                                   # sides of its pipeline's main loop, and rows / columns past C
+                                   # 16-byte rows (N, K multiples of 4), with K below a 16-deep slice,
+                                   # K tails of 4 / 8 / 12, and rows / columns past C (shapes this small
+                                   # run on 32 x 32 tiles; the staged forms: test_gemm_forms)
                                    (1, 4, 4), (33, 68, 8), (100, 124, 12), (64, 64, 32), (70, 260, 48),
                                    (130, 132, 96), (129, 256, 112), (200, 196, 116), (256, 256, 200),
                                    (300, 300, 1028)])
@@ -720,12 +719,12 @@ def test_gemm_shapes(spmd, tile, M, N, K):
 @pytest.mark.parametrize("M,N,K,shift", [
     # 32 x 32 tiles, K split over 8 waves: one group of 8 per wave, fewer, a tail of K % 8
     (31, 33, 7, 0), (33, 35, 8, 0), (97, 61, 129, 0), (40, 40, 260, 1),
-    # 64 x 64 tiles, K split over 4 waves: rows at any alignment
+    # 64 x 64 tiles staged in LDS, rows at any alignment
     (1000, 901, 6, 0), (997, 905, 35, 0), (1000, 904, 160, 3),
-    # staged in LDS, 16-byte rows: tiles of 64, 128 and 256, below one slice, with tails, past the pipeline's main loop
+    # the same with 16-byte rows, tiles of 64 and 128: below one slice, with tails, past the pipeline's main loop
     (1020, 1000, 4, 0), (1020, 1000, 100, 0), (1023, 1004, 256, 0), (2040, 2044, 12, 0), (2041, 2036, 132, 0),
     (4092, 4088, 24, 0), (4089, 4096, 120, 0),
-    # the same without 16-byte rows (4-byte loads): tiles of 128 and 256
+    # without 16-byte rows again (4-byte loads), large
     (2045, 2047, 5, 0), (2046, 2045, 131, 0), (4090, 4095, 19, 0), (4090, 4093, 113, 0), (4096, 4096, 64, 1)])
 def test_gemm_forms(spmd, M, N, K, shift):
     """Each form at sizes that its rule takes, at the edges of tiles, slices
