@@ -61,7 +61,8 @@ struct alignas(16) BatchDesc {
     uint32_t aux;      // REDUCE/HIST: elements per block; JACOBI: blocks per row
     uint64_t in, out;
     uint64_t ws;       // run-area scratch of this instance
-    uint32_t pad[2];
+    uint32_t keep;     // JACOBI: stores that leave the output in the caches (kept_sweeps)
+    uint32_t pad;
 };
 static_assert(sizeof(BatchDesc) == 64, "descriptor is 64 bytes");
 
@@ -154,10 +155,10 @@ __device__ __forceinline__ void run_logical_block(const BatchDesc& d, uint32_t b
 // to 2^22 1164 (1178); the stencil queue of those, 2.2 GB in 0.50 ms, is held
 // by HBM's rate for many rows of odd widths at once (4.6 TB/s), not by its
 // traffic (1.1 of the least).  One large grid by itself takes 0.75 of the tiles'
-// time over all schedules, but up to 1.2 of it in some (4096^2 in (256, 4, 16) 31.5
-// us a sweep against 26.5, in (256, 8, 32) 35.7 against 68.2).
-template <int B, int C>
-__device__ __forceinline__ void jacobi_chunk(const BatchDesc& d, uint32_t first, uint32_t last) {
+// time over all schedules, but up to 1.15 of it in some (8192^2 in (256, 4, 32) 143
+// us a sweep against 126, in (256, 8, 32) 134 against 149).
+template <int B, int C, bool KEEP>
+__device__ __forceinline__ void jacobi_chunk_of(const BatchDesc& d, uint32_t first, uint32_t last) {
     const float* u = reinterpret_cast<const float*>(d.in);
     float* v = reinterpret_cast<float*>(d.out);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -170,8 +171,16 @@ __device__ __forceinline__ void jacobi_chunk(const BatchDesc& d, uint32_t first,
         const int64_t x0 = 64 * (int64_t)bx, xe = x0 + 64 * run;
         if (y0 >= (int64_t)d.ny) continue;
         if (run == 1) jacobi_narrow<C>(u, v, d.n, d.ny, x0, xe < (int64_t)d.n ? xe : (int64_t)d.n, y0);
-        else jacobi_strip<C>(u, v, d.n, d.ny, x0, xe < (int64_t)d.n ? xe : (int64_t)d.n, y0);
+        else jacobi_strip<C, KEEP>(u, v, d.n, d.ny, x0, xe < (int64_t)d.n ? xe : (int64_t)d.n, y0);
     }
+}
+
+// The two kinds of store in bodies of their own: a choice at each store comes out
+// as plain stores for both.
+template <int B, int C>
+__device__ __forceinline__ void jacobi_chunk(const BatchDesc& d, uint32_t first, uint32_t last) {
+    if (d.keep) jacobi_chunk_of<B, C, true>(d, first, last);
+    else jacobi_chunk_of<B, C, false>(d, first, last);
 }
 
 // REDUCE and HIST: the logical blocks of one fetch cover one contiguous
@@ -826,6 +835,29 @@ void fuse_chains(const spmd_batch_item* items, std::vector<BatchSegment>& seg, b
     }
 }
 
+// Stencil instances whose output a later level reads, input and output together
+// no more than the 256 MB cache holds: their stores leave it there (two sweeps of
+// 4096^2 in (256, 4, 16) 49.4 us, 63 with stores that pass the caches by).  All
+// others pass them by: 2000 independent launches 1164 us, 1188 with plain stores;
+// two sweeps of 8192^2 by schedule 256 and 250, 210 and 217.
+constexpr uint64_t KEEP_BYTES = 256ull << 20;
+
+std::vector<uint8_t> kept_sweeps(const spmd_batch_item* items, const std::vector<uint32_t>& level, int n) {
+    std::vector<uint8_t> keep(n, 0);
+    std::vector<std::pair<uintptr_t, uint32_t>> reads;  // (input, level), levels above 0
+    for (int i = 0; i < n; ++i)
+        if (level[i] > 0) reads.emplace_back((uintptr_t)items[i].in, level[i]);
+    std::sort(reads.begin(), reads.end());
+    for (int i = 0; i < n && !reads.empty(); ++i) {
+        if (items[i].kernel_id != SPMD_JACOBI5_F32) continue;
+        const uint64_t bytes = 4ull * items[i].n * items[i].ny;
+        if (2 * bytes > KEEP_BYTES) continue;
+        const auto at = std::lower_bound(reads.begin(), reads.end(), std::make_pair((uintptr_t)items[i].out, level[i] + 1));
+        keep[i] = at != reads.end() && at->first == (uintptr_t)items[i].out;
+    }
+    return keep;
+}
+
 template <int CLS, int B>
 int occupancy(int* nb) {
     hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(nb, batch_persistent_kernel<CLS, B>, B, 0);
@@ -1082,6 +1114,7 @@ int spmd_batch_create_dep(const spmd_batch_item* items, const spmd_schedule* sch
     std::vector<std::vector<uint32_t>> cmap(nseg);
     for (size_t k = 0; k < nseg; ++k) cmap[k].reserve(b->seg[k].chunks);
     std::vector<std::pair<uint32_t, uint64_t>> hist_lv;  // (level, bins) of queued HIST instances
+    const std::vector<uint8_t> keep = kept_sweeps(items, L.level, n);
     size_t run = L.cursor_bytes, each = L.each_off;
     b->each_ws.assign(n, 0);
     b->each_partials.assign(n, 0);
@@ -1105,7 +1138,10 @@ int spmd_batch_create_dep(const spmd_batch_item* items, const spmd_schedule* sch
         case SPMD_REDUCE_I32:
         case SPMD_HIST256_U32: d.aux = s.block * s.items; break;
         case SPMD_SCAN_I32: break;
-        case SPMD_JACOBI5_F32: d.aux = (uint32_t)cdiv(it.n, 64); break;
+        case SPMD_JACOBI5_F32:
+            d.aux = (uint32_t)cdiv(it.n, 64);
+            d.keep = keep[i];
+            break;
         }
         if (it.kernel_id == SPMD_HIST256_U32 && !is_direct(s))  // own grids clear their bins themselves
             hist_lv.emplace_back(L.level[i], (uint64_t)(uintptr_t)it.out);

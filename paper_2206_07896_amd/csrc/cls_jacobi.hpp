@@ -95,8 +95,8 @@ __device__ __forceinline__ void jacobi_thin(const float* __restrict__ u, float* 
 }
 
 // One wave: columns [x0, xe), xe <= x0 + 256, of rows [y0, min(y0 + R, NY)),
-// y0 < NY.  xe is NX or x0 plus a multiple of 4.
-template <int R>
+// y0 < NY.  xe is NX or x0 plus a multiple of 4.  KEEP: v is read again soon.
+template <int R, bool KEEP = false>
 __device__ __forceinline__ void jacobi_strip(const float* __restrict__ u, float* __restrict__ v, int64_t NX, int64_t NY,
                                              int64_t x0, int64_t xe, int64_t y0) {
 #pragma clang fp contract(off)
@@ -157,7 +157,8 @@ __device__ __forceinline__ void jacobi_strip(const float* __restrict__ u, float*
             // nontemporal: no part of this sweep reads v again (2001 x 1999
             // 6.6 us against 8.2, 8192^2 88 against 90)
             if (own && full) {
-                __builtin_nontemporal_store(o, reinterpret_cast<f32x4_a4*>(p));
+                if constexpr (KEEP) *reinterpret_cast<f32x4_a4*>(p) = o;
+                else __builtin_nontemporal_store(o, reinterpret_cast<f32x4_a4*>(p));
             } else if (own) {
                 p[0] = o.x;
                 if (gx + 1 < NX) p[1] = o.y;

@@ -548,6 +548,40 @@ def test_stencil_chains_under_a_worker_cap(spmd, wpc, bpf):
         assert np.array_equal(host(bufs[(sweeps - back) % 2]), oracle.jacobi5_f32_sweeps(u, sweeps - back)), back
 
 
+@pytest.mark.parametrize("block,cells", [(64, 1), (128, 8), (256, 2), (512, 4), (512, 8)])
+@pytest.mark.parametrize("nx,ny", [(64, 70), (515, 77), (1024, 130), (4100, 4093)])
+def test_stencils_that_later_levels_read(spmd, block, cells, nx, ny):
+    """Sweeps whose output a later level reads (a reduction, another sweep) keep
+    it in the caches, the last one's nobody does; nothing beside them changes."""
+    import torch
+
+    say("stencils that later levels read", block, cells, nx, ny)
+    n = nx * ny
+    u = synth.uniform_f32(0xC4A5 + nx, n).reshape(ny, nx)
+    store = [torch.full((n + 8,), -2.0, device="cuda") for _ in range(4)]
+    bufs = [s[3:3 + n] for s in store]
+    bufs[0].copy_(torch.from_numpy(u.ravel()))
+    total = torch.empty(1, dtype=torch.int32, device="cuda")
+    J = spmd.JACOBI5_F32
+    items = [(J, nx, ny, 256, bufs[0], bufs[1]), (spmd.REDUCE_I32, n, 1, 256, bufs[1].view(torch.int32), total),
+             (J, nx, ny, 256, bufs[1], bufs[2]), (J, nx, ny, 256, bufs[2], bufs[3])]
+    want = [oracle.jacobi5_f32_sweeps(u, k) for k in range(4)]
+    for bpf in (1, 3, 32):
+        for q in bufs[1:]:
+            q.fill_(-1.0)
+        b = spmd.batch.Batch(items, [(block, cells, bpf), (256, 4, 8), (block, cells, bpf), (block, cells, bpf)],
+                             deps=[None, 0, 0, 2])
+        b.launch()
+        spmd.sync()
+        b.close()
+        for k in (1, 2, 3):
+            got = host(store[k])
+            assert np.array_equal(got[3:3 + n].reshape(ny, nx), want[k]), (bpf, k)
+            assert (got[:3] == -2.0).all() and (got[3 + n:] == -2.0).all(), (bpf, k)
+        bits = host(store[1])[3:3 + n].view(np.int32)
+        assert int(host(total)[0]) == int(bits.astype(np.int64).sum().astype(np.int32)), bpf
+
+
 @pytest.mark.parametrize("count,log2n", [(1, 10), (3, 10), (5, 12), (30, 10), (30, 21)])
 def test_grids_side_by_side(spmd, count, log2n):
     """Independent instances that run as their own grids: in a row, on a few
