@@ -181,13 +181,16 @@ def launch(kernel, grid, block, dyn_shmem: int = 0, args=(), stream=None, events
     stream), to be measured from an earlier event."""
     kid = KERNELS[kernel] if isinstance(kernel, str) else int(kernel)
     rc = None
-    if not isinstance(args, (list, tuple)):  # any iterable, an iterator among them
+    try:
+        nargs = len(args)
+    except TypeError:  # an iterator
         args = list(args)
-    if events is None and len(args) == _NARGS.get(kid):
+        nargs = len(args)
+    if events is None and nargs == _NARGS.get(kid):
         rc = _launch.launch(kid, grid, block, dyn_shmem, args, _stream_handle(stream))
         if rc == SPMD_OK:
             return
-    arr, keep = pack_args(kid, args)
+    arr, keep = pack_args(kid, list(args))
     argv = ctypes.cast(arr, ctypes.POINTER(ctypes.c_void_p))
     if events is None:
         if rc is None:  # not in the plain forms
